@@ -8,24 +8,29 @@
 // Solving it on the GPU keeps the n x n Hessian on the device (only dx
 // returns to the host), the step the paper names as future work.
 //
-// Dense Cholesky M = L L^T in FP64, blocked right-looking with 64-column
-// panels; B independent systems per call (grid dimension y / x):
-//   * kkt_assemble: L = M (full square, row-major), info = 0;
-//   * per panel k: kkt_potrf factors the 64 x 64 diagonal block in LDS and
-//     writes it back; a pivot that is not positive (or not finite) stops that
-//     system with info = its global order (LAPACK's convention: the leading
-//     minor of that order is not positive definite); kkt_trsm then solves
-//     each 64-row block below against it (L_ik = A_ik L_kk^-T, one row per
-//     thread, in LDS);
-//   * kkt_update: A_IJ -= L_Ik L_Jk^T on the lower block triangle of the
-//     trailing matrix, one 64 x 64 tile per workgroup, 4 x 4 outputs per
-//     thread from two panel blocks staged in LDS;
-//   * kkt_solve: forward substitution L y = r then back substitution
-//     L^T x = y, one workgroup per system: each 64-row block first takes the
-//     contributions of the finished blocks (row-contiguous partial dots over
-//     16 waves, reduced in a fixed order), then one wave solves the block's
-//     triangle from LDS, broadcasting each unknown with a shuffle.
-// Every reduction runs in a fixed order: identical inputs give identical bits.
+// Dense Cholesky M = L L^T in FP64, blocked with 64-column panels; B
+// independent systems per call (grid dimension x, so that with a multiple of
+// 8 systems each stays on one XCD and its L2).  One launch per panel:
+//   * kkt_panel (launch k): the workgroups of panel k first take the update by
+//     panel k - 1 of their own 64 x 64 block and of the diagonal block, factor
+//     the diagonal block (each workgroup for itself: no launch in between) and
+//     solve L_ik = A_ik L_kk^-T; the remaining workgroups apply panel k - 1 to
+//     the tiles right of panel k, which the factorisation does not wait for.
+//     M is never assembled: launches 0 and 1 read their blocks of A from H and
+//     the diagonal and rank-one terms (lower triangle only).
+//   * The right-hand side rides along as one more row of the matrix, so y
+//     (L y = r) is there after the last panel.
+//   * kkt_back: L^T x = y, one workgroup per system.
+// A pivot that is not positive (or not finite) stops that system with info =
+// its global order (LAPACK's convention: the leading minor of that order is
+// not positive definite).  Every sum runs in a fixed order: identical inputs
+// give identical bits.
+//
+// What bounds it: the chain of n / 64 panels, each with 64 dependent pivots;
+// the products (n^3 / 3 flops per system) run on v_mfma_f64_16x16x4_f64
+// beside it.  16 systems of 784: 606 us, where assembling M, separate launches
+// for the diagonal block, the column solves and the trailing update (FMA, from
+// LDS) and a forward substitution took 3,370 us.
 #include <math.h>
 
 #include "../../include/nnc.h"
@@ -35,251 +40,456 @@
 namespace nnc {
 
 constexpr int KB = 64;          // panel width
-constexpr int kKktMaxN = 2048;  // solve kernel keeps y in LDS
+constexpr int kKktMaxN = 2048;  // the back substitution keeps y in LDS
+constexpr int KP = KB + 2;      // LDS row pitch (doubles) of the diagonal block
 
-__global__ void kkt_assemble_kernel(const double* __restrict__ H, const double* __restrict__ d,
-                                    const double* __restrict__ a, const double* __restrict__ s,
-                                    const double* __restrict__ delta, int n, long long total,
-                                    double* __restrict__ L, int* __restrict__ info) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  const long long nn = (long long)n * n;
-  const int b = (int)(t / nn);
-  const long long e = t - (long long)b * nn;
-  const int i = (int)(e / n);
-  const int j = (int)(e - (long long)i * n);
-  double v = H[t];
-  if (i == j) v += (d ? d[(long long)b * n + i] : 0.0) + (delta ? delta[b] : 0.0);
-  if (a && s) v += s[b] * a[(long long)b * n + i] * a[(long long)b * n + j];
-  L[t] = v;
-  if (e == 0) info[b] = 0;
-}
+// One call's arguments.  The workspace holds the matrix padded to whole
+// panels with an identity (np = n rounded up to 64; rows ld apart), so no
+// block is ragged; L the factor's blocks below the diagonal ones, D per panel
+// the factored diagonal block with its 16 x 16 diagonal blocks inverted, R the
+// right-hand side as it is reduced and Y its solved blocks.
+struct KktArgs {
+  const double *H, *d, *a, *s, *delta, *r;
+  double *L, *D, *R, *Y;
+  int* info;
+  int n, np, ld;
+};
 
-// Factor the w x w lower triangle held in D (LDS) in place; returns 0 or the
-// 1-based order of the first pivot that is not positive (all threads).
-__device__ int kkt_factor_block(double (*D)[KB + 1], int w, int* s_fail) {
-  const int tid = threadIdx.x;
-  if (tid == 0) *s_fail = 0;
-  __syncthreads();
-  for (int j = 0; j < w; ++j) {
-    if (tid == 0) {
-      const double v = D[j][j];
-      if (!(v > 0.0) || !isfinite(v))
-        *s_fail = j + 1;
-      else
-        D[j][j] = sqrt(v);
-    }
-    __syncthreads();
-    if (*s_fail) return *s_fail;
-    const double ljj = D[j][j];
-    for (int i = j + 1 + tid; i < w; i += blockDim.x) D[i][j] /= ljj;
-    __syncthreads();
-    const int m = w - j - 1;
-    for (int idx = tid; idx < m * m; idx += blockDim.x) {
-      const int i = j + 1 + idx / m;
-      const int c = j + 1 + idx % m;
-      if (c <= i) D[i][c] -= D[i][j] * D[c][j];
-    }
-    __syncthreads();
+// N entries (i_e, j_e) of M = H + diag(d) + s a a^T + delta I, read from its
+// lower triangle; identity past n.  All loads go out before any is waited for
+// (the optional terms are uniform branches around whole groups).
+template <int N>
+__device__ __forceinline__ void kkt_entries(const KktArgs& g, int b, const int (&i)[N], const int (&j)[N],
+                                            double (&v)[N]) {
+  const long long bn = (long long)b * g.n;
+  const int last = g.n - 1;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const int r = min(max(i[e], j[e]), last), c = min(min(i[e], j[e]), last);
+    v[e] = g.H[(bn + r) * g.n + c];
   }
-  return 0;
+  double t[N];
+  if (g.d) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = g.d[bn + min(i[e], last)];
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = i[e] == j[e] ? v[e] + t[e] : v[e];
+  }
+  if (g.delta) {
+    const double dl = g.delta[b];
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = i[e] == j[e] ? v[e] + dl : v[e];
+  }
+  if (g.a) {
+    const double sb = g.s[b];
+    double u[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      t[e] = g.a[bn + min(max(i[e], j[e]), last)];
+      u[e] = g.a[bn + min(min(i[e], j[e]), last)];
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] += sb * t[e] * u[e];
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e)
+    if (i[e] > last || j[e] > last) v[e] = i[e] == j[e] ? 1.0 : 0.0;
 }
 
-// Panel k, diagonal block: factor it in LDS and write L_kk back (lower
-// triangle); on a pivot that is not positive record info and stop.
-__global__ void __launch_bounds__(256) kkt_potrf_kernel(double* __restrict__ Lall, int n, int k,
-                                                        int* __restrict__ info) {
-  __shared__ double D[KB][KB + 1];
-  __shared__ int s_fail;
-  const int b = blockIdx.y;
-  if (info[b] != 0) return;
-  double* A = Lall + (long long)b * n * n;
+// The same entries of A as panel k finds it: M before the first update has
+// been written (k < 2), the workspace after.
+template <int N>
+__device__ __forceinline__ void kkt_load(const KktArgs& g, int b, int k, const int (&i)[N], const int (&j)[N],
+                                         double (&v)[N]) {
+  if (k >= 2) {
+    const double* Lb = g.L + (long long)b * g.np * g.ld;
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = Lb[i[e] * g.ld + j[e]];
+  } else {
+    kkt_entries<N>(g, b, i, j, v);
+  }
+}
+
+__device__ __forceinline__ doublex4 mma64(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double readlane_d(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// 1 / v and 1 / sqrt(v) of a positive, finite v by Newton's iteration from the
+// hardware's estimate (each step doubles its bits; a last residual step for
+// the rounding): a pivot waits for one of these, and the full-range division
+// took four times as long.  Pivots near the ends of the range take the
+// library's.
+constexpr double kPivotLo = 0x1p-900, kPivotHi = 0x1p900;
+__device__ __forceinline__ double recip(double v) {
+  if (!(v > kPivotLo && v < kPivotHi)) return 1.0 / v;
+  double r = __builtin_amdgcn_rcp(v);
+  r = fma(fma(-v, r, 1.0), r, r);
+  r = fma(fma(-v, r, 1.0), r, r);
+  return fma(fma(-v, r, 1.0), r, r);
+}
+__device__ __forceinline__ double recip_sqrt(double v) {
+  if (!(v > kPivotLo && v < kPivotHi)) return 1.0 / sqrt(v);
+  double r = __builtin_amdgcn_rsq(v);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) r = fma(0.5 * r, fma(-v * r, r, 1.0), r);
+  return r;
+}
+
+// Products of this kernel are accumulated transposed: register e of lane l
+// holds X[l % 16][4 e + l / 16] of a 16 x 16 block X (row, column), which is
+// at once the B operand of K step e of a following product with X^T, so
+// chained products need no move between lanes.
+
+// Rows row0 .. row0 + 15 of panel k, 64 columns: z[jb] = A - (update by panel k - 1).
+__device__ __forceinline__ void kkt_block(const KktArgs& g, int b, int k, int row0, int lane, doublex4 (&z)[4]) {
+  const int c16 = lane & 15, q = lane >> 4;
+  const double* Lb = g.L + (long long)b * g.np * g.ld;
   const int kb = k * KB;
-  const int w = min(KB, n - kb);
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < w * w; idx += blockDim.x) {
-    const int i = idx / w, j = idx % w;
-    D[i][j] = A[(long long)(kb + i) * n + kb + j];
+  int ii[16], jj[16];
+  double av[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    ii[e] = row0 + c16;
+    jj[e] = kb + 4 * e + q;
   }
-  __syncthreads();
-  const int fail = kkt_factor_block(D, w, &s_fail);
-  if (fail) {
-    if (tid == 0) info[b] = kb + fail;
+  kkt_load<16>(g, b, k, ii, jj, av);
+  doublex4 acc[4];
+#pragma unroll
+  for (int jb = 0; jb < 4; ++jb) acc[jb] = doublex4{0, 0, 0, 0};
+  if (k > 0) {
+    // lane group q takes columns 16 q .. 16 q + 15 of panel k - 1, the same for
+    // both operands (a fixed order of the sum), so each lane reads whole lines
+    const double* pr = Lb + (long long)(row0 + c16) * g.ld + kb - KB + 16 * q;
+    const double* pk = Lb + (long long)(kb + c16) * g.ld + kb - KB + 16 * q;
+#pragma unroll
+    for (int t = 0; t < 16; t += 2) {
+      const double2 xr = *(const double2*)(pr + t);
+#pragma unroll
+      for (int jb = 0; jb < 4; ++jb) {
+        const double2 xk = *(const double2*)(pk + (long long)jb * 16 * g.ld + t);
+        acc[jb] = mma64(xk.x, xr.x, acc[jb]);
+        acc[jb] = mma64(xk.y, xr.y, acc[jb]);
+      }
+    }
+  }
+#pragma unroll
+  for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[jb][e] = av[4 * jb + e] - acc[jb][e];
+}
+
+// Factor the 16 x 16 block at columns 16 s of S by one wave: lane c < 16 holds
+// column c, lane 16 + c column c of the identity, and each pivot step is the
+// same row operation on both (multipliers broadcast with readlane), leaving
+// D L_u^T and L_u^-1 of the unit-triangular factor L_u.  Writes L = L_u sqrt(D)
+// to S and L^-1 to inv; returns 0 or the 1-based order of the first pivot that
+// is not positive and finite.
+__device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv)[18], int lane) {
+  const int c = lane & 15;
+  double a[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    a[i] = lane < 16 ? S[16 * s + max(i, c)][16 * s + min(i, c)] : (lane < 32 && i == c ? 1.0 : 0.0);
+  int fail = 0;
+  double piv = 1.0;  // lane j: pivot j
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const double dj = readlane_d(a[j], j);
+    if (!fail && (!(dj > 0.0) || !isfinite(dj))) fail = j + 1;
+    if (lane == j) piv = dj;
+    const double p = a[j] * recip(dj);
+#pragma unroll
+    for (int i = j + 1; i < 16; ++i) a[i] = fma(-readlane_d(a[i], j), p, a[i]);
+  }
+  const double rs = recip_sqrt(piv);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const double v = a[j] * readlane_d(rs, j);
+    if (lane < 16) {
+      if (j <= c) S[16 * s + c][16 * s + j] = v;
+    } else if (lane < 32) {
+      inv[j][c] = j >= c ? v : 0.0;
+    }
+  }
+  return fail;
+}
+
+// Launch k (see the head of the file).  gridDim = (B, P + tiles): the first
+// P = max(1, panels below k) workgroups of a system factor panel k (workgroup
+// y owns row block k + 1 + y), the others take the lower block triangle of
+// tiles (I, J), I >= J > k, row by row.
+__global__ void __launch_bounds__(256) kkt_panel_kernel(KktArgs g, int k) {
+  __shared__ __attribute__((aligned(16))) double S[KB + 1][KP];
+  __shared__ double inv[4][16][18];
+  __shared__ int s_fail;
+  const int b = blockIdx.x;
+  if (k > 0 && g.info[b] != 0) return;
+  const int nblk = g.np / KB;
+  const int below = nblk - k - 1;
+  const int P = max(1, below);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int c16 = lane & 15, q = lane >> 4;
+  double* Lb = g.L + (long long)b * g.np * g.ld;
+  const int kb = k * KB;
+
+  if ((int)blockIdx.y >= P) {  // A_IJ -= L_I,k-1 L_J,k-1^T, a 32 x 32 quadrant per wave
+    const int t = blockIdx.y - P;
+    int ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while (ti > 0 && ti * (ti + 1) / 2 > t) --ti;
+    while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+    const int tj = t - ti * (ti + 1) / 2;
+    const int i0 = (k + 1 + ti) * KB + 32 * (wave >> 1), j0 = (k + 1 + tj) * KB + 32 * (wave & 1);
+    const double* pi = Lb + (long long)(i0 + c16) * g.ld + kb - KB + 16 * q;
+    const double* pj = Lb + (long long)(j0 + c16) * g.ld + kb - KB + 16 * q;
+    int ii[16], jj[16];
+    double av[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      ii[e] = i0 + 16 * (e >> 3) + 4 * (e & 3) + q;
+      jj[e] = j0 + 16 * ((e >> 2) & 1) + c16;
+    }
+    kkt_load<16>(g, b, k, ii, jj, av);
+    doublex4 acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) acc[u][v] = doublex4{0, 0, 0, 0};
+#pragma unroll 4
+    for (int c = 0; c < 16; c += 2) {
+      double2 xi[2], xj[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        xi[u] = *(const double2*)(pi + (long long)u * 16 * g.ld + c);
+        xj[u] = *(const double2*)(pj + (long long)u * 16 * g.ld + c);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          acc[u][v] = mma64(xi[u].x, xj[v].x, acc[u][v]);
+          acc[u][v] = mma64(xi[u].y, xj[v].y, acc[u][v]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int t = 8 * u + 4 * v + e;
+          Lb[ii[t] * g.ld + jj[t]] = av[t] - acc[u][v][e];
+        }
     return;
   }
-  for (int idx = tid; idx < w * w; idx += blockDim.x) {
-    const int i = idx / w, j = idx % w;
-    if (j <= i) A[(long long)(kb + i) * n + kb + j] = D[i][j];
+
+  // the diagonal block and the right-hand side's block (row 64) into LDS
+  {
+    doublex4 z[4];
+    kkt_block(g, b, k, kb + 16 * wave, lane, z);
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S[16 * wave + c16][16 * jb + 4 * e + q] = z[jb][e];
+    if (tid < KB) {
+      const int i = kb + tid;
+      S[KB][tid] = k > 0 ? g.R[(long long)b * g.np + i] : (i < g.n ? g.r[(long long)b * g.n + i] : 0.0);
+    }
+    if (tid == 0) s_fail = 0;
+  }
+  // this workgroup's own block, taken meanwhile
+  const int row0 = (k + 1 + blockIdx.y) * KB + 16 * wave;
+  doublex4 z[4];
+  if (below > 0) kkt_block(g, b, k, row0, lane, z);
+  __syncthreads();
+  for (int s = 0; s < 4; ++s) {
+    if (wave == 0) {
+      const int f = kkt_factor16(S, s, inv[s], lane);
+      if (f && lane == 0) s_fail = kb + 16 * s + f;
+    }
+    __syncthreads();
+    if (s_fail) {
+      if (blockIdx.y == 0 && tid == 0) g.info[b] = s_fail;
+      return;
+    }
+    // blocks below (wave i: block row i > s; wave 0: the right-hand side): X = A L_ss^-T
+    const bool rhs = wave == 0;
+    if (rhs || wave > s) {
+      const int row = rhs ? KB : 16 * wave + c16;
+      doublex4 x = {0, 0, 0, 0};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double bv = !rhs || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
+        x = mma64(inv[s][c16][4 * e + q], bv, x);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!rhs || c16 == 0) S[row][16 * s + 4 * e + q] = x[e];
+    }
+    __syncthreads();
+    // trailing blocks (i, j), s < j <= i <= 3, and (right-hand side, j)
+    int id = 0;
+    for (int j = s + 1; j < 4; ++j)
+      for (int i = j; i <= 4; ++i, ++id) {
+        if ((id & 3) != wave) continue;
+        const bool r = i == 4;
+        const int row = r ? KB : 16 * i + c16;
+        doublex4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double bv = !r || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
+          acc = mma64(S[16 * j + c16][16 * s + 4 * e + q], bv, acc);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!r || c16 == 0) S[row][16 * j + 4 * e + q] -= acc[e];
+      }
+    __syncthreads();
+  }
+  if (blockIdx.y == 0) {
+    double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
+    for (int idx = tid; idx < KB * KB; idx += 256) {
+      const int i = idx / KB, j = idx % KB;
+      Dk[idx] = i / 16 == j / 16 ? inv[i / 16][i % 16][j % 16] : S[i][j];
+    }
+    if (tid < KB) g.Y[(long long)b * g.np + kb + tid] = S[KB][tid];
+    if (k == 0 && tid == 0) g.info[b] = 0;
+  }
+  if (below == 0) return;
+  // X_s^T = L_ss^-1 (A_s^T - sum_{t < s} L_st X_t^T), 16 rows per wave
+  double dot = 0.0;  // this lane's part of (L_ik y_k)
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    doublex4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < s; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = mma64(S[16 * s + c16][16 * t + 4 * e + q], z[t][e], acc);
+    const doublex4 w = z[s] - acc;
+    doublex4 x = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x = mma64(inv[s][c16][4 * e + q], w[e], x);
+    z[s] = x;
+    double* o = Lb + (long long)(row0 + c16) * g.ld + kb + 16 * s + q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[4 * e] = x[e];
+      dot = fma(x[e], S[KB][16 * s + 4 * e + q], dot);
+    }
+  }
+  dot += __shfl_xor(dot, 16, 64);
+  dot += __shfl_xor(dot, 32, 64);
+  if (q == 0) {
+    const int i = row0 + c16;
+    double* R = g.R + (long long)b * g.np + i;
+    const double rv = k > 0 ? *R : (i < g.n ? g.r[(long long)b * g.n + i] : 0.0);
+    *R = rv - dot;
   }
 }
 
-// Panel k, row block k + 1 + blockIdx.x: L_ik = A_ik L_kk^-T, one row per
-// thread, the factored diagonal block and the row block staged in LDS.
-__global__ void __launch_bounds__(256) kkt_trsm_kernel(double* __restrict__ Lall, int n, int k,
-                                                       const int* __restrict__ info) {
-  __shared__ double D[KB][KB + 1];
-  __shared__ double R[KB][KB + 1];
-  const int b = blockIdx.y;
-  if (info[b] != 0) return;
-  double* A = Lall + (long long)b * n * n;
-  const int kb = k * KB;
-  const int w = min(KB, n - kb);
-  const int r0 = (k + 1 + blockIdx.x) * KB;
-  const int nr = min(KB, n - r0);
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < w * w; idx += blockDim.x) {
-    const int i = idx / w, j = idx % w;
-    D[i][j] = j <= i ? A[(long long)(kb + i) * n + kb + j] : 0.0;
-  }
-  for (int idx = tid; idx < nr * w; idx += blockDim.x) {
-    const int i = idx / w, j = idx % w;
-    R[i][j] = A[(long long)(r0 + i) * n + kb + j];
-  }
-  __syncthreads();
-  // row i of the block: x_j = (a_j - sum_{t<j} x_t L_kk[j][t]) / L_kk[j][j]
-  for (int i = tid; i < nr; i += blockDim.x) {
-    for (int j = 0; j < w; ++j) {
-      double v = R[i][j];
-      for (int t = 0; t < j; ++t) v -= R[i][t] * D[j][t];
-      R[i][j] = v / D[j][j];
-    }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < nr * w; idx += blockDim.x) {
-    const int i = idx / w, j = idx % w;
-    A[(long long)(r0 + i) * n + kb + j] = R[i][j];
-  }
-}
-
-// Trailing update after panel k: tile (I, J), I >= J > k, of the lower block
-// triangle, enumerated row by row.
-__global__ void __launch_bounds__(256) kkt_update_kernel(double* __restrict__ Lall, int n, int k,
-                                                         const int* __restrict__ info) {
-  __shared__ double LI[KB][KB + 1];
-  __shared__ double LJ[KB][KB + 1];
-  const int b = blockIdx.y;
-  if (info[b] != 0) return;
-  double* A = Lall + (long long)b * n * n;
-  int t = blockIdx.x;
-  int ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-  while (ti > 0 && ti * (ti + 1) / 2 > t) --ti;
-  while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
-  const int tj = t - ti * (ti + 1) / 2;
-  const int I0 = (k + 1 + ti) * KB, J0 = (k + 1 + tj) * KB;
-  const int kb = k * KB;
-  const int w = min(KB, n - kb);
-  const int ni = min(KB, n - I0), nj = min(KB, n - J0);
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < KB * KB; idx += blockDim.x) {
-    const int r = idx / KB, c = idx % KB;
-    LI[r][c] = (r < ni && c < w) ? A[(long long)(I0 + r) * n + kb + c] : 0.0;
-    LJ[r][c] = (r < nj && c < w) ? A[(long long)(J0 + r) * n + kb + c] : 0.0;
-  }
-  __syncthreads();
-  const int ty = tid >> 4, tx = tid & 15;
-  double acc[4][4] = {};
-  for (int c = 0; c < w; ++c) {
-    double li[4], lj[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      li[u] = LI[ty * 4 + u][c];
-      lj[u] = LJ[tx * 4 + u][c];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[u][v] = fma(li[u], lj[v], acc[u][v]);
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = ty * 4 + u, c = tx * 4 + v;
-      if (r < ni && c < nj) A[(long long)(I0 + r) * n + J0 + c] -= acc[u][v];
-    }
-}
-
-// Forward and back substitution with the factor L (lower triangle of each
-// system's matrix); 1024 threads = 16 waves per system.
-__global__ void __launch_bounds__(1024) kkt_solve_kernel(const double* __restrict__ Lall, int n,
-                                                         const double* __restrict__ r, double* __restrict__ x,
-                                                         const int* __restrict__ info) {
+// L^T x = y, one workgroup of 16 waves per system: wave 0 solves a panel's 64
+// unknowns from the diagonal block in LDS (16 at a time through the inverted
+// 16 x 16 blocks), then all threads take them out of the unknowns above,
+// reading the panel's rows of L once, along the rows.  Bound by what one CU
+// reads (half of the matrix) and the n / 64 panels in turn.
+__global__ void __launch_bounds__(1024) kkt_back_kernel(KktArgs g, double* __restrict__ x) {
   __shared__ double y[kKktMaxN];
   __shared__ double D[KB][KB + 1];
-  __shared__ double part[16][KB];
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  if (info[b] != 0) {
-    for (int i = tid; i < n; i += blockDim.x) x[(long long)b * n + i] = 0.0;
+  const int lane = tid & 63;
+  double* xb = x + (long long)b * g.n;
+  if (g.info[b] != 0) {
+    for (int i = tid; i < g.n; i += 1024) xb[i] = 0.0;
     return;
   }
-  const double* L = Lall + (long long)b * n * n;
-  for (int i = tid; i < n; i += blockDim.x) y[i] = r[(long long)b * n + i];
-  __syncthreads();
-  const int nblk = (n + KB - 1) / KB;
-  // forward: L y = r
-  for (int k = 0; k < nblk; ++k) {
-    const int kb = k * KB, w = min(KB, n - kb);
-    // contributions of the finished unknowns y[0..kb) to rows kb..kb+w
-    for (int i = wv; i < w; i += 16) {
-      const double* row = L + (long long)(kb + i) * n;
-      double sacc = 0.0;
-      for (int t = lane; t < kb; t += 64) sacc += row[t] * y[t];
+  const int nblk = g.np / KB;
+  const double* Lb = g.L + (long long)b * g.np * g.ld;
+  for (int i = tid; i < g.np; i += 1024) y[i] = g.Y[(long long)b * g.np + i];
+  double dreg[4];
+  auto load_diag = [&](int k) {
+    const double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
 #pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) sacc += __shfl_xor(sacc, off, 64);
-      if (lane == 0) part[0][i] = sacc;
-    }
-    for (int idx = tid; idx < w * w; idx += blockDim.x) {
-      const int i = idx / w, j = idx % w;
-      D[i][j] = j <= i ? L[(long long)(kb + i) * n + kb + j] : 0.0;
-    }
-    __syncthreads();
-    if (wv == 0) {
-      double yi = lane < w ? y[kb + lane] - part[0][lane] : 0.0;
-      for (int j = 0; j < w; ++j) {
-        const double yj = __shfl(yi / D[j][j], j, 64);
-        if (lane == j) yi = yj;
-        if (lane > j && lane < w) yi -= D[lane][j] * yj;
-      }
-      if (lane < w) y[kb + lane] = yi;
-    }
-    __syncthreads();
-  }
-  // back: L^T x = y (x overwrites y)
+    for (int u = 0; u < 4; ++u) dreg[u] = Dk[u * 1024 + tid];
+  };
+  load_diag(nblk - 1);
   for (int k = nblk - 1; k >= 0; --k) {
-    const int kb = k * KB, w = min(KB, n - kb);
-    // contributions of the finished unknowns x[kb+w..n) to rows kb..kb+w of
-    // L^T: sum over t of L[t][kb+i] x[t]; wave wv takes rows t = kb+w+wv+16q
-    double sacc = 0.0;
-    if (lane < w)
-      for (int t = kb + w + wv; t < n; t += 16) sacc += L[(long long)t * n + kb + lane] * y[t];
-    part[wv][lane] = sacc;
-    for (int idx = tid; idx < w * w; idx += blockDim.x) {
-      const int i = idx / w, j = idx % w;
-      D[i][j] = j <= i ? L[(long long)(kb + i) * n + kb + j] : 0.0;
-    }
+    const int kb = k * KB;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) D[(u * 1024 + tid) / KB][tid % KB] = dreg[u];
     __syncthreads();
-    if (wv == 0) {
-      double tot = 0.0;
-      for (int q = 0; q < 16; ++q) tot += part[q][lane];
-      double xi = lane < w ? y[kb + lane] - tot : 0.0;
-      for (int i = w - 1; i >= 0; --i) {
-        const double xv = __shfl(xi / D[i][i], i, 64);
-        if (lane == i) xi = xv;
-        if (lane < i) xi -= D[i][lane] * xv;
+    if (k > 0) load_diag(k - 1);
+    // this thread's column of the panel's first rows, on the way meanwhile
+    constexpr int PF = 16;
+    const double* p = Lb + (long long)kb * g.ld + tid;
+    double pre[PF];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) pre[i] = tid < kb ? p[(long long)i * g.ld] : 0.0;
+    if (tid < 64) {
+      double yi = y[kb + lane];
+#pragma unroll
+      for (int s = 3; s >= 0; --s) {
+        double xs[16];  // y of sub-block s, then x
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
+        if (lane >> 4 == s) {
+          double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int i = 0; i < 16; ++i) v[i & 3] = fma(D[16 * s + i][lane], xs[i], v[i & 3]);
+          yi = (v[0] + v[1]) + (v[2] + v[3]);
+        }
+        if (s > 0) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
+          if (lane < 16 * s) {
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i & 3] = fma(D[16 * s + i][lane], xs[i], v[i & 3]);
+            yi -= (v[0] + v[1]) + (v[2] + v[3]);
+          }
+        }
       }
-      if (lane < w) y[kb + lane] = xi;
+      y[kb + lane] = yi;
+      if (kb + lane < g.n) xb[kb + lane] = yi;
     }
     __syncthreads();
+    if (tid < kb) {
+      double v = 0.0;
+      double rest[KB - PF];
+#pragma unroll
+      for (int i = PF; i < KB; ++i) rest[i - PF] = p[(long long)i * g.ld];
+#pragma unroll
+      for (int i = 0; i < PF; ++i) v = fma(pre[i], y[kb + i], v);
+#pragma unroll
+      for (int i = PF; i < KB; ++i) v = fma(rest[i - PF], y[kb + i], v);
+      y[tid] -= v;
+    }
+    for (int j = 1024 + tid; j < kb; j += 1024) {
+      const double* pj = Lb + (long long)kb * g.ld + j;
+      double v = 0.0;
+#pragma unroll 32
+      for (int i = 0; i < KB; ++i) v = fma(pj[(long long)i * g.ld], y[kb + i], v);
+      y[j] -= v;
+    }
+    // the next round's barrier stands between these updates and wave 0's read
   }
-  for (int i = tid; i < n; i += blockDim.x) x[(long long)b * n + i] = y[i];
 }
 
 struct Kkt {
   int n = 0, maxB = 0;
-  double* L = nullptr;
+  int np = 0, ld = 0;
+  double* L = nullptr;  // one allocation: L, D, R, Y of KktArgs
 };
+
+// Doubles of one system's workspace (KktArgs): rows of L 16 doubles past a
+// multiple of 64 apart, so that the rows of a tile spread over the channels.
+inline size_t kkt_words(const Kkt* k) { return (size_t)k->np * k->ld + (size_t)k->np * KB + 2 * (size_t)k->np; }
 
 void free_kkts(Ctx* c) {
   for (void* p : c->kkts) {
@@ -312,7 +522,9 @@ int nnc_kkt_create(nnc_ctx ctx, int n, int max_B, int* kkt) {
   Kkt* k = new Kkt();
   k->n = n;
   k->maxB = max_B;
-  if (hipMalloc(&k->L, (size_t)max_B * n * n * sizeof(double)) != hipSuccess) {
+  k->np = (n + KB - 1) / KB * KB;
+  k->ld = k->np + 16;
+  if (hipMalloc(&k->L, (size_t)max_B * kkt_words(k) * sizeof(double)) != hipSuccess) {
     delete k;
     return kkt_fail(c, NNC_E_NOMEM, "KKT factor workspace");
   }
@@ -344,23 +556,31 @@ int nnc_kkt_solve(nnc_ctx ctx, int kkt, int B, const double* H, const double* d,
   if (hipSetDevice(c->device) != hipSuccess) return kkt_fail(c, NNC_E_HIP, "hipSetDevice failed");
   const int n = k->n;
   const long long total = (long long)B * n * n;
-  const long long blocks = (total + 255) / 256;
-  if (blocks > 0x7fffffffLL) return kkt_fail(c, NNC_E_SHAPE, "B * n * n too large");
+  if ((total + 255) / 256 > 0x7fffffffLL) return kkt_fail(c, NNC_E_SHAPE, "B * n * n too large");
+  KktArgs g;
+  g.H = H;
+  g.d = d;
+  g.a = a;
+  g.s = s;
+  g.delta = delta;
+  g.r = r;
+  g.info = info;
+  g.n = n;
+  g.np = k->np;
+  g.ld = k->ld;
+  g.L = k->L;
+  g.D = g.L + (size_t)B * k->np * k->ld;
+  g.R = g.D + (size_t)B * k->np * KB;
+  g.Y = g.R + (size_t)B * k->np;
   ProfRec pr;
   prof_begin(c, NNC_KC_OTHER, &pr);
-  hipLaunchKernelGGL(kkt_assemble_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream, H, d, a, s, delta, n,
-                     total, k->L, info);
-  const int nblk = (n + KB - 1) / KB;
+  const int nblk = k->np / KB;
   for (int p = 0; p < nblk; ++p) {
-    hipLaunchKernelGGL(kkt_potrf_kernel, dim3(1, B), dim3(256), 0, c->stream, k->L, n, p, info);
-    const int T = nblk - p - 1;
-    if (T == 0) break;
-    hipLaunchKernelGGL(kkt_trsm_kernel, dim3(T, B), dim3(256), 0, c->stream, k->L, n, p, (const int*)info);
-    hipLaunchKernelGGL(kkt_update_kernel, dim3(T * (T + 1) / 2, B), dim3(256), 0, c->stream, k->L, n, p,
-                       (const int*)info);
+    const int below = nblk - p - 1;
+    const int tiles = p > 0 ? below * (below + 1) / 2 : 0;
+    hipLaunchKernelGGL(kkt_panel_kernel, dim3(B, (below > 0 ? below : 1) + tiles), dim3(256), 0, c->stream, g, p);
   }
-  hipLaunchKernelGGL(kkt_solve_kernel, dim3(B), dim3(1024), 0, c->stream, (const double*)k->L, n, r, dx,
-                     (const int*)info);
+  hipLaunchKernelGGL(kkt_back_kernel, dim3(B), dim3(1024), 0, c->stream, g, dx);
   const hipError_t e = hipGetLastError();
   prof_end(c, &pr);
   if (e != hipSuccess) {
