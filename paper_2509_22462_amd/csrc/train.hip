@@ -12,6 +12,12 @@
 // copies for the next wgrad).  Master parameters and Adam moments are FP32;
 // the GEMM copies of W and W^T are BF16 (or FP32).  All reductions are in a
 // fixed order, so a step is deterministic.
+//
+// Networks whose products are all small (the warm-start network and anything
+// with fewer than 128 tiles of 128 x 128 per product) take tr_mm_kernel and
+// tr_wgrad_kernel below instead of the GEMM library: a step is then 2 L + 1
+// launches.  Larger ones keep the LDS-tiled GEMMs, which read each operand
+// from L2 a quarter as often, and separate bias-gradient and Adam launches.
 #include <math.h>
 #include <string.h>
 
@@ -29,7 +35,20 @@ namespace {
 
 inline int rup(int x, int a) { return (x + a - 1) / a * a; }
 
+// One layer of the grouped weight-gradient launch.
+struct TrLayer {
+  const void *dZT, *AT;  // [dp_l][bp], [dp_{l-1}][bp]
+  float *W, *m, *v, *dW;
+  float *b, *mb, *vb, *db;
+  void *Wc, *WTc;
+  int rows, cols;  // dp_l, dp_{l-1}
+  int tile0;       // first tile of the layer
+};
+
 struct Trainer {
+  bool small = false;         // tr_mm_kernel / tr_wgrad_kernel path
+  TrLayer* dlayers = nullptr;  // device table of the grouped launch
+  int wtiles = 0;
   int L = 0, batch = 0, bp = 0;
   DType ct = DT_BF16;
   size_t csz = 2;
@@ -42,7 +61,7 @@ struct Trainer {
   float* Yhat = nullptr;        // [bp][dp_L]
   double* partial = nullptr;    // loss partial sums
   double* lossd = nullptr;
-  int nblocks_loss = 0;
+  int npartial = 0;
   int step = 0;
   std::vector<void*> allocs;
 };
@@ -65,15 +84,23 @@ void free_trainer(Trainer* t) {
 }
 
 // ---------------------------------------------------------------- kernels
+// Input batch as GEMM operands, row-major and transposed, in 32 x 32 tiles
+// through LDS so that both copies are written along their rows.
 template <typename T>
-__global__ void tr_cast_input(const double* X, int rows, int d0, int bp, int dp0, T* A, T* AT) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)bp * dp0) return;
-  const int r = (int)(i / dp0);
-  const int c = (int)(i % dp0);
-  const double v = (r < rows && c < d0) ? X[(long long)r * d0 + c] : 0.0;
-  A[i] = from_d<T>(v);
-  AT[(long long)c * bp + r] = from_d<T>(v);
+__global__ void __launch_bounds__(256) tr_cast_input(const double* X, int rows, int d0, int bp, int dp0, T* A, T* AT) {
+  __shared__ T tile[32][34];
+  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+  for (int y = ty; y < 32; y += 8) {
+    const int r = r0 + y, c = c0 + tx;
+    const T v = from_d<T>(r < rows && c < d0 ? X[(long long)r * d0 + c] : 0.0);
+    A[(long long)r * dp0 + c] = v;
+    tile[y][tx] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int y = ty; y < 32; y += 8) AT[(long long)(c0 + y) * bp + r0 + tx] = tile[tx][y];
 }
 
 // dZ_L = 2 (Yhat - Y) / (batch * m) on the true region; per-block loss partials.
@@ -104,46 +131,274 @@ __global__ void tr_mse_grad(const float* Yhat, const double* Y, int batch, int m
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ void tr_sum_partials(const double* partial, int n, double scale, double* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < n; ++i) s += partial[i];
-    *out = s * scale;
+// Sum of the loss partials by one workgroup: strided sums per thread, then a
+// tree in LDS (one thread adding them in turn waited for each load: 51 us for
+// the warm-start network's 832 partials).
+__global__ void __launch_bounds__(256) tr_sum_partials(const double* partial, int n, double scale, double* out) {
+  __shared__ double red[256];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) s += partial[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) *out = red[0] * scale;
 }
 
-// db[j] = sum_k dZT[j][k] in a fixed order.
+// db[j] = sum_k dZT[j][k] in batch order, one thread per row, 16 bytes a load.
 template <typename T>
-__global__ void tr_colsum(const T* dZT, int rows, int bp, float* db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(64) tr_colsum(const T* dZT, int rows, int bp, float* db) {
+  constexpr int V = 16 / (int)sizeof(T);
+  const int j = blockIdx.x * 64 + threadIdx.x;
   if (j >= rows) return;
   float s = 0.f;
-  for (int k = 0; k < bp; ++k) s += to_f(dZT[(long long)j * bp + k]);
+#pragma unroll 8
+  for (int k = 0; k < bp; k += V) {
+    float e[V];
+    Vec16<T, float>::unpack(*(const uint4*)(dZT + (long long)j * bp + k), e);
+#pragma unroll
+    for (int q = 0; q < V; ++q) s += e[q];
+  }
   db[j] = s;
+}
+
+struct AdamArgs {
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// The fused operations are written out: both kernels below round every step
+// alike, whatever the compiler would contract in each.
+__device__ __forceinline__ float adam_update(const AdamArgs& h, float g, float& m1, float& m2, float p) {
+#pragma clang fp contract(off)
+  m1 = fmaf(1.f - h.b1, g, h.b1 * m1);
+  m2 = fmaf(g, (1.f - h.b2) * g, h.b2 * m2);
+  return p - h.lr * (m1 / h.c1) / (sqrtf(m2 / h.c2) + h.eps);
 }
 
 // Adam on one parameter block; refreshes the GEMM copies (W and W^T) when
 // `wc` is given.  rows x cols is the padded block shape.
 template <typename T>
-__global__ void tr_adam(float* p, float* m1, float* m2, const float* g, long long count, int cols,
-                        int rows, float lr, float b1, float b2, float eps, float c1, float c2, T* wc,
-                        T* wtc) {
+__global__ void tr_adam(float* p, float* m1, float* m2, const float* g, long long count, int cols, int rows,
+                        AdamArgs h, T* wc, T* wtc) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
-  const float gi = g[i];
-  const float a = b1 * m1[i] + (1.f - b1) * gi;
-  const float b = b2 * m2[i] + (1.f - b2) * gi * gi;
+  float a = m1[i], b = m2[i];
+  const float np_ = adam_update(h, g[i], a, b, p[i]);
   m1[i] = a;
   m2[i] = b;
-  const float mh = a / c1;
-  const float vh = b / c2;
-  const float np_ = p[i] - lr * mh / (sqrtf(vh) + eps);
   p[i] = np_;
   if (wc) {
     const int r = (int)(i / cols);
     const int c = (int)(i % cols);
     wc[i] = from_f<T>(np_);
     wtc[(long long)c * rows + r] = from_f<T>(np_);
+  }
+}
+
+// ---------------------------------------------------------------- small products
+// C[r][c] = sum_k R[r][k] C[c][k] of a training step: 32 x 32 outputs per
+// workgroup, one 16 x 16 block per wave, whose operand fragments go straight
+// from L2 into registers (the next 8 K steps' on the way while these are
+// multiplied); no LDS and no barrier stands between load and MFMA.  These
+// products are a few dozen K steps of operands that fit L2, so what counts is
+// how long the chain of loads is and how many CUs take part: the 64 x 64 LDS
+// tiles put 256 x 512 x 832 on 32 CUs in 13 dependent rounds.  One wave runs
+// the whole of K in order, as the LDS tiles do, so both give the same bits (a
+// BF16 step that rounds one sum the other way moves the parameters after an
+// epoch by 2e-4).  The lane's results are columns 4 (l / 16) .. + 3 of row
+// l % 16.
+// 256 x 512 x 832 in BF16: 10.1 -> 8.2 us; a step of the warm-start network
+// 20 launches and 264 us of kernels -> 7 launches and 75 us.
+template <typename T> struct TrMma;
+template <> struct TrMma<bf16> {
+  static constexpr int VEC = 8;
+  __device__ __forceinline__ static void mma(floatx4& c, const uint4& a, const uint4& b) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                0);
+  }
+};
+template <> struct TrMma<float> {
+  static constexpr int VEC = 4;
+  __device__ __forceinline__ static void mma(floatx4& c, const uint4& a, const uint4& b) {
+    float x[4], y[4];
+    Vec16<float, float>::unpack(a, x);
+    Vec16<float, float>::unpack(b, y);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], c, 0, 0, 0);
+  }
+};
+
+// C, R: this wave's 16 operand rows of the columns and of the rows, K a
+// multiple of 64 (so of 2 BF16 and 4 FP32 steps).
+template <typename T>
+__device__ __forceinline__ floatx4 tr_block(const T* C, const T* R, int K) {
+  using M = TrMma<T>;
+  constexpr int KSTEP = 4 * M::VEC;
+  constexpr int U = 8;
+  const int lane = threadIdx.x & 63;
+  const long long o = (long long)(lane & 15) * K + (lane >> 4) * M::VEC;
+  const T* cp = C + o;
+  const T* rp = R + o;
+  const int steps = K / KSTEP;
+  floatx4 acc = {0, 0, 0, 0};
+  uint4 cf[U], rf[U], cn[U], rn[U];
+  auto load = [&](int s, uint4 (&c)[U], uint4 (&r)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(s + u, steps - 1) * KSTEP;  // past the end: loaded again, not used
+      c[u] = *(const uint4*)(cp + k);
+      r[u] = *(const uint4*)(rp + k);
+    }
+  };
+  auto mul = [&](int s, const uint4 (&c)[U], const uint4 (&r)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < steps) M::mma(acc, c[u], r[u]);
+  };
+  load(0, cf, rf);
+  for (int s = 0; s < steps; s += 2 * U) {
+    if (s + U < steps) load(s + U, cn, rn);
+    mul(s, cf, rf);
+    if (s + 2 * U < steps) load(s + 2 * U, cf, rf);
+    if (s + U < steps) mul(s + U, cn, rn);
+  }
+  return acc;
+}
+
+// Four consecutive values into the row-major and the transposed copy.
+template <typename T>
+__device__ __forceinline__ void tr_put(T* o, T* ot, int row, int col, long long ldo, long long ldt, const float (&v)[4]) {
+  union {
+    T e[4];
+    uint2 u2;
+    uint4 u4;
+  } w;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w.e[e] = from_f<T>(v[e]);
+  if constexpr (sizeof(T) == 2)
+    *(uint2*)(o + row * ldo + col) = w.u2;
+  else
+    *(uint4*)(o + row * ldo + col) = w.u4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) ot[(col + e) * ldt + row] = w.e[e];
+}
+
+enum { TRM_HIDDEN, TRM_OUT, TRM_BWD };
+
+struct TrMm {
+  const void *C, *R;  // [cols][K], [rows][K]
+  int K, ld;          // ld of row-major outputs (= columns)
+  int bp;             // ld of transposed outputs (= rows)
+  const float* bias;
+  void *out, *outT;
+  float* d1;          // sigma': written by TRM_HIDDEN, read by TRM_BWD
+  float* yhat;        // TRM_OUT
+  const double* Y;    // TRM_OUT: targets, or NULL (prediction only)
+  int batch, m;
+  double* partial;    // TRM_OUT: one loss partial per wave
+};
+
+// Hidden layer forward (bias, tanh, sigma'), output layer forward (with the
+// loss gradient dZ_L = 2 (Yhat - Y) / (batch m) when there are targets), or
+// backward through a layer (times sigma').
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) tr_mm_kernel(TrMm g) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int c0 = blockIdx.x * 32 + (wave & 1) * 16, r0 = blockIdx.y * 32 + (wave >> 1) * 16;
+  const floatx4 a = tr_block<T>((const T*)g.C + (long long)c0 * g.K, (const T*)g.R + (long long)r0 * g.K, g.K);
+  const int row = r0 + (lane & 15);
+  const int col = c0 + (lane >> 4) * 4;
+  const long long o = (long long)row * g.ld + col;
+  float v[4] = {a[0], a[1], a[2], a[3]};
+  if constexpr (MODE == TRM_HIDDEN) {
+    const float4 b = *(const float4*)(g.bias + col);
+    v[0] = tanhf(v[0] + b.x);
+    v[1] = tanhf(v[1] + b.y);
+    v[2] = tanhf(v[2] + b.z);
+    v[3] = tanhf(v[3] + b.w);
+    tr_put<T>((T*)g.out, (T*)g.outT, row, col, g.ld, g.bp, v);
+    *(float4*)(g.d1 + o) = make_float4(1.0f - v[0] * v[0], 1.0f - v[1] * v[1], 1.0f - v[2] * v[2], 1.0f - v[3] * v[3]);
+  } else if constexpr (MODE == TRM_BWD) {
+    const float4 d = *(const float4*)(g.d1 + o);
+    v[0] *= d.x;
+    v[1] *= d.y;
+    v[2] *= d.z;
+    v[3] *= d.w;
+    tr_put<T>((T*)g.out, (T*)g.outT, row, col, g.ld, g.bp, v);
+  } else {
+    const float4 b = *(const float4*)(g.bias + col);
+    v[0] += b.x;
+    v[1] += b.y;
+    v[2] += b.z;
+    v[3] += b.w;
+    *(float4*)(g.yhat + o) = make_float4(v[0], v[1], v[2], v[3]);
+    if (!g.Y) return;
+    double sq = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float dz = 0.f;
+      if (row < g.batch && col + e < g.m) {
+        const double diff = (double)v[e] - g.Y[(long long)row * g.m + col + e];
+        sq += diff * diff;
+        dz = (float)(2.0 * diff / ((double)g.batch * g.m));
+      }
+      v[e] = dz;
+    }
+    tr_put<T>((T*)g.out, (T*)g.outT, row, col, g.ld, g.bp, v);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, 64);
+    if (lane == 0) g.partial[((long long)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave] = sq;
+  }
+}
+
+// Weight and bias gradients of every layer in one launch, with Adam on the
+// tile while it is in registers: dW_l = dZ_l^T A_{l-1}, the new W in FP32 and
+// as both GEMM copies.  The layer's first column of tiles also sums dZ over
+// the batch for the bias, one thread per row in batch order.
+template <typename T>
+__global__ void __launch_bounds__(256) tr_wgrad_kernel(const TrLayer* __restrict__ layers, int L, int bp, AdamArgs h) {
+  int l = 0;
+  while (l + 1 < L && layers[l + 1].tile0 <= (int)blockIdx.x) ++l;
+  const TrLayer y = layers[l];
+  const int t = blockIdx.x - y.tile0;
+  const int tc = y.cols / 32;
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int c0 = t % tc * 32 + (wave & 1) * 16, r0 = t / tc * 32 + (wave >> 1) * 16;
+  const floatx4 a = tr_block<T>((const T*)y.AT + (long long)c0 * bp, (const T*)y.dZT + (long long)r0 * bp, bp);
+  const int row = r0 + (lane & 15);
+  const int col = c0 + (lane >> 4) * 4;
+  const long long o = (long long)row * y.cols + col;
+  *(float4*)(y.dW + o) = make_float4(a[0], a[1], a[2], a[3]);
+  const float4 p4 = *(const float4*)(y.W + o), m4 = *(const float4*)(y.m + o), v4 = *(const float4*)(y.v + o);
+  const float g[4] = {a[0], a[1], a[2], a[3]};
+  float p[4] = {p4.x, p4.y, p4.z, p4.w}, m[4] = {m4.x, m4.y, m4.z, m4.w}, v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) p[e] = adam_update(h, g[e], m[e], v[e], p[e]);
+  *(float4*)(y.W + o) = make_float4(p[0], p[1], p[2], p[3]);
+  *(float4*)(y.m + o) = make_float4(m[0], m[1], m[2], m[3]);
+  *(float4*)(y.v + o) = make_float4(v[0], v[1], v[2], v[3]);
+  tr_put<T>((T*)y.Wc, (T*)y.WTc, row, col, y.cols, y.rows, p);
+  if (t % tc == 0 && threadIdx.x < 32) {
+    constexpr int V = 16 / (int)sizeof(T);
+    const int i = t / tc * 32 + threadIdx.x;
+    const T* z = (const T*)y.dZT + (long long)i * bp;
+    float gb = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < bp; k += V) {
+      float e[V];
+      Vec16<T, float>::unpack(*(const uint4*)(z + k), e);
+#pragma unroll
+      for (int q = 0; q < V; ++q) gb += e[q];
+    }
+    y.db[i] = gb;
+    float mb = y.mb[i], vb = y.vb[i];
+    y.b[i] = adam_update(h, gb, mb, vb, y.b[i]);
+    y.mb[i] = mb;
+    y.vb[i] = vb;
   }
 }
 
@@ -174,6 +429,15 @@ inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
       (c)->err = std::string(#call) + " failed: " + hipGetErrorString(e_);           \
       return NNC_E_HIP;                                                             \
     }                                                                               \
+  } while (0)
+
+// Launch of a small-product kernel, profiled as a GEMM.
+#define TR_MM(c, kernel, ...)                       \
+  do {                                              \
+    ProfRec pr_;                                    \
+    prof_begin((c), NNC_KC_GEMM, &pr_);             \
+    hipLaunchKernelGGL(kernel, __VA_ARGS__);        \
+    prof_end((c), &pr_);                            \
   } while (0)
 
 int get_trainer(Ctx* c, int id, Trainer** out) {
@@ -211,13 +475,44 @@ GemmArgs gargs(const void* A, long long lda, const void* B, long long ldb, int M
   return g;
 }
 
+// Grid of the 32 x 32 tiles of a rows x cols product (both multiples of 64).
+inline dim3 tr_grid(int rows, int cols) { return dim3(cols / 32, rows / 32); }
+
+// Forward pass of `rows` samples; with targets Y (the small path) the output
+// layer's launch also writes dZ_L and the loss partials.
 template <typename T>
-int tr_forward(Ctx* c, Trainer* t, const double* X, int rows) {
+int tr_forward(Ctx* c, Trainer* t, const double* X, int rows, const double* Y) {
   hipStream_t s = c->stream;
-  hipLaunchKernelGGL(tr_cast_input<T>, dim3(nblk((long long)t->bp * t->dp[0])), dim3(256), 0, s, X,
-                     rows, t->d[0], t->bp, t->dp[0], (T*)t->A[0], (T*)t->AT[0]);
+  hipLaunchKernelGGL(tr_cast_input<T>, tr_grid(t->bp, t->dp[0]), dim3(256), 0, s, X, rows, t->d[0], t->bp, t->dp[0],
+                     (T*)t->A[0], (T*)t->AT[0]);
   TR_HIP(c, hipGetLastError());
   for (int l = 1; l <= t->L; ++l) {
+    if (t->small) {
+      TrMm g{};
+      g.C = t->Wc[l - 1];
+      g.R = t->A[l - 1];
+      g.K = t->dp[l - 1];
+      g.ld = t->dp[l];
+      g.bp = t->bp;
+      g.bias = t->bm[l - 1];
+      if (l < t->L) {
+        g.out = t->A[l];
+        g.outT = t->AT[l];
+        g.d1 = t->D1[l];
+        TR_MM(c, (tr_mm_kernel<T, TRM_HIDDEN>), tr_grid(t->bp, t->dp[l]), dim3(256), 0, s, g);
+      } else {
+        g.out = t->dZ[l];
+        g.outT = t->dZT[l];
+        g.yhat = t->Yhat;
+        g.Y = Y;
+        g.batch = t->batch;
+        g.m = t->d[l];
+        g.partial = t->partial;
+        TR_MM(c, (tr_mm_kernel<T, TRM_OUT>), tr_grid(t->bp, t->dp[l]), dim3(256), 0, s, g);
+      }
+      TR_HIP(c, hipGetLastError());
+      continue;
+    }
     GemmArgs g = gargs(t->A[l - 1], t->dp[l - 1], t->Wc[l - 1], t->dp[l - 1], t->bp, t->dp[l],
                        t->dp[l - 1]);
     g.epi = EPI_TRAIN_FWD;
@@ -239,18 +534,39 @@ int tr_forward(Ctx* c, Trainer* t, const double* X, int rows) {
   return NNC_OK;
 }
 
+// Backward pass and update by the small kernels: dZ down the layers, then
+// every layer's gradients and Adam in one launch (the weights are read by the
+// backward passes before).
 template <typename T>
-int tr_step(Ctx* c, Trainer* t, const double* X, const double* Y, float lr, float* loss) {
+int tr_backward_small(Ctx* c, Trainer* t, const AdamArgs& h) {
   hipStream_t s = c->stream;
-  int rc = tr_forward<T>(c, t, X, t->batch);
-  if (rc) return rc;
+  for (int l = t->L; l >= 2; --l) {
+    TrMm g{};
+    g.C = t->WTc[l - 1];
+    g.R = t->dZ[l];
+    g.K = t->dp[l];
+    g.ld = t->dp[l - 1];
+    g.bp = t->bp;
+    g.d1 = t->D1[l - 1];
+    g.out = t->dZ[l - 1];
+    g.outT = t->dZT[l - 1];
+    TR_MM(c, (tr_mm_kernel<T, TRM_BWD>), tr_grid(t->bp, t->dp[l - 1]), dim3(256), 0, s, g);
+    TR_HIP(c, hipGetLastError());
+  }
+  TR_MM(c, tr_wgrad_kernel<T>, dim3(t->wtiles), dim3(256), 0, s, (const TrLayer*)t->dlayers, t->L, t->bp, h);
+  TR_HIP(c, hipGetLastError());
+  return NNC_OK;
+}
+
+// The same by the LDS-tiled GEMMs, from Yhat on.
+template <typename T>
+int tr_backward_large(Ctx* c, Trainer* t, const double* Y, const AdamArgs& h) {
+  hipStream_t s = c->stream;
   const int L = t->L;
+  int rc;
   const long long nout = (long long)t->bp * t->dp[L];
   hipLaunchKernelGGL(tr_mse_grad<T>, dim3(nblk(nout)), dim3(256), 0, s, t->Yhat, Y, t->batch,
                      t->d[L], t->bp, t->dp[L], (T*)t->dZ[L], (T*)t->dZT[L], t->partial);
-  TR_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(tr_sum_partials, dim3(1), dim3(64), 0, s, t->partial, (int)nblk(nout),
-                     1.0 / ((double)t->batch * t->d[L]), t->lossd);
   TR_HIP(c, hipGetLastError());
   for (int l = L; l >= 1; --l) {
     // wgrad: dW_l[dp_l][dp_{l-1}] = dZT_l [dp_l][bp] x AT_{l-1} [dp_{l-1}][bp]^T
@@ -259,42 +575,54 @@ int tr_step(Ctx* c, Trainer* t, const double* X, const double* Y, float lr, floa
     g.out0 = t->dW[l - 1];
     g.ldo = t->dp[l - 1];
     if ((rc = tr_gemm(c, t, g))) return rc;
-    hipLaunchKernelGGL(tr_colsum<T>, dim3(nblk(t->dp[l])), dim3(256), 0, s, (const T*)t->dZT[l],
+    hipLaunchKernelGGL(tr_colsum<T>, dim3((t->dp[l] + 63) / 64), dim3(64), 0, s, (const T*)t->dZT[l],
                        t->dp[l], t->bp, t->db[l - 1]);
     TR_HIP(c, hipGetLastError());
     if (l >= 2) {
       // dgrad: dZ_{l-1} = (dZ_l W_l) * sigma'_{l-1};  W_l = (W_l^T)^T
-      GemmArgs h = gargs(t->dZ[l], t->dp[l], t->WTc[l - 1], t->dp[l], t->bp, t->dp[l - 1], t->dp[l]);
-      h.epi = EPI_TRAIN_BWD;
-      h.v0 = t->D1[l - 1];
-      h.ldv = t->dp[l - 1];
-      h.out0 = t->dZ[l - 1];
-      h.out1 = t->dZT[l - 1];
-      h.ldo = t->dp[l - 1];
-      h.ldt = t->bp;
-      if ((rc = tr_gemm(c, t, h))) return rc;
+      GemmArgs b = gargs(t->dZ[l], t->dp[l], t->WTc[l - 1], t->dp[l], t->bp, t->dp[l - 1], t->dp[l]);
+      b.epi = EPI_TRAIN_BWD;
+      b.v0 = t->D1[l - 1];
+      b.ldv = t->dp[l - 1];
+      b.out0 = t->dZ[l - 1];
+      b.out1 = t->dZT[l - 1];
+      b.ldo = t->dp[l - 1];
+      b.ldt = t->bp;
+      if ((rc = tr_gemm(c, t, b))) return rc;
     }
   }
-  t->step += 1;
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = 1.f - powf(b1, (float)t->step);
-  const float c2 = 1.f - powf(b2, (float)t->step);
   for (int l = 1; l <= L; ++l) {
     const long long cw = (long long)t->dp[l] * t->dp[l - 1];
     hipLaunchKernelGGL(tr_adam<T>, dim3(nblk(cw)), dim3(256), 0, s, t->Wm[l - 1], t->mW[l - 1],
-                       t->vW[l - 1], t->dW[l - 1], cw, t->dp[l - 1], t->dp[l], lr, b1, b2, eps, c1,
-                       c2, (T*)t->Wc[l - 1], (T*)t->WTc[l - 1]);
+                       t->vW[l - 1], t->dW[l - 1], cw, t->dp[l - 1], t->dp[l], h, (T*)t->Wc[l - 1],
+                       (T*)t->WTc[l - 1]);
     TR_HIP(c, hipGetLastError());
     hipLaunchKernelGGL(tr_adam<T>, dim3(nblk(t->dp[l])), dim3(256), 0, s, t->bm[l - 1], t->mb[l - 1],
-                       t->vb[l - 1], t->db[l - 1], (long long)t->dp[l], t->dp[l], 1, lr, b1, b2, eps,
-                       c1, c2, (T*)nullptr, (T*)nullptr);
+                       t->vb[l - 1], t->db[l - 1], (long long)t->dp[l], t->dp[l], 1, h, (T*)nullptr, (T*)nullptr);
     TR_HIP(c, hipGetLastError());
   }
+  return NNC_OK;
+}
+
+template <typename T>
+int tr_step(Ctx* c, Trainer* t, const double* X, const double* Y, float lr, float* loss) {
+  hipStream_t s = c->stream;
+  int rc = tr_forward<T>(c, t, X, t->batch, Y);
+  if (rc) return rc;
+  const float b1 = 0.9f, b2 = 0.999f;
+  const int step = t->step + 1;
+  const AdamArgs h{lr, b1, b2, 1e-8f, 1.f - powf(b1, (float)step), 1.f - powf(b2, (float)step)};
+  rc = t->small ? tr_backward_small<T>(c, t, h) : tr_backward_large<T>(c, t, Y, h);
+  if (rc) return rc;
+  t->step = step;
   if (loss) {
-    double h = 0.0;
-    TR_HIP(c, hipMemcpyAsync(&h, t->lossd, sizeof(double), hipMemcpyDeviceToHost, s));
+    hipLaunchKernelGGL(tr_sum_partials, dim3(1), dim3(256), 0, s, t->partial, t->npartial,
+                       1.0 / ((double)t->batch * t->d[t->L]), t->lossd);
+    TR_HIP(c, hipGetLastError());
+    double v = 0.0;
+    TR_HIP(c, hipMemcpyAsync(&v, t->lossd, sizeof(double), hipMemcpyDeviceToHost, s));
     TR_HIP(c, hipStreamSynchronize(s));
-    *loss = (float)h;
+    *loss = (float)v;
   }
   return NNC_OK;
 }
@@ -395,13 +723,35 @@ int nnc_train_create(nnc_ctx ctx, int L, const int* dims, int batch, int prec,
     t->dZT[l] = A((size_t)t->bp * t->dp[l] * t->csz);
   }
   t->Yhat = (float*)A((size_t)t->bp * t->dp[L] * 4);
-  t->nblocks_loss = (int)nblk((long long)t->bp * t->dp[L]);
-  t->partial = (double*)A((size_t)t->nblocks_loss * 8);
+  // small: every product of a step below 128 tiles of 128 x 128 (tr_gemm's own
+  // line between its small and its large tiles)
+  t->small = true;
+  for (int l = 1; l <= L; ++l) {
+    auto tiles = [](int a, int b) { return (long long)((a + 127) / 128) * ((b + 127) / 128); };
+    if (tiles(t->bp, t->dp[l]) >= 128 || tiles(t->dp[l], t->dp[l - 1]) >= 128 || tiles(t->bp, t->dp[l - 1]) >= 128)
+      t->small = false;
+  }
+  // loss partials: one per wave of 256 outputs (small), or per block of 256
+  t->npartial = (int)nblk((long long)t->bp * t->dp[L]);
+  t->partial = (double*)A((size_t)t->npartial * 8);
+  t->dlayers = (TrLayer*)A(sizeof(TrLayer) * L);
   t->lossd = (double*)A(8);
   if (!ok) {
     free_trainer(t);
     c->err = "device allocation failed";
     return NNC_E_NOMEM;
+  }
+  std::vector<TrLayer> table(L);
+  for (int l = 1; l <= L; ++l) {
+    table[l - 1] = TrLayer{t->dZT[l],   t->AT[l - 1], t->Wm[l - 1], t->mW[l - 1], t->vW[l - 1], t->dW[l - 1],
+                           t->bm[l - 1], t->mb[l - 1], t->vb[l - 1], t->db[l - 1], t->Wc[l - 1], t->WTc[l - 1],
+                           t->dp[l],     t->dp[l - 1], t->wtiles};
+    if (t->small) t->wtiles += t->dp[l] / 32 * (t->dp[l - 1] / 32);
+  }
+  if (hipMemcpy(t->dlayers, table.data(), sizeof(TrLayer) * L, hipMemcpyHostToDevice) != hipSuccess) {
+    free_trainer(t);
+    c->err = "layer table upload failed";
+    return NNC_E_HIP;
   }
   // N(0, 1/fan_in) initial weights from `seed` (host generator), zero biases.
   std::mt19937_64 gen(seed);
@@ -467,7 +817,7 @@ int nnc_train_predict(nnc_ctx ctx, int id, int B, const double* X, double* Yhat)
     return NNC_E_ARG;
   }
   if (hipSetDevice(c->device) != hipSuccess) return NNC_E_HIP;
-  rc = t->ct == DT_BF16 ? tr_forward<bf16>(c, t, X, B) : tr_forward<float>(c, t, X, B);
+  rc = t->ct == DT_BF16 ? tr_forward<bf16>(c, t, X, B, nullptr) : tr_forward<float>(c, t, X, B, nullptr);
   if (rc) return rc;
   const int m = t->d[t->L];
   hipLaunchKernelGGL(tr_out_f64, dim3(nblk((long long)B * m)), dim3(256), 0, c->stream, t->Yhat, B, m,
