@@ -420,6 +420,8 @@ int run_forward_bufs(Ctx* c, Net* net, int B, const double* x, const double* y, 
       continue;
     }
     SkinnyArgs a = skinny_args(ly.W, ly.dinp, ly.doutp, ly.dinp, X, ly.dinp, B, SK_PRIMAL);
+    a.part = net->at == DT_F64 ? (void*)net->spart64 : (void*)net->spart;
+    a.part_elems = net->at == DT_F64 ? net->spart64_elems : net->spart_elems;
     a.dtrue = ly.dout;
     a.act = ly.act;
     a.bias = ly.b;
@@ -1105,13 +1107,15 @@ int nnc_net_create(nnc_ctx ctx, int L, const int* dims, const int* acts, const d
   net->R0 = A((size_t)B * net->m * maxdp * net->asz);
   net->R1 = A((size_t)B * net->m * maxdp * net->asz);
   net->dflag = (int*)A(16);
-  if (net->at == DT_F32) {  // K slices of the MFMA weight streams: up to 16 slices of 64 rows x widest W^T
+  {  // K slices of the MFMA weight streams: up to 16 slices of 64 rows x widest W^T (FP64: of the points' rows)
     size_t maxn = 0;
     for (int l = 1; l <= L; ++l) maxn = std::max(maxn, (size_t)net->ly[l - 1].dinp);
-    net->spart_elems = 16LL * 64 * (long long)maxn;
-    net->spart64_elems = 16LL * (long long)maxn;
-    net->spart = (float*)A((size_t)net->spart_elems * 4);
+    net->spart64_elems = 16LL * (B > 4 ? std::min(B, 64) : 1) * (long long)maxn;
     net->spart64 = (double*)A((size_t)net->spart64_elems * 8);
+    if (net->at == DT_F32) {
+      net->spart_elems = 16LL * 64 * (long long)maxn;
+      net->spart = (float*)A((size_t)net->spart_elems * 4);
+    }
   }
   if (net->softmax_out) {
     net->usm = (double*)A((size_t)B * net->n * 8);

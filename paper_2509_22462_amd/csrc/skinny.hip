@@ -179,6 +179,67 @@ __global__ void __launch_bounds__(KSPLIT * 64) skinny_ksplit_kernel(SkinnyArgs a
   }
 }
 
+// FP64 output layer at more than 4 points: a workgroup owns 4 points and 8
+// outputs and its 256 threads split K (two elements a step, W_L and the points
+// straight from L2).  m is a handful, so the MFMA stream below would put the
+// whole product on ceil(m / 16) workgroups per 64 points.  The 32 sums are
+// scattered over the lanes while they are reduced (halving what each lane
+// keeps at every step), then added over the waves in wave order.  21 points, 10
+// outputs of 4,096 elements: 57.7 -> 12.1 us.
+template <typename TX>
+__global__ void __launch_bounds__(256) skinny_out_kernel(SkinnyArgs a) {
+  constexpr int R = 4, JO = 8;
+  __shared__ double red[4][R * JO];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int r0 = blockIdx.x * R;
+  const int j0 = blockIdx.y * JO;
+  const TX* xr[R];
+  const double* wr[JO];
+#pragma unroll
+  for (int r = 0; r < R; ++r) xr[r] = (const TX*)a.X + (long long)min(r0 + r, a.rows - 1) * a.ldx;
+#pragma unroll
+  for (int j = 0; j < JO; ++j) wr[j] = (const double*)a.W + (long long)min(j0 + j, a.N - 1) * a.ldw;
+  double acc[R * JO];
+#pragma unroll
+  for (int i = 0; i < R * JO; ++i) acc[i] = 0.0;
+#pragma unroll 2
+  for (int k = 2 * tid; k < a.K; k += 512) {  // K is even
+    double x[R][2];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      x[r][0] = (double)xr[r][k];
+      x[r][1] = (double)xr[r][k + 1];
+    }
+#pragma unroll
+    for (int j = 0; j < JO; ++j) {
+      const double2 w = *(const double2*)(wr[j] + k);
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r * JO + j] = fma(w.y, x[r][1], fma(w.x, x[r][0], acc[r * JO + j]));
+    }
+  }
+  // after the step with offset 2^s the lane keeps the half of its sums that
+  // bit s of the lane names
+#pragma unroll
+  for (int s = 5, cnt = R * JO / 2; s >= 1; --s, cnt /= 2) {
+    const bool up = (lane >> s) & 1;
+#pragma unroll
+    for (int i = 0; i < cnt; ++i) {
+      const double give = up ? acc[i] : acc[cnt + i];
+      const double keep = up ? acc[cnt + i] : acc[i];
+      acc[i] = keep + __shfl_xor(give, 1 << s, 64);
+    }
+  }
+  acc[0] += __shfl_xor(acc[0], 1, 64);
+  if ((lane & 1) == 0) red[tid >> 6][lane >> 1] = acc[0];
+  __syncthreads();
+  if (tid < R * JO) {
+    const double v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+    const int r = r0 + tid / JO, j = j0 + tid % JO;
+    if (r < a.rows && j < a.N) skinny_epilogue<double>(a, a.row0 + r, j, v);
+  }
+}
+
 // MFMA form of the weight stream, for more than 4 rows (Jacobian rows): a
 // workgroup of KSPLIT waves owns 16 weight rows j0..j0+15 and the waves split
 // K.  Per step each lane loads 16 bytes of one weight row (lane % 16) and the
@@ -405,8 +466,9 @@ __global__ void __launch_bounds__(KSPLIT * 64) skinny_mfma_kernel(SkinnyArgs a, 
   }
 }
 
-// FP32 Jacobian rows (one to four 16-row blocks, optionally with the FP64
-// adjoint row) against packed W^T, rows staged in LDS.  skinny_mfma_kernel
+// FP32 rows (Jacobian rows against packed W^T, optionally with the FP64
+// adjoint row; points against row-major W, PACKED = false), one to four 16-row
+// blocks, staged in LDS.  skinny_mfma_kernel
 // re-reads the rows from L2 once per weight block: RB x 16 rows of FP32 per
 // 16 weight rows, several bytes through L2 per weight byte.  Here a
 // workgroup of 8 waves covers 8 weight blocks (128 weight rows) over one K
@@ -428,7 +490,7 @@ __global__ void __launch_bounds__(KSPLIT * 64) skinny_mfma_kernel(SkinnyArgs a, 
 // already split into BF16 hi and lo parts (x = hi + lo to about 2^-17
 // relative), once per workgroup at staging instead of once per wave, in
 // two planes; a lane's 8-element K chunk is one b128 read from each.
-template <typename TW, int RB, bool ADJ>
+template <typename TW, int RB, bool ADJ, bool PACKED>
 __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, SkinnyArgs d) {
   constexpr int WV = 16 / (int)sizeof(TW);  // weight elements per 16-byte load
   constexpr int KSTEP = 4 * WV;
@@ -456,12 +518,21 @@ __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, Skin
   const int c1 = min(nchunks, c0 + cper);
   const long long jb = (long long)blockIdx.x * 8 + wave;  // this wave's weight block
   const bool wok = jb * 16 < a.N;
-  const TW* wp = (const TW*)a.Wp + (jb * nsteps * 64 + lane) * WV;
+  // row-major: 16 rows of 64 bytes per step, whole lines over two steps; rows
+  // past N (a partial block) read row N - 1 again
+  const TW* wp = PACKED ? (const TW*)a.Wp + (jb * nsteps * 64 + lane) * WV
+                        : (const TW*)a.W + min(jb * 16 + c16, (long long)a.N - 1) * a.ldw + q * WV;
+  constexpr int WSTEP = PACKED ? 64 * WV : KSTEP;
   const float* X = (const float*)a.X;
   const double* Z = ADJ ? (const double*)d.X : nullptr;
-  floatx4 acc[RB][2];
+  // BF16 weights: the hi and the lo parts' sums; FP32: one sum per element of a
+  // lane's 16 bytes (short chains of roundings, independent MFMAs)
+  constexpr int NA = BF16_MMA ? 2 : WV;
+  floatx4 acc[RB][NA];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = floatx4{0, 0, 0, 0};
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[rb][i] = floatx4{0, 0, 0, 0};
   double adj[2] = {0.0, 0.0};
   uint4 wa[CH], wb[CH];
   float4 xr[XV];
@@ -470,7 +541,7 @@ __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, Skin
 #pragma unroll
     for (int st = 0; st < CH; ++st) {
       const int sg = ch * CH + st;
-      w[st] = wok && sg < nsteps ? *(const uint4*)(wp + (long long)sg * 64 * WV) : make_uint4(0u, 0u, 0u, 0u);
+      w[st] = wok && sg < nsteps ? *(const uint4*)(wp + (long long)sg * WSTEP) : make_uint4(0u, 0u, 0u, 0u);
     }
   };
   auto load_rows = [&](int ch) {
@@ -553,7 +624,7 @@ __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, Skin
         for (int e = 0; e < WV; ++e)
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb)
-            acc[rb][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xe[rb][e], wf[e], acc[rb][e & 1], 0, 0, 0);
+            acc[rb][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(xe[rb][e], wf[e], acc[rb][e], 0, 0, 0);
       }
       if constexpr (ADJ) {
         double wd[WV];
@@ -575,7 +646,8 @@ __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, Skin
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = rb * 16 + q * 4 + e;  // accumulator row of element e: 4 (lane / 16) + e
-      const float v = acc[rb][0][e] + acc[rb][1][e];
+      float v = acc[rb][0][e] + acc[rb][1][e];
+      if constexpr (NA == 4) v += acc[rb][2][e] + acc[rb][3][e];
       if (r < a.rows && j < a.N) {
         if (split)
           ((float*)a.part)[((long long)blockIdx.y * a.rows + r) * a.N + j] = v;
@@ -594,6 +666,120 @@ __global__ void __launch_bounds__(512) skinny_rows_lds_kernel(SkinnyArgs a, Skin
         skinny_epilogue<double>(d, d.row0, j, t);
     }
   }
+}
+
+// FP64 rows (the adjoint of 5 to 64 points, and every stream of an FP64
+// network's points), staged in LDS as in skinny_rows_lds_kernel: a workgroup of
+// 8 waves covers 8 blocks of 16 weight rows over one K slice, chunks of 64 K
+// elements, two buffers, one barrier per chunk.  skinny_mfma_kernel reads
+// every FP64 row from L2 once per weight block (4 KiB per 64 K elements and 16
+// weight rows, in 16-byte pieces a row apart) and waited on that, not on HBM
+// or the matrix cores: the adjoint of 32 points through 8192 x 8192 BF16
+// weights, beside the forward sweep, 505 -> 218 us.  FP64 weights of one row
+// block stay there (four times slower here without K slices).
+template <typename TW, int RB, bool PACKED>
+__global__ void __launch_bounds__(512) skinny_rows64_kernel(SkinnyArgs a) {
+  constexpr int WV = 16 / (int)sizeof(TW);
+  constexpr int KSTEP = 4 * WV;
+  constexpr int CK = 64;
+  constexpr int CH = CK / KSTEP;
+  constexpr int NR = 16 * RB;
+  constexpr int PD = CK + 2;  // row pitch in doubles: the 16 rows of a read start 4 banks apart
+  constexpr int XV = NR * (CK / 2) / 512;  // 16-byte pairs of staged rows per thread and chunk
+  static_assert(XV * 512 == NR * (CK / 2), "rows x chunk must split evenly over 512 threads");
+  __shared__ __attribute__((aligned(16))) double xs[2][NR * PD];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int c16 = lane & 15;
+  const int q = lane >> 4;
+  const int nchunks = a.K / CK;  // K is a multiple of 64
+  const int cper = (nchunks + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int c0 = min(nchunks, (int)blockIdx.y * cper);
+  const int c1 = min(nchunks, c0 + cper);
+  const long long jb = (long long)blockIdx.x * 8 + wave;
+  const bool wok = jb * 16 < a.N;
+  const TW* wp = PACKED ? (const TW*)a.Wp + (jb * (a.K / KSTEP) * 64 + lane) * WV
+                        : (const TW*)a.W + min(jb * 16 + c16, (long long)a.N - 1) * a.ldw + q * WV;
+  constexpr int WSTEP = PACKED ? 64 * WV : KSTEP;
+  const double* X = (const double*)a.X;
+  doublex4 acc[RB][2];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = doublex4{0, 0, 0, 0};
+  uint4 wa[CH], wb[CH];
+  double2 xr[XV];
+  auto load_w = [&](int ch, uint4* w) {
+#pragma unroll
+    for (int st = 0; st < CH; ++st)
+      w[st] = wok ? *(const uint4*)(wp + (long long)(ch * CH + st) * WSTEP) : make_uint4(0u, 0u, 0u, 0u);
+  };
+  auto load_rows = [&](int ch) {
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+      const int t = tid + i * 512;
+      const int r = t / (CK / 2);
+      const int f = t - r * (CK / 2);
+      xr[i] = r < a.rows ? *(const double2*)(X + (long long)r * a.ldx + ch * CK + 2 * f) : make_double2(0.0, 0.0);
+    }
+  };
+  auto store_rows = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+      const int t = tid + i * 512;
+      const int r = t / (CK / 2);
+      const int f = t - r * (CK / 2);
+      *(double2*)&xs[buf][r * PD + 2 * f] = xr[i];
+    }
+  };
+  if (c0 < c1) {
+    load_w(c0, wa);
+    load_rows(c0);
+    store_rows(0);
+  }
+  __syncthreads();
+  for (int ch = c0; ch < c1; ++ch) {
+    const int buf = (ch - c0) & 1;
+    const bool more = ch + 1 < c1;
+    if (more) {
+      load_w(ch + 1, wb);
+      load_rows(ch + 1);
+    }
+#pragma unroll
+    for (int st = 0; st < CH; ++st) {
+      double wd[WV];
+      Vec16<TW, double>::unpack(wa[st], wd);
+#pragma unroll
+      for (int e2 = 0; e2 < WV; e2 += 2) {
+        double2 xv[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+          xv[rb] = *(const double2*)&xs[buf][(rb * 16 + c16) * PD + st * KSTEP + q * WV + e2];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[rb][0] = SkMma<double>::mma(xv[rb].x, wd[e2], acc[rb][0]);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[rb][1] = SkMma<double>::mma(xv[rb].y, wd[e2 + 1], acc[rb][1]);
+      }
+    }
+    if (more) store_rows(buf ^ 1);  // that buffer was last read before the previous barrier
+    __syncthreads();
+#pragma unroll
+    for (int st = 0; st < CH; ++st) wa[st] = wb[st];
+  }
+  const bool split = gridDim.y > 1;
+  const int j = (int)(jb * 16) + c16;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = rb * 16 + SkMma<double>::row(lane, e);
+      const double v = acc[rb][0][e] + acc[rb][1][e];
+      if (r < a.rows && j < a.N) {
+        if (split)
+          ((double*)a.part)[((long long)blockIdx.y * a.rows + r) * a.N + j] = v;
+        else
+          skinny_epilogue<double>(a, a.row0 + r, j, v);
+      }
+    }
 }
 
 // Sum of the K slices of an MFMA weight stream, in slice order, through the
@@ -620,9 +806,11 @@ __global__ void skinny_slice_reduce_kernel(SkinnyArgs a, SkinnyArgs d, int kslic
 // Row blocks for `rows` rows (at most kStreamRows).
 constexpr int kStreamRows = 64;
 
-// Launch rules for the 5..64-row streams.  Packed FP32 Jacobian rows go to
+// Launch rules for the 5..64-row streams.  FP32 rows go to
 // skinny_rows_lds_kernel (rows staged in LDS), except one row block on a
-// narrow layer.  The remaining packed streams at one row block (the adjoint
+// narrow layer, and FP64 rows to skinny_rows64_kernel from 512 K elements on
+// (the output layer's adjoint, K = the padded number of outputs, has nothing
+// to stage ahead and keeps one workgroup per weight block).  The remaining packed streams at one row block (the adjoint
 // alone, or narrow layers) use two 16-row blocks per wave (each X and
 // adjoint fragment read serves both), 16 waves per workgroup for BF16
 // weights and 8 otherwise; measured on the 137M network's reverse streams
@@ -630,7 +818,24 @@ constexpr int kStreamRows = 64;
 template <typename TW, typename TX, typename A, int RB, bool JAC, bool ADJ, bool PACKED>
 static hipError_t skinny_mfma_launch_p(SkinnyArgs c, SkinnyArgs d, hipStream_t s) {
   const int blocks = (c.N + 15) / 16;
-  if constexpr (PACKED && JAC && sizeof(A) == 4 && std::is_same<TX, float>::value) {
+  if constexpr (JAC && !ADJ && sizeof(A) == 8 && std::is_same<TX, double>::value) {
+    const int groups = (blocks + 7) / 8;
+    if (c.K >= 512 && (sizeof(TW) < 8 || RB > 1)) {
+      const int nchunks = c.K / 64;
+      int ksw = std::max(1, std::min(256 / groups, nchunks / 2));
+      while (ksw > 1 && (!c.part || (long long)ksw * c.rows * c.N > c.part_elems)) --ksw;
+      const int cper = (nchunks + ksw - 1) / ksw;
+      ksw = (nchunks + cper - 1) / cper;
+      hipLaunchKernelGGL((skinny_rows64_kernel<TW, RB, PACKED>), dim3(groups, ksw), dim3(512), 0, s, c);
+      if (ksw > 1) {
+        const long long work = (long long)c.rows * c.N;
+        hipLaunchKernelGGL(skinny_slice_reduce_kernel<A>, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, c, d,
+                           ksw, c.rows, 0);
+      }
+      return hipGetLastError();
+    }
+  }
+  if constexpr (JAC && sizeof(A) == 4 && std::is_same<TX, float>::value && (PACKED || !ADJ)) {
    const int groups = (blocks + 7) / 8;
    if (RB >= 2 || groups >= 16) {
     // FP32 Jacobian rows: rows staged in LDS per workgroup of 8 weight
@@ -647,7 +852,7 @@ static hipError_t skinny_mfma_launch_p(SkinnyArgs c, SkinnyArgs d, hipStream_t s
     if (!c.part || (ADJ && !d.part)) ksw = 1;
     const int cper = std::max(1, (nchunks + ksw - 1) / ksw);
     ksw = std::max(1, (nchunks + cper - 1) / cper);
-    hipLaunchKernelGGL((skinny_rows_lds_kernel<TW, RB, ADJ>), dim3(groups, ksw), dim3(512), 0, s, c, d);
+    hipLaunchKernelGGL((skinny_rows_lds_kernel<TW, RB, ADJ, PACKED>), dim3(groups, ksw), dim3(512), 0, s, c, d);
     if (ksw > 1) {
       const long long work = (long long)c.rows * c.N + (ADJ ? d.N : 0);
       hipLaunchKernelGGL(skinny_slice_reduce_kernel<A>, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, c, d,
@@ -754,6 +959,12 @@ static hipError_t skinny_launch_r(SkinnyArgs a, hipStream_t s) {
 
 template <typename TW, typename TX, typename A>
 static hipError_t skinny_launch(SkinnyArgs a, hipStream_t s) {
+  if constexpr (std::is_same<TW, double>::value) {
+    if (a.epi == SK_OUT && a.rows > 4) {
+      hipLaunchKernelGGL(skinny_out_kernel<TX>, dim3((a.rows + 3) / 4, (a.N + 7) / 8), dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   const int total = a.rows;
   const int base = a.row0;
   const char* X = (const char*)a.X;
