@@ -34,6 +34,7 @@ namespace {
 struct GroupLaunch {
   int cfg = 0;
   bool acc64 = false;
+  bool pk = false;  // packed products
   int ngroups = 0;
   int grid = 0;
   GemmArgs* dargs = nullptr;
@@ -98,13 +99,13 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     }
   }
   const DType ct = nets.empty() ? DT_F32 : nets[0]->ct;
-  auto add_launch = [&](int phase, int idx) -> int {
+  auto add_launch = [&](int phase, int idx, bool pk) -> int {
     std::vector<std::pair<GemmArgs, int>> groups;  // (args, splits)
     bool acc64 = false, sym = false;
     long long work = 0;
     for (int i = 0; i < njobs; ++i)
       for (const PlannedGemm& p : per[i])
-        if (p.phase == phase && p.idx == idx) {
+        if (p.phase == phase && p.idx == idx && p.pk == pk) {
           groups.push_back({p.g, p.splits});
           acc64 = p.acc64;
           sym = sym || p.g.sym > 0;
@@ -126,6 +127,13 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     if (!acc64 && c->forced_cfg[ct] >= 0 && gemm_grouped_supports(ct, c->forced_cfg[ct], acc64))
       cfg = c->forced_cfg[ct];
     if (!gemm_grouped_supports(ct, cfg, acc64)) cfg = 3;
+    // packed products: the tiling their largest one would take alone
+    if (pk) {
+      const GemmArgs* big = &groups[0].first;
+      for (const auto& gr : groups)
+        if ((long long)gr.first.M * gr.first.N * gr.first.K > (long long)big->M * big->N * big->K) big = &gr.first;
+      cfg = pk_choose(ct, big->M, big->N, big->K, 0).cfg;
+    }
     // symmetric layer-sum products need square tiles of their own edge
     // (the 64 x 64 tiling also serves any other H product of the launch)
     if (sym) cfg = kSymCfg;
@@ -140,7 +148,10 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     std::vector<GemmArgs> args;
     for (auto& gr : groups) {
       GemmArgs g = gr.first;
-      gemm_set_tiles(cfg, g);
+      if (pk)
+        pk_set_tiles(ct, cfg, g);
+      else
+        gemm_set_tiles(cfg, g);
       total += (long long)gemm_tiles_per_split(g) * gr.second;
       offs.push_back((int)total);
       args.push_back(g);
@@ -148,8 +159,9 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     GroupLaunch L;
     L.cfg = cfg;
     L.acc64 = acc64;
+    L.pk = pk;
     L.ngroups = (int)args.size();
-    const int occ = gemm_grouped_occupancy(cfg);
+    const int occ = pk ? pk_grouped_occupancy(ct, cfg) : gemm_grouped_occupancy(cfg);
     L.grid = (int)std::min<long long>(total, (long long)kCUs * occ);
     void* a = nullptr;
     void* o = nullptr;
@@ -165,14 +177,15 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     return NNC_OK;
   };
   for (int s = 0; s < maxf; ++s) {
-    int rc = add_launch(0, s);
+    int rc = add_launch(0, s, true);  // networks on packed operands, then the others
+    if (!rc) rc = add_launch(0, s, false);
     if (rc) return rc;
   }
   for (int r = 0; r < maxr; ++r) {
-    int rc = add_launch(1, r);
+    int rc = add_launch(1, r, false);
     if (rc) return rc;
   }
-  return add_launch(2, 0);
+  return add_launch(2, 0, false);
 }
 
 // The captured sequence.
@@ -190,8 +203,10 @@ int record(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, int njobs
   for (const GroupLaunch& L : plan->launches) {
     ProfRec pr;
     prof_begin(c, NNC_KC_GEMM, &pr);
-    B_HIP(c, launch_gemm_grouped(nets[0]->ct, L.cfg, L.acc64, L.dargs, L.doffs, L.ngroups, L.grid,
-                                 c->stream));
+    if (L.pk)
+      B_HIP(c, launch_gemm_pk_grouped(nets[0]->ct, L.cfg, L.dargs, L.doffs, L.ngroups, L.grid, c->stream));
+    else
+      B_HIP(c, launch_gemm_grouped(nets[0]->ct, L.cfg, L.acc64, L.dargs, L.doffs, L.ngroups, L.grid, c->stream));
     prof_end(c, &pr);
   }
   for (int i = 0; i < njobs; ++i) {
@@ -374,6 +389,7 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
   B_HIP(c, hipEventCreate(&e1));
   const bool prof = c->prof;
   c->prof = false;
+  internal_update_pk(c, net, false);  // the tilings of the row-major products are what is timed
   rc = nnc_eval_hess_lag(ctx, id, B, dx, 0.0, dl, dH);
   std::vector<PlannedGemm> plan;
   if (!rc) rc = internal_plan_tangents(net, B, plan);
@@ -495,6 +511,7 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
               best.ks, have_ref ? "true" : "false", best.err, (int)timed.size() + rejected, rejected);
   }
   if (cache) fclose(cache);
+  internal_update_pk(c, net, true);
   c->prof = prof;
   hipEventDestroy(e0);
   hipEventDestroy(e1);

@@ -1,0 +1,512 @@
+// Sweep products on packed operands (gfx950 / CDNA4): FP32 by three BF16
+// parts per element, BF16, and FP64.
+//
+// C[M][N] = P[M][K] W[N][K]^T, P the tangents (one row per tangent column), W
+// the weights.  Both operands are stored in the order the matrix units read
+// them: for each block of 16 rows, each 32 elements of K and each part, the
+// 1 KiB that one wave reads as a v_mfma_f32_16x16x32_bf16 operand (lane l
+// holds row l % 16, elements 8 (l / 16) .. + 7; FP64: blocks of 8 elements for
+// v_mfma_f64_16x16x4_f64).  A wave's LDS-DMA load
+// therefore reads one contiguous KiB of memory, lands it in LDS as it is, and
+// a fragment read is 64 consecutive 16-byte lanes: no bank conflicts, no
+// swizzle, no address arithmetic per row.
+//
+// FP32 (NP = 3): x = hi + mid + lo, each the leading 8 significant bits of
+// what is left, so the three parts hold all 24 bits (cut_parts below), and
+//   x y = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + O(2^-24 x y),
+// six BF16 products accumulated in FP32, smallest first: at 16x the rate of
+// the FP32 instruction they cost 6/16 of its time.  The dropped terms are a
+// quarter ulp of each product.  The five smaller products have accumulators of
+// their own, so the large ones are rounded by one product in six: on normally
+// distributed operands the error against FP64 sums is 5.9e-7 at K = 8192 and
+// 1.9e-7 at K = 1024, where the FP32 instruction's is 1.6e-6 and 5.7e-7.
+//
+// What bounds it: the matrix cores and the LDS reads that feed them (each
+// three-part fragment pair feeds six MFMAs, a BF16 pair one).  Measured with
+// the sweep's epilogue, against the tuned tilings of the row-major kernels:
+// FP32 25,088 x 8192 x 8192 24.2 -> 15.0 ms (139 -> 225 TF/s), 784 x 8192 x 8192
+// 0.83 -> 0.55 ms; BF16 the same shapes 3.67 -> 3.15 ms and 0.118 -> 0.106 ms;
+// FP64 784 x 8192 x 8192 1.93 -> 1.75 ms.
+#include <algorithm>
+#include <type_traits>
+
+#include "nnc_device.h"
+#include "nnc_internal.h"
+#include "pk_device.h"
+
+namespace nnc {
+
+typedef __attribute__((address_space(3))) void* lds_ptr;
+
+namespace {
+
+// s_waitcnt until at most N vector-memory operations of this wave are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
+__device__ __forceinline__ void barrier_nofence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// MFMA accumulators: FP32 for BF16 parts, FP64 for FP64.
+template <typename T> struct PkAcc {
+  using A = float;
+  using V = floatx4;
+};
+template <> struct PkAcc<double> {
+  using A = double;
+  using V = doublex4;
+};
+
+// Four consecutive elements of a row-major FP32, BF16 or FP64 array (aligned
+// to the four).
+template <typename T, typename A>
+__device__ __forceinline__ void put4(T* o, const A (&x)[4]) {
+  if constexpr (sizeof(T) == 8) {
+    *(double2*)o = make_double2(x[0], x[1]);
+    *(double2*)(o + 2) = make_double2(x[2], x[3]);
+  } else if constexpr (sizeof(T) == 4) {
+    *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
+  } else {
+    uint2 t[1];
+    cut_parts<1>(x, t);
+    *(uint2*)o = t[0];
+  }
+}
+
+// Four consecutive results of one row through the epilogue of g.epi.
+template <typename T>
+__device__ __forceinline__ void pk_epilogue(const GemmArgs& g, int row, int col, int b,
+                                            const typename PkAcc<T>::A (&v)[4], int split) {
+  using A = typename PkAcc<T>::A;
+  if (g.epi == EPI_PART) {
+    put4<A, A>((A*)g.out0 + (long long)split * g.split_stride + (long long)row * g.ldo + col, v);
+    return;
+  }
+  const long long o = (long long)row * g.ldo + col;
+  const long long vi = (long long)b * g.ldv + col;
+  put4<T, A>((T*)g.out0 + o, v);
+  if (g.out2) {
+    const double2 s0 = *(const double2*)((const double*)g.v1 + vi);
+    const double2 s1 = *(const double2*)((const double*)g.v1 + vi + 2);
+    const A x[4] = {v[0] * (A)s0.x, v[1] * (A)s0.y, v[2] * (A)s1.x, v[3] * (A)s1.y};
+    put4<T, A>((T*)g.out2 + o, x);
+  }
+  if (g.out1) {
+    const A* d = (const A*)g.v0 + vi;
+    const A x[4] = {v[0] * d[0], v[1] * d[1], v[2] * d[2], v[3] * d[3]};
+    put_packed<T>(g.out1, row, col, (int)(g.ldo1 / PkElem<T>::KB), x);
+  }
+}
+
+// One output tile: WN x WM waves, each FN x FM blocks of 16 neurons x 16
+// tangent rows; NS LDS stages of KS K blocks.  The weights are the MFMA's
+// first operand, so lane l holds neurons 4 (l / 16) .. + 3 of tangent row
+// l % 16: four consecutive columns of the row-major outputs.  (The FP64
+// instruction gives lane l its rows l / 16 + 4 e; pack_operand_kernel orders
+// the 16 rows of a weight block to match.)
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+struct PkTile {
+  static constexpr int NP = PkElem<T>::NP;
+  static constexpr int NW = WN * WM;
+  static constexpr int BNB = WN * FN, BMB = WM * FM;  // 16-row blocks of W and P per tile
+  static constexpr int CW = BNB * KS * NP, CP = BMB * KS * NP;  // KiB per stage
+  static constexpr int LW = (CW + NW - 1) / NW, LP = (CP + NW - 1) / NW;
+  static constexpr int CPT = LW + LP;  // DMA loads per wave and stage
+  static constexpr int PBASE = LW * NW * 1024;  // P's blocks follow W's in a stage
+  static constexpr int STAGE = CPT * NW * 1024;
+};
+
+// (GROUPED only names the caller: one instantiation per kernel.)
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS, bool GROUPED>
+__device__ __forceinline__ void pk_tile(const GemmArgs& g, int t, int split, char* st0, char* st1, char* st2,
+                                        char* st3) {
+  using S = PkTile<T, WN, WM, FN, FM, KS, NS>;
+  // distinct LDS arrays, chosen at compile time in each step: the compiler then
+  // waits, before a fragment read, only for loads into that stage
+  auto st = [&](int i) -> char* { return i == 0 ? st0 : i == 1 ? st1 : i == 2 ? st2 : st3; };
+  const int tm = t % g.tiles_m, tn = t / g.tiles_m;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave % WN, wm = wave / WN;
+  constexpr int NP = S::NP, KB = PkElem<T>::KB;
+  const int kt = g.K / KB;
+  const int k0 = split * (g.kper / KB);
+  const int nk = (min(kt, k0 + g.kper / KB) - k0) / KS;  // stages (K and kper are multiples of KB KS)
+  const int nb0 = tn * S::BNB, mb0 = tm * S::BMB;
+  const int nbw = (g.N + 15) >> 4, mbw = (g.M + 15) >> 4;
+  // One buffer resource per operand, from the tile's first block on.
+  const unsigned rowb = (unsigned)kt * NP * 1024u;  // bytes of one 16-row block
+  const int nbv = min(S::BNB, nbw - nb0), mbv = min(S::BMB, mbw - mb0);  // the tile's blocks inside the operands
+  const __amdgpu_buffer_rsrc_t rsW = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const char*)g.B + (long long)nb0 * rowb), (short)0, (int)(nbv * rowb), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsP = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const char*)g.A + (long long)mb0 * rowb), (short)0, (int)(mbv * rowb), 0x00020000);
+  const int vofs = lane * 16;
+  // Chunk c of a stage's operand: block c / (KS NP), K block and part c % (KS NP),
+  // which follow one another in memory as in LDS.  What lies past the tile's
+  // last block, and the loads that only fill a wave's count, read the last
+  // block again (their results are not stored), so every wave issues the same
+  // number of loads per stage and none of them is conditional.
+  int so0[S::CPT];
+#pragma unroll
+  for (int p = 0; p < S::CPT; ++p) {
+    const bool isw = p < S::LW;
+    const int c = (isw ? p : p - S::LW) * S::NW + wave;
+    so0[p] = (int)(min(c / (KS * NP), (isw ? nbv : mbv) - 1) * rowb + (unsigned)(c % (KS * NP)) * 1024u);
+  }
+  auto dma = [&](int s, char* dst) {  // stages past the last one read it again
+    const int ko = (k0 + min(s, nk - 1) * KS) * NP * 1024;
+#pragma unroll
+    for (int p = 0; p < S::CPT; ++p) {
+      const lds_ptr d = (lds_ptr)(dst + (p * S::NW + wave) * 1024);
+      if (p < S::LW)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, d, 16, vofs, so0[p] + ko, 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsP, d, 16, vofs, so0[p] + ko, 0, 0);
+    }
+  };
+  using V = typename PkAcc<T>::V;
+  V acc[FN][FM], low[FN][FM];  // low: the products of the smaller parts (NP = 3)
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) acc[i][j] = low[i][j] = V{0, 0, 0, 0};
+  const int wbase = wn * FN * KS * NP * 1024 + lane * 16;
+  const int pbase = S::PBASE + wm * FM * KS * NP * 1024 + lane * 16;
+  auto compute = [&](const char* sb) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      using Frag = typename std::conditional<sizeof(T) == 8, double2, bf16x8>::type;
+      Frag w[NP][FN], x[NP][FM];
+#pragma unroll
+      for (int p = NP - 1; p >= 0; --p) {
+#pragma unroll
+        for (int i = 0; i < FN; ++i) w[p][i] = *(const Frag*)(sb + wbase + ((i * KS + ks) * NP + p) * 1024);
+#pragma unroll
+        for (int j = 0; j < FM; ++j) x[p][j] = *(const Frag*)(sb + pbase + ((j * KS + ks) * NP + p) * 1024);
+      }
+      if constexpr (sizeof(T) == 8) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? w[0][i].y : w[0][i].x, h ? x[0][j].y : x[0][j].x,
+                                                               acc[i][j], 0, 0, 0);
+      } else {
+        auto prod = [&](int a, int b, V(&to)[FN][FM]) {
+#pragma unroll
+          for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j)
+              to[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[a][i], x[b][j], to[i][j], 0, 0, 0);
+        };
+        if constexpr (NP == 3) {
+          prod(2, 0, low);
+          prod(0, 2, low);
+          prod(1, 1, low);
+          prod(1, 0, low);
+          prod(0, 1, low);
+        }
+        prod(0, 0, acc);
+        if constexpr (NP == 1) __builtin_amdgcn_sched_barrier(0);  // one K block's fragments at a time in registers
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) dma(s, st(s));
+  for (int s0 = 0;; s0 += NS) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      wait_vm<(NS - 2) * S::CPT>();
+      barrier_nofence();
+      dma(s0 + u + NS - 1, st((u + NS - 1) % NS));
+      compute(st(u));
+      if (s0 + u + 1 >= nk) goto done;
+    }
+  }
+done:
+  wait_vm<0>();
+#pragma unroll
+  for (int j = 0; j < FM; ++j) {
+    const int row = (mb0 + wm * FM + j) * 16 + (lane & 15);
+    if (row >= g.M) continue;
+    const int b = row / g.rdiv;
+#pragma unroll
+    for (int i = 0; i < FN; ++i) {
+      const int col = (nb0 + wn * FN + i) * 16 + (lane >> 4) * 4;
+      if (col < g.N) {
+        const V a = NP == 3 ? acc[i][j] + low[i][j] : acc[i][j];
+        const typename PkAcc<T>::A v[4] = {a[0], a[1], a[2], a[3]};
+        pk_epilogue<T>(g, row, col, b, v, split);
+      }
+    }
+  }
+}
+
+// Each XCD takes a contiguous run of tiles (which share weight blocks in its L2).
+__device__ __forceinline__ int pk_xcd(int t, int tiles) {
+  const int full = tiles - tiles % 8;
+  return t < full ? (t % 8) * (full / 8) + t / 8 : t;
+}
+
+#define PK_STAGES                                                                                 \
+  using S = PkTile<T, WN, WM, FN, FM, KS, NS>;                                                   \
+  static_assert(NS >= 2 && NS <= 4 && S::STAGE * NS <= 160 * 1024, "LDS");                        \
+  __shared__ __attribute__((aligned(16))) char st0[S::STAGE];                                     \
+  __shared__ __attribute__((aligned(16))) char st1[S::STAGE];                                     \
+  __shared__ __attribute__((aligned(16))) char st2[NS > 2 ? S::STAGE : 16];                       \
+  __shared__ __attribute__((aligned(16))) char st3[NS > 3 ? S::STAGE : 16]
+
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+__global__ void __launch_bounds__(WN * WM * 64) gemm_pk_kernel(GemmArgs g) {
+  PK_STAGES;
+  pk_tile<T, WN, WM, FN, FM, KS, NS, false>(g, pk_xcd(blockIdx.x, g.tiles_m * g.tiles_n), blockIdx.y, st0, st1, st2, st3);
+}
+
+
+// Persistent grouped launch: workgroup w takes work items w, w + gridDim.x, ...
+// (as gemm_grouped_kernel).
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+__global__ void __launch_bounds__(WN * WM * 64)
+gemm_pk_grouped_kernel(const GemmArgs* __restrict__ groups, const int* __restrict__ offsets, int ngroups) {
+  PK_STAGES;
+  const int total = offsets[ngroups];
+  for (int w = blockIdx.x; w < total; w += gridDim.x) {
+    int gi = 0;
+    while (gi + 1 < ngroups && offsets[gi + 1] <= w) ++gi;
+    const GemmArgs g = groups[gi];
+    pk_tile<T, WN, WM, FN, FM, KS, NS, true>(g, pk_xcd(w - offsets[gi], g.tiles_m * g.tiles_n), 0, st0, st1, st2, st3);
+    __syncthreads();  // every wave done with the stages before the next item refills them
+  }
+}
+#undef PK_STAGES
+
+// Sum of the K slices in slice order through the product's epilogue, four
+// columns per thread.
+template <typename T>
+__global__ void __launch_bounds__(256) pk_reduce_kernel(GemmArgs g, const void* __restrict__ part, int splits) {
+  using A = typename PkAcc<T>::A;
+  using V = typename PkAcc<T>::V;
+  const int q = g.N / 4;
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long long)g.M * q) return;
+  const int row = (int)(i / q);
+  const int col = (int)(i - (long long)row * q) * 4;
+  const long long MN = (long long)g.M * g.N;
+  const A* p = (const A*)part + (long long)row * g.N + col;
+  V t = *(const V*)p;
+#pragma unroll 4
+  for (int s = 1; s < splits; ++s) t += *(const V*)(p + s * MN);
+  const A v[4] = {t[0], t[1], t[2], t[3]};
+  pk_epilogue<T>(g, row, col, row / g.rdiv, v, 0);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) pack_operand_kernel(const T* __restrict__ W, long long ldw, long long total, int K,
+                                                           void* __restrict__ out) {
+  using A = typename PkAcc<T>::A;
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= total) return;
+  const int q = K / 4;
+  const int row = (int)(i / q);
+  const int col = (int)(i - (long long)row * q) * 4;
+  const T* w = W + row * ldw + col;
+  const A v[4] = {(A)w[0], (A)w[1], (A)w[2], (A)w[3]};
+  const int r16 = row & 15;
+  const int prow = sizeof(T) == 8 ? (row - r16) + (r16 >> 2) + 4 * (r16 & 3) : row;
+  put_packed<T>(out, prow, col, K / PkElem<T>::KB, v);
+}
+
+// The tilings.  us1 / us2: time 32 elements of K take a CU for one tile,
+// with one workgroup on it and (us2) with several in turn or at once, measured
+// at 25088 x 8192 x 8192 and 784 x 8192 x 8192 (us2, us1 of the large tiles)
+// and 117 x 4032 x 4032 (us1 of the small ones).
+struct PkCfg {
+  int bm, bn, ks, occ;
+  double us1, us2;
+};
+constexpr int kPkCfgs = 4;
+constexpr PkCfg kPkF32[kPkCfgs] = {
+    {128, 256, 32, 1, 2.05, 2.28},  // 8 waves of 64 x 64
+    {112, 256, 32, 1, 1.87, 2.04},  // 8 waves of 32 x 112: whole tiles of 784 rows
+    {64, 128, 32, 2, 1.00, 0.70},   // 4 waves of 64 x 32
+    {64, 64, 32, 2, 0.75, 0.45},    // 4 waves of 32 x 32
+};
+constexpr PkCfg kPkBf16[kPkCfgs] = {
+    {256, 256, 32, 1, 0.80, 0.97},  // 8 waves of 64 x 128
+    {112, 256, 64, 1, 0.41, 0.49},  // 8 waves of 32 x 112
+    {128, 64, 64, 2, 0.23, 0.29},   // 8 waves of 16 x 64
+    {64, 64, 64, 3, 0.17, 0.15},    // 4 waves of 32 x 32
+};
+constexpr PkCfg kPkF64[kPkCfgs] = {
+    {128, 256, 16, 1, 7.20, 7.20},  // 8 waves of 64 x 64
+    {112, 256, 16, 1, 6.30, 6.30},  // 8 waves of 32 x 112
+    {64, 128, 16, 2, 2.60, 1.90},   // 4 waves of 64 x 32
+    {64, 64, 16, 3, 1.30, 0.95},    // 4 waves of 32 x 32
+};
+
+inline const PkCfg& pk_cfg(DType t, int cfg) {
+  return t == DT_F32 ? kPkF32[cfg] : t == DT_BF16 ? kPkBf16[cfg] : kPkF64[cfg];
+}
+
+// CALL(type, WN, WM, FN, FM, KS, NS) of tiling cfg.
+#define PK_DISPATCH(T, CALL)                        \
+  do {                                              \
+    if constexpr (sizeof(T) == 4) {                 \
+      switch (cfg) {                                \
+        case 0: CALL(float, 4, 2, 4, 4, 1, 2);      \
+        case 1: CALL(float, 8, 1, 2, 7, 1, 2);      \
+        case 2: CALL(float, 2, 2, 4, 2, 1, 2);      \
+        case 3: CALL(float, 2, 2, 2, 2, 1, 3);      \
+        default: return hipErrorInvalidValue;       \
+      }                                             \
+    } else if constexpr (sizeof(T) == 2) {          \
+      switch (cfg) {                                \
+        case 0: CALL(bf16, 4, 2, 4, 8, 1, 4);       \
+        case 1: CALL(bf16, 8, 1, 2, 7, 2, 3);       \
+        case 2: CALL(bf16, 4, 2, 1, 4, 2, 3);       \
+        case 3: CALL(bf16, 2, 2, 2, 2, 2, 3);       \
+        default: return hipErrorInvalidValue;       \
+      }                                             \
+    } else {                                        \
+      switch (cfg) {                                \
+        case 0: CALL(double, 4, 2, 4, 4, 2, 3);     \
+        case 1: CALL(double, 8, 1, 2, 7, 2, 3);     \
+        case 2: CALL(double, 2, 2, 4, 2, 2, 3);     \
+        case 3: CALL(double, 2, 2, 2, 2, 2, 3);     \
+        default: return hipErrorInvalidValue;       \
+      }                                             \
+    }                                               \
+  } while (0)
+
+template <typename T>
+hipError_t pk_launch(int cfg, const GemmArgs& g, int splits, hipStream_t s) {
+  const dim3 grid(g.tiles_m * g.tiles_n, splits);
+#define PK_CALL(T_, WN, WM, FN, FM, KS, NS)                                                            \
+  hipLaunchKernelGGL((gemm_pk_kernel<T_, WN, WM, FN, FM, KS, NS>), grid, dim3(WN * WM * 64), 0, s, g); \
+  return hipGetLastError()
+  PK_DISPATCH(T, PK_CALL);
+#undef PK_CALL
+}
+
+template <typename T>
+hipError_t pk_launch_grouped(int cfg, const GemmArgs* groups, const int* offsets, int ngroups, int grid, hipStream_t s) {
+#define PK_CALL(T_, WN, WM, FN, FM, KS, NS)                                                                    \
+  hipLaunchKernelGGL((gemm_pk_grouped_kernel<T_, WN, WM, FN, FM, KS, NS>), dim3(grid), dim3(WN * WM * 64), 0, \
+                     s, groups, offsets, ngroups);                                                                \
+  return hipGetLastError()
+  PK_DISPATCH(T, PK_CALL);
+#undef PK_CALL
+}
+
+inline int pk_kper(const PkCfg& c, int K, int ks) {
+  return ((K + ks - 1) / ks + c.ks - 1) / c.ks * c.ks;
+}
+
+}  // namespace
+
+// The tiling and K split of the least estimated time: the rounds of tiles a CU
+// takes, each K / ksplit long, and with a split the partials written and read
+// at 4.5 TB/s by one more launch.
+PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes) {
+  PkChoice best{0, 1};
+  double best_us = 1e30;
+  const double psz = t == DT_F64 ? 8.0 : 4.0;  // bytes of a partial
+  for (int i = 0; i < kPkCfgs; ++i) {
+    const PkCfg& c = pk_cfg(t, i);
+    const long long tiles = (long long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    for (int ks = 1; ks <= 8; ++ks) {
+      const int kper = pk_kper(c, K, ks);
+      if ((K + kper - 1) / kper != ks) continue;
+      if (ks > 1 && ks * psz * M * N > (double)part_bytes) break;
+      const long long rounds = (tiles * ks + 255) / 256;
+      double us = kper / 32.0 * (rounds == 1 ? c.us1 : rounds * c.us2) + 4.0;
+      if (ks > 1) us += 4.0 + 2.0 * psz * ks * M * N / 4.5e6;
+      if (us < best_us) {
+        best_us = us;
+        best = PkChoice{i, ks};
+      }
+    }
+  }
+  return best;
+}
+
+size_t pk_operand_bytes(DType t, long long rows, int K) {
+  return (size_t)((rows + 15) / 16 * 16) * K * (t == DT_F32 ? 6 : t == DT_BF16 ? 2 : 8);
+}
+
+hipError_t launch_pack_operand(DType t, const void* W, long long ldw, int rows, int K, void* out, hipStream_t s) {
+  if (rows <= 0 || rows % 16 != 0 || K <= 0 || K % 64 != 0) return hipErrorInvalidValue;
+  const long long total = (long long)rows * (K / 4);
+  const long long blocks = (total + 255) / 256;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+#define PK_PACK(T)                                                                                            \
+  hipLaunchKernelGGL(pack_operand_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, (const T*)W, ldw, total, K, \
+                     out)
+  switch (t) {
+    case DT_F32: PK_PACK(float); break;
+    case DT_BF16: PK_PACK(bf16); break;
+    case DT_F64: PK_PACK(double); break;
+  }
+#undef PK_PACK
+  return hipGetLastError();
+}
+
+void pk_set_tiles(DType t, int cfg, GemmArgs& g) {
+  const PkCfg& c = pk_cfg(t, cfg);
+  g.tiles_m = (g.M + c.bm - 1) / c.bm;
+  g.tiles_n = (g.N + c.bn - 1) / c.bn;
+}
+
+int pk_grouped_occupancy(DType t, int cfg) { return pk_cfg(t, cfg).occ; }
+
+hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (ch.cfg < 0 || ch.cfg >= kPkCfgs || g.K <= 0 || g.K % 64 != 0 || g.N % 16 != 0 ||
+      (ch.ksplit > 1 && !part))
+    return hipErrorInvalidValue;
+  pk_set_tiles(t, ch.cfg, g);
+  GemmArgs p = g;
+  p.kper = pk_kper(pk_cfg(t, ch.cfg), g.K, ch.ksplit);
+  const int splits = (g.K + p.kper - 1) / p.kper;
+  if (splits > 1) {
+    p.epi = EPI_PART;
+    p.out0 = part;
+    p.ldo = g.N;
+    p.split_stride = (long long)g.M * g.N;
+  }
+  hipError_t e = t == DT_F32    ? pk_launch<float>(ch.cfg, p, splits, s)
+                 : t == DT_BF16 ? pk_launch<bf16>(ch.cfg, p, splits, s)
+                                : pk_launch<double>(ch.cfg, p, splits, s);
+  if (e != hipSuccess || splits == 1) return e;
+  const long long blocks = ((long long)g.M * (g.N / 4) + 255) / 256;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks);
+  switch (t) {
+    case DT_F32: hipLaunchKernelGGL(pk_reduce_kernel<float>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
+    case DT_BF16: hipLaunchKernelGGL(pk_reduce_kernel<bf16>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
+    case DT_F64: hipLaunchKernelGGL(pk_reduce_kernel<double>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_pk_grouped(DType t, int cfg, const GemmArgs* groups, const int* offsets, int ngroups, int grid,
+                                  hipStream_t s) {
+  if (grid <= 0) return hipErrorInvalidValue;
+  switch (t) {
+    case DT_F32: return pk_launch_grouped<float>(cfg, groups, offsets, ngroups, grid, s);
+    case DT_BF16: return pk_launch_grouped<bf16>(cfg, groups, offsets, ngroups, grid, s);
+    case DT_F64: return pk_launch_grouped<double>(cfg, groups, offsets, ngroups, grid, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace nnc

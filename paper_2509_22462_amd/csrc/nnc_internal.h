@@ -116,6 +116,27 @@ void gemm_set_tiles(int cfg, GemmArgs& g);
 hipError_t launch_gemm_grouped(DType t, int cfg, bool acc64, const GemmArgs* groups, const int* offsets,
                                int ngroups, int grid, hipStream_t s);
 
+// ---------------------------------------------------------------- packed products
+// Layer-sum sweep products on packed operands (gemm_pk.hip; FP32 and BF16):
+// g.A the packed tangents P_l [M][K], g.B the packed weights [N][K] (K and N
+// multiples of 64), epilogues EPI_FWD_LS / EPI_FWD_LT with out1 packed (ldo1 =
+// its K) and EPI_PART.
+struct PkChoice {
+  int cfg, ksplit;
+};
+// Tiling and K split for an M x N x K product whose K-split partials may take
+// part_bytes.
+PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes);
+size_t pk_operand_bytes(DType t, long long rows, int K);
+hipError_t launch_pack_operand(DType t, const void* W, long long ldw, int rows, int K, void* out, hipStream_t s);
+// One product in ksplit K slices (partials in part, added in slice order).
+hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStream_t s);
+// Persistent grouped launch, as launch_gemm_grouped.
+int pk_grouped_occupancy(DType t, int cfg);
+void pk_set_tiles(DType t, int cfg, GemmArgs& g);
+hipError_t launch_gemm_pk_grouped(DType t, int cfg, const GemmArgs* groups, const int* offsets, int ngroups, int grid,
+                                  hipStream_t s);
+
 // ---------------------------------------------------------------- skinny NT
 // out[r][j] = sum_k X[r][k] * W[j][k] for few rows r (weight streaming).
 enum SkinnyEpi {
@@ -215,9 +236,10 @@ hipError_t launch_finalize_h(const double* part, int splits, long long split_str
                              const double* v, hipStream_t s);
 // Layer-sum seeds of layer 1 (T_1 = W_1): for tangent row r = b*n + j and
 // column k < dp1, T[r][k] = W1T[j][k], S[r][k] = s_1[b][k] * W1T[j][k]
-// (ld ldts), and unless P is null P[r][k] = sigma_1'[b][k] * W1T[j][k] (ld dp1).
+// (ld ldts), and unless P is null P[r][k] = sigma_1'[b][k] * W1T[j][k] (ld dp1,
+// or packed: as an operand of launch_gemm_pk).
 hipError_t launch_seed_layersum(DType t, const void* W1T, int n, int dp1, const void* d1, const double* s1,
-                                int B, void* T, void* S, long long ldts, void* P, hipStream_t s);
+                                int B, void* T, void* S, long long ldts, void* P, bool packed, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // Hp[b][i(i+1)/2 + j] = H[b][i][j], j <= i (row-major lower triangle)
 hipError_t launch_pack_lower(const double* H, int B, int n, double* Hp, hipStream_t s);
@@ -233,6 +255,7 @@ struct Layer {
   int din = 0, dout = 0, dinp = 0, doutp = 0, act = 0;
   void* W = nullptr;   // [doutp][dinp] compute type
   void* WT = nullptr;  // [dinp][doutp] compute type
+  void* Wk = nullptr;  // W as a packed sweep operand (launch_pack_operand), layers 2..Lt of Net::pk_bufs
   void* WTP = nullptr;  // WT packed in the MFMA weight stream's read order (launch_pack_fragments)
   double* b = nullptr;  // [doutp]
   // per-point vectors, [maxB][doutp]
@@ -265,6 +288,9 @@ struct Net {
   double* usm = nullptr;     // SoftMax rank-two vectors u, v [maxB][n]
   double* vsm = nullptr;
   bool for_bufs = false, ls_bufs = false;  // which method's buffers exist
+  // Layer-sum sweep on packed operands: pk_bufs the buffers exist (packed
+  // weights, P_l large enough), pk they are used (no forced tiling or K split).
+  bool pk_bufs = false, pk = false;
   void* TC = nullptr;  // layer-sum T_l of all layers, [maxB*n][Ktot], layer l at column koff[l]
   void* SC = nullptr;  // layer-sum S_l = diag(s_l) T_l, same layout
   int Ktot = 0;
@@ -345,6 +371,7 @@ struct PlannedGemm {
   bool acc64;
   int splits;
   int slot;  // index in the network's tuning table
+  bool pk = false;  // launch_gemm_pk's operands
 };
 
 // Tile edge of the symmetric (lower block triangle) layer-sum H product.
@@ -365,6 +392,7 @@ int internal_seed(Ctx* c, Net* net, int B);
 hipError_t internal_launch_gemm_ks(Net* net, GemmArgs g, bool acc64, int splits, int cfg, int ks,
                                    hipStream_t s);
 bool internal_ksplit_ok(const Net* net, const GemmArgs& g, bool acc64, int splits);
+void internal_update_pk(Ctx* c, Net* net, bool allow);
 int internal_ensure_part(Ctx* c, Net* net, size_t bytes);
 int internal_finalize(Ctx* c, Net* net, int B, int splits, double obj, double* H, int symtile);
 // SoftMax output: the rank-two vectors from the output layer's tangents (after the forward sweep).

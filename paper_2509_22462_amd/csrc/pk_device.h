@@ -1,0 +1,81 @@
+// Packed MFMA operands of the sweep products (gemm_pk.hip): for each block of
+// 16 rows, each 32 elements of K and each part, the KiB that one wave reads as
+// an operand of v_mfma_f32_16x16x32_bf16 (lane l holds row l % 16, elements
+// 8 (l / 16) .. + 7 of the 32).  BF16 elements have one part, FP32 elements
+// three BF16 parts that hold all their bits.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <math.h>
+
+#include "nnc_device.h"
+
+namespace nnc {
+
+template <typename T> struct PkElem {  // BF16
+  static constexpr int NP = 1;   // parts
+  static constexpr int KB = 32;  // elements along K of one block
+};
+template <> struct PkElem<float> {
+  static constexpr int NP = 3;
+  static constexpr int KB = 32;
+};
+template <> struct PkElem<double> {
+  static constexpr int NP = 1;
+  static constexpr int KB = 8;
+};
+
+// The parts of four consecutive elements.
+template <int NP>
+__device__ __forceinline__ void cut_parts(const float (&v)[4], uint2 (&o)[NP]) {
+  if constexpr (NP == 1) {
+    bf16x4 t;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = (bf16)v[e];
+    o[0] = __builtin_bit_cast(uint2, t);
+  } else {
+    // Each part is the leading 8 significant bits of what is left (cut off,
+    // not rounded): the differences are exact, the third part leaves nothing,
+    // and no finite element becomes infinite.  An infinite element is its
+    // first part alone.
+    uint32_t w[3][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      w[0][e] = __float_as_uint(v[e]) & 0xffff0000u;
+      const float r = fabsf(v[e]) == INFINITY ? 0.f : v[e] - __uint_as_float(w[0][e]);
+      w[1][e] = __float_as_uint(r) & 0xffff0000u;
+      w[2][e] = __float_as_uint(r - __uint_as_float(w[1][e]));
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      o[p] = make_uint2((w[p][0] >> 16) | (w[p][1] & 0xffff0000u), (w[p][2] >> 16) | (w[p][3] & 0xffff0000u));
+  }
+}
+
+// Byte offset of element (row, col) of part 0 of an operand with kt blocks
+// along K; part p is p KiB on.
+template <typename T>
+__device__ __forceinline__ long long packed_offset(int row, int col, int kt) {
+  using E = PkElem<T>;
+  constexpr int LANE = E::KB / 4;  // elements of one lane
+  return ((long long)(row >> 4) * kt + col / E::KB) * (E::NP * 1024) + col % E::KB / LANE * 256 + (row & 15) * 16 +
+         col % LANE * (16 / LANE);
+}
+
+// Four consecutive elements (row, col .. col + 3), col a multiple of 4, into a
+// packed operand.
+template <typename T, typename A>
+__device__ __forceinline__ void put_packed(void* base, int row, int col, int kt, const A (&v)[4]) {
+  char* o = (char*)base + packed_offset<T>(row, col, kt);
+  if constexpr (sizeof(T) == 8) {
+    *(double2*)o = make_double2(v[0], v[1]);
+    *(double2*)(o + 256) = make_double2(v[2], v[3]);  // the next lane group's pair
+  } else {
+    constexpr int NP = PkElem<T>::NP;
+    uint2 t[NP];
+    cut_parts<NP>(v, t);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) *(uint2*)(o + p * 1024) = t[p];
+  }
+}
+
+}  // namespace nnc

@@ -9,6 +9,8 @@
 //     the output layer also in FP64 (W_L and W_L^T) for the FP64 residual and
 //     the FP64 lambda-weighted adjoint;
 //   * per point and layer: z_l (FP64), a_l, sigma'_l, zbar_l and s_l;
+//   * layer-sum networks in FP32 and BF16: W_l (l >= 2) once more as packed
+//     MFMA operands (gemm_pk.hip), three BF16 parts per FP32 element;
 //   * tangents stored "transposed", one row per tangent column (b, j):
 //     [B*n][d_l'] so that rows are feature-contiguous; G_l of the reverse
 //     sweep overwrites P_l (consumed by the forward sweep) in place;
@@ -174,6 +176,11 @@ int ensure_part(Ctx* c, Net* net, size_t bytes) {
 
 int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out);
 
+// Most that the K-split partials of one packed product may take: the choice
+// of the split, and so the rounding of a result, must not depend on what the
+// network has allocated for other shapes.
+constexpr size_t kPkPartBytes = (size_t)64 << 20;
+
 // Workspace for the K splits the tuned table (or a forced split) asks for at
 // B = 1 and B = max_points.
 int size_part(Ctx* c, Net* net) {
@@ -190,6 +197,13 @@ int size_part(Ctx* c, Net* net) {
       if (ks > 1) need = std::max(need, (size_t)ks * p.g.M * p.g.N * part_size(net));
     }
   }
+  if (net->pk_bufs)
+    for (int B = 1; B <= net->maxB; ++B)
+      for (int l = 1; l < net->Lt; ++l) {
+        const int M = B * net->n, N = net->ly[l].doutp;
+        const int ks = pk_choose(net->ct, M, N, net->ly[l].dinp, kPkPartBytes).ksplit;
+        if (ks > 1) need = std::max(need, (size_t)ks * M * N * part_size(net));
+      }
   return ensure_part(c, net, need);
 }
 
@@ -206,14 +220,18 @@ void layersum_layout(Net* net) {
 }
 
 // K splits of the symmetric layer-sum product at B points: enough work items
-// for about four workgroups per CU, at most 8 slices, whole K tiles.
+// for about four workgroups per CU, at most 8 slices, whole K tiles.  Fewer
+// than 64 tiles (one point of up to 640 inputs) would leave most CUs without
+// a workgroup at 8 slices: they take as many as make about two per CU, each of
+// 16 K tiles or more.  (117 inputs, K = 152,064, FP32: 3 tiles, 24 workgroups
+// at 8 slices: 522 -> 55 us.)
 int ls_hsplits(const Net* net, int B) {
   const long long tt = (net->n + kSymTile - 1) / kSymTile;
   const long long tiles = (long long)B * tt * (tt + 1) / 2;
-  long long sp = (1024 + tiles - 1) / tiles;
-  sp = std::max(1LL, std::min(8LL, sp));
-  const int ktiles = std::max(1, net->Ktot / (128 / (int)net->csz));
-  return (int)std::min<long long>(sp, ktiles);
+  const long long ktiles = std::max<long long>(1, net->Ktot / (128 / (int)net->csz));
+  long long sp = std::max(1LL, std::min(8LL, (1024 + tiles - 1) / tiles));
+  if (tiles < 64) sp = std::max(sp, std::min(512 / tiles, ktiles / 16));
+  return (int)std::min(sp, ktiles);
 }
 
 // The cheaper method by algorithmic flops of the work they do not share
@@ -251,6 +269,45 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
     if (!p) ok = false;
     return p;
   };
+  // Packed sweep operands: weights, and P_l large enough for the packed form
+  // as well.  Without the memory for them the sweep stays on the row-major
+  // operands below.
+  if (method == NNC_HESS_LAYERSUM && !net->pk_bufs && Lt >= 2) {
+    std::vector<void*> got;
+    auto G = [&](size_t bytes) -> void* {
+      void* p = nullptr;
+      if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      got.push_back(p);
+      return p;
+    };
+    std::vector<void*> P(Lt, nullptr), W(Lt + 1, nullptr);
+    bool have = true;
+    for (int l = 1; have && l < Lt; ++l) {
+      const Layer& nx = net->ly[l];
+      P[l] = G(std::max(N * nx.dinp * net->csz, pk_operand_bytes(net->ct, (long long)N, nx.dinp)));
+      W[l + 1] = P[l] ? G(pk_operand_bytes(net->ct, nx.doutp, nx.dinp)) : nullptr;
+      have = W[l + 1] != nullptr;
+    }
+    if (have) {
+      for (int l = 1; l < Lt; ++l) {
+        if (net->P[l]) {  // the smaller buffer of the other method
+          free_batch(c);
+          NNC_HIP(c, hipDeviceSynchronize());
+          net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), net->P[l]));
+          hipFree(net->P[l]);
+        }
+        net->P[l] = P[l];
+        net->ly[l].Wk = W[l + 1];
+      }
+      net->allocs.insert(net->allocs.end(), got.begin(), got.end());
+      net->pk_bufs = true;
+    } else {
+      for (void* p : got) hipFree(p);
+    }
+  }
   if (Lt >= 2 && !net->P[1])
     for (int l = 1; l <= Lt - 1; ++l) net->P[l] = A(N * net->ly[l - 1].doutp * net->csz);
   if (method == NNC_HESS_FOR && !net->for_bufs) {
@@ -283,6 +340,26 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
   return NNC_OK;
 }
 
+// The packed weights, once the row-major ones are in place (network creation
+// and a change of method: plan time).
+int pack_weights(Ctx* c, Net* net) {
+  if (!net->pk_bufs) return NNC_OK;
+  for (int l = 2; l <= net->Lt; ++l) {
+    Layer& ly = net->ly[l - 1];
+    NNC_HIP(c, launch_pack_operand(net->ct, ly.W, ly.dinp, ly.doutp, ly.dinp, ly.Wk, 0));
+  }
+  NNC_HIP(c, hipDeviceSynchronize());
+  return NNC_OK;
+}
+
+// Whether the sweep runs on packed operands: whenever the network has them,
+// unless the caller forces a tiling or K split of the row-major kernels (or
+// `allow` is false: autotuning times those).
+void update_pk(Ctx* c, Net* net, bool allow) {
+  net->pk = allow && net->pk_bufs && net->hess_method == NNC_HESS_LAYERSUM && c->forced_cfg[net->ct] < 0 &&
+            c->forced_ksplit[net->ct] < 1;
+}
+
 int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kind = NNC_KC_GEMM) {
   int cfg = -1, ks = 1;
   (void)slot;
@@ -300,6 +377,16 @@ int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kin
   if (cfg < 0 || !gemm_cfg_supports(net->ct, cfg, acc64)) cfg = pick_cfg(net, g.M, g.N, acc64);
   NNC_LAUNCH(c, kind, launch_gemm_ks(net, g, acc64, splits, cfg, ks, c->stream));
   return NNC_OK;
+}
+
+// One planned product.
+int run_product(Ctx* c, Net* net, const PlannedGemm& p) {
+  if (p.pk) {
+    const PkChoice ch = pk_choose(net->ct, p.g.M, p.g.N, p.g.K, kPkPartBytes);
+    NNC_LAUNCH(c, NNC_KC_GEMM, launch_gemm_pk(net->ct, ch, p.g, net->part, c->stream));
+    return NNC_OK;
+  }
+  return gemm(c, net, p.slot, p.g, p.acc64, p.splits, p.phase == 2 ? NNC_KC_GEMM_H : NNC_KC_GEMM);
 }
 
 GemmArgs gemm_args(const void* A, long long lda, const void* B, long long ldb, int M, int N, int K) {
@@ -652,7 +739,7 @@ int plan_layersum(Net* net, int B, std::vector<PlannedGemm>& out, bool defer_s =
   for (int l = 1; l <= Lt - 1; ++l, ++slot) {
     Layer& nx = net->ly[l];  // layer l+1
     Layer& cu = net->ly[l - 1];
-    GemmArgs g = gemm_args(net->P[l], cu.doutp, nx.W, nx.dinp, N, nx.doutp, cu.doutp);
+    GemmArgs g = gemm_args(net->P[l], cu.doutp, net->pk ? nx.Wk : nx.W, nx.dinp, N, nx.doutp, cu.doutp);
     g.rdiv = n;
     g.epi = defer_s ? EPI_FWD_LT : EPI_FWD_LS;
     g.out0 = (char*)net->TC + (size_t)net->koff[l + 1] * net->csz;
@@ -663,7 +750,7 @@ int plan_layersum(Net* net, int B, std::vector<PlannedGemm>& out, bool defer_s =
     g.v0 = nx.d1;
     g.v1 = nx.s;
     g.ldv = nx.doutp;
-    out.push_back(PlannedGemm{0, l - 1, g, false, 1, slot});
+    out.push_back(PlannedGemm{0, l - 1, g, false, 1, slot, net->pk});
   }
   GemmArgs g = gemm_args(net->TC, net->Ktot, net->SC, net->Ktot, n, n, net->Ktot);
   g.epi = EPI_H64;
@@ -761,7 +848,7 @@ int run_seed(Ctx* c, Net* net, int B, bool defer_s = false) {
   if (net->hess_method == NNC_HESS_LAYERSUM) {
     NNC_LAUNCH(c, NNC_KC_OTHER, launch_seed_layersum(net->ct, l1.WT, n, l1.doutp, l1.d1, l1.s, B, net->TC,
                                                       defer_s ? nullptr : net->SC, net->Ktot,
-                                                      net->Lt >= 2 ? net->P[1] : nullptr, c->stream));
+                                                      net->Lt >= 2 ? net->P[1] : nullptr, net->pk, c->stream));
     return NNC_OK;
   }
   if (net->Lt == 1) {
@@ -800,7 +887,7 @@ int run_softmax_uv(Ctx* c, Net* net, int B) {
 int run_planned(Ctx* c, Net* net, std::vector<PlannedGemm>& plan, int lo, int hi, int* splits, int* symtile) {
   for (PlannedGemm& p : plan) {
     if (p.phase < lo || p.phase > hi) continue;
-    NNC_TRY(gemm(c, net, p.slot, p.g, p.acc64, p.splits, p.phase == 2 ? NNC_KC_GEMM_H : NNC_KC_GEMM));
+    NNC_TRY(run_product(c, net, p));
     if (p.phase == 2) {
       *splits = p.splits;
       *symtile = p.g.sym;
@@ -898,7 +985,7 @@ int run_hess_overlapped(Ctx* c, Net* net, int B, const double* x, const double* 
     if (p.phase != 0) continue;
     // sweep step idx writes T_{idx+2} with sigma' of layer idx + 2
     if (by_layer) er = hipStreamWaitEvent(c->side, c->ev_layer[p.idx + 1], 0);
-    if (er == hipSuccess) rc = gemm(c, net, p.slot, p.g, p.acc64, p.splits, NNC_KC_GEMM);
+    if (er == hipSuccess) rc = run_product(c, net, p);
   }
   const hipError_t ej = hipEventRecord(c->ev_join, c->side);
   c->stream = main;
@@ -1175,7 +1262,9 @@ int nnc_net_create(nnc_ctx ctx, int L, const int* dims, const int* acts, const d
     if (hipDeviceSynchronize() != hipSuccess) rc = fail(c, NNC_E_HIP, "weight conversion failed");
   }
   hipFree(tmp);
-  if (rc == NNC_OK) rc = size_part(c, net);  // K-split workspace the tuned table asks for
+  if (rc == NNC_OK) rc = pack_weights(c, net);
+  update_pk(c, net, true);
+  if (rc == NNC_OK) rc = size_part(c, net);  // K-split workspace of the sweep's products
   if (rc != NNC_OK) {
     free_net(net);
     return rc;
@@ -1231,7 +1320,9 @@ int nnc_net_set_hess_method(nnc_ctx ctx, int id, int method) {
   NNC_TRY(ensure_hess_bufs(c, net, m));
   if (m != net->hess_method) {
     free_batch(c);  // batched launches are planned per method
+    NNC_TRY(pack_weights(c, net));
     net->hess_method = m;
+    update_pk(c, net, true);
     NNC_TRY(size_part(c, net));
   }
   return NNC_OK;
@@ -1360,6 +1451,8 @@ int nnc_set_gemm_config(nnc_ctx ctx, int prec, int config) {
   if (config < -1 || config >= gemm_num_cfgs()) return fail(c, NNC_E_ARG, "unknown GEMM config");
   c->forced_cfg[dt] = config;
   free_batch(c);  // batched launches are planned with the tiling: re-plan on the next call
+  for (Net* net : c->nets)
+    if (net) update_pk(c, net, true);
   return NNC_OK;
 }
 
@@ -1373,7 +1466,10 @@ int nnc_set_gemm_ksplit(nnc_ctx ctx, int prec, int ksplit) {
   if (hipSetDevice(c->device) != hipSuccess) return fail(c, NNC_E_HIP, "hipSetDevice failed");
   free_batch(c);
   for (Net* net : c->nets)
-    if (net && net->ct == t) NNC_TRY(size_part(c, net));
+    if (net && net->ct == t) {
+      update_pk(c, net, true);
+      NNC_TRY(size_part(c, net));
+    }
   return NNC_OK;
 }
 
@@ -1464,6 +1560,7 @@ hipError_t internal_launch_gemm_ks(Net* net, GemmArgs g, bool acc64, int splits,
 bool internal_ksplit_ok(const Net* net, const GemmArgs& g, bool acc64, int splits) {
   return ksplit_ok(net, g, acc64, splits);
 }
+void internal_update_pk(Ctx* c, Net* net, bool allow) { update_pk(c, net, allow); }
 int internal_ensure_part(Ctx* c, Net* net, size_t bytes) { return ensure_part(c, net, bytes); }
 int internal_finalize(Ctx* c, Net* net, int B, int splits, double obj, double* H, int symtile) {
   return run_finalize(c, net, B, splits, obj, H, symtile);

@@ -18,6 +18,7 @@
 
 #include "nnc_device.h"
 #include "nnc_internal.h"
+#include "pk_device.h"
 
 namespace nnc {
 
@@ -1196,53 +1197,83 @@ hipError_t launch_seed_tangent(DType t, const void* W1T, int n, int dp1, const v
 
 // Layer-sum seeds of layer 1: T_1 = W_1 (rows of W_1^T per tangent column),
 // S_1 = diag(s_1) T_1 and, when a forward product follows, P_1 = D_1 T_1.
-// Block row x = tangent row r = b * n + j, y = chunk of 256 16-byte vectors
-// along the layer: each thread converts one vector (V elements) of row j of
-// W_1^T, elementwise as before, and writes one vector of each output.
-template <typename T, typename VT>
-__global__ void seed_layersum_kernel(const T* W1T, int n, int dp1, const VT* d1, const double* s1, T* Tc, T* Sc,
-                                     long long ldts, T* P) {
+// A wave takes 16 tangent rows (r = b * n + j) and one K block of the packed
+// operand (PACKED: P is the packed operand of the sweep products,
+// pk_device.h), lane l row l % 16 and the LANE elements of lane group l / 16:
+// the packed blocks are written a contiguous KiB at a time and the row-major
+// outputs 128 bytes per row (64 for FP64).  (With a row per workgroup the
+// packed stores of 16 rows met in one 128-byte line from different XCDs:
+// 2.59 instead of 0.90 ms per 122,880 x 2048 FP32 seed.)
+template <typename T, typename VT, bool PACKED>
+__global__ void __launch_bounds__(256) seed_layersum_kernel(const T* W1T, int n, int dp1, int rows, const VT* d1,
+                                                            const double* s1, T* Tc, T* Sc, long long ldts, T* P) {
+  constexpr int LANE = PkElem<T>::KB / 4;
   constexpr int V = 16 / (int)sizeof(T);
-  const int r = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * 16 + (lane & 15);
+  const int k0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * PkElem<T>::KB + (lane >> 4) * LANE;
+  if (r >= rows || k0 >= dp1) return;  // dp1 is a multiple of 64, so of LANE
   const int b = r / n;
   const int j = r - b * n;
-  const int k0 = (blockIdx.y * blockDim.x + threadIdx.x) * V;
-  if (k0 >= dp1) return;  // dp1 is a multiple of 64, so of V
   union Vec {
-    uint4 u;
-    T e[V];
+    uint4 u[LANE / V];
+    T e[LANE];
   };
   Vec w, sv, pv;
-  w.u = *(const uint4*)(W1T + (long long)j * dp1 + k0);
+#pragma unroll
+  for (int v = 0; v < LANE / V; ++v) w.u[v] = *(const uint4*)(W1T + (long long)j * dp1 + k0 + v * V);
   const double* sr = s1 + (long long)b * dp1 + k0;
   const VT* dr = d1 + (long long)b * dp1 + k0;
 #pragma unroll
-  for (int e = 0; e < V; ++e) {
+  for (int e = 0; e < LANE; ++e) {
     const double wd = to_d(w.e[e]);
     if (Sc) sv.e[e] = from_d<T>(wd * sr[e]);
     if (P) pv.e[e] = from_d<T>(wd * (double)dr[e]);
   }
   const long long o = (long long)r * ldts + k0;
-  *(uint4*)(Tc + o) = w.u;
-  if (Sc) *(uint4*)(Sc + o) = sv.u;
-  if (P) *(uint4*)(P + (long long)r * dp1 + k0) = pv.u;
+#pragma unroll
+  for (int v = 0; v < LANE / V; ++v) {
+    *(uint4*)(Tc + o + v * V) = w.u[v];
+    if (Sc) *(uint4*)(Sc + o + v * V) = sv.u[v];
+  }
+  if (!P) return;
+  if constexpr (PACKED && sizeof(T) == 4) {
+    uint2 lo[3], hi[3];
+    const float a[4] = {(float)pv.e[0], (float)pv.e[1], (float)pv.e[2], (float)pv.e[3]};
+    const float c[4] = {(float)pv.e[4], (float)pv.e[5], (float)pv.e[6], (float)pv.e[7]};
+    cut_parts<3>(a, lo);
+    cut_parts<3>(c, hi);
+    char* q = (char*)P + packed_offset<T>(r, k0, dp1 / PkElem<T>::KB);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *(uint4*)(q + p * 1024) = make_uint4(lo[p].x, lo[p].y, hi[p].x, hi[p].y);
+  } else if constexpr (PACKED) {  // a lane's elements are one 16-byte piece
+    *(uint4*)((char*)P + packed_offset<T>(r, k0, dp1 / PkElem<T>::KB)) = pv.u[0];
+  } else {
+#pragma unroll
+    for (int v = 0; v < LANE / V; ++v) *(uint4*)(P + (long long)r * dp1 + k0 + v * V) = pv.u[v];
+  }
 }
 
 hipError_t launch_seed_layersum(DType t, const void* W1T, int n, int dp1, const void* d1, const double* s1,
-                                int B, void* Tc, void* Sc, long long ldts, void* P, hipStream_t s) {
+                                int B, void* Tc, void* Sc, long long ldts, void* P, bool packed, hipStream_t s) {
   const long long rows = (long long)B * n;
   if (rows == 0 || dp1 == 0) return hipSuccess;
   if (rows > 0x7fffffffLL || dp1 % 64 != 0 || ldts % 64 != 0) return hipErrorInvalidValue;
-  const int esz = t == DT_F64 ? 8 : t == DT_F32 ? 4 : 2;
-  const int vecs = dp1 / (16 / esz);
-  const dim3 grid((unsigned)rows, (unsigned)((vecs + 255) / 256));
-#define NNC_SEED_LS(T, VT)                                                                              \
-  hipLaunchKernelGGL((seed_layersum_kernel<T, VT>), grid, dim3(256), 0, s, (const T*)W1T, n, dp1,          \
+  const int kb = t == DT_F64 ? PkElem<double>::KB : PkElem<float>::KB;
+  const dim3 grid((unsigned)((rows + 15) / 16), (unsigned)((dp1 / kb + 3) / 4));
+#define NNC_SEED_LS(T, VT, PK)                                                                          \
+  hipLaunchKernelGGL((seed_layersum_kernel<T, VT, PK>), grid, dim3(256), 0, s, (const T*)W1T, n, dp1, (int)rows, \
                      (const VT*)d1, s1, (T*)Tc, (T*)Sc, ldts, (T*)P)
   switch (t) {
-    case DT_F32: NNC_SEED_LS(float, float); break;
-    case DT_BF16: NNC_SEED_LS(bf16, float); break;
-    case DT_F64: NNC_SEED_LS(double, double); break;
+    case DT_F32:
+      if (packed) NNC_SEED_LS(float, float, true); else NNC_SEED_LS(float, float, false);
+      break;
+    case DT_BF16:
+      if (packed) NNC_SEED_LS(bf16, float, true); else NNC_SEED_LS(bf16, float, false);
+      break;
+    case DT_F64:
+      if (packed) NNC_SEED_LS(double, double, true); else NNC_SEED_LS(double, double, false);
+      break;
   }
 #undef NNC_SEED_LS
   return hipGetLastError();
