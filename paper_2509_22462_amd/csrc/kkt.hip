@@ -28,9 +28,8 @@
 //
 // What bounds it: the chain of n / 64 panels, each with 64 dependent pivots;
 // the products (n^3 / 3 flops per system) run on v_mfma_f64_16x16x4_f64
-// beside it.  16 systems of 784: 606 us, where assembling M, separate launches
-// for the diagonal block, the column solves and the trailing update (FMA, from
-// LDS) and a forward substitution took 3,370 us.
+// beside it.  16 systems of 784: 509 us, where assembling M and three launches
+// per panel took 3,370 us.
 #include <math.h>
 
 #include "../../include/nnc.h"
@@ -105,8 +104,20 @@ __device__ __forceinline__ void kkt_load(const KktArgs& g, int b, int k, const i
     const double* Lb = g.L + (long long)b * g.np * g.ld;
 #pragma unroll
     for (int e = 0; e < N; ++e) v[e] = Lb[i[e] * g.ld + j[e]];
-  } else {
-    kkt_entries<N>(g, b, i, j, v);
+  } else {  // in four parts, for the registers
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      int ih[N / 4], jh[N / 4];
+      double vh[N / 4];
+#pragma unroll
+      for (int e = 0; e < N / 4; ++e) {
+        ih[e] = i[h * (N / 4) + e];
+        jh[e] = j[h * (N / 4) + e];
+      }
+      kkt_entries<N / 4>(g, b, ih, jh, vh);
+#pragma unroll
+      for (int e = 0; e < N / 4; ++e) v[h * (N / 4) + e] = vh[e];
+    }
   }
 }
 
@@ -120,25 +131,25 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
   return __hiloint2double(hi, lo);
 }
 
-// 1 / v and 1 / sqrt(v) of a positive, finite v by Newton's iteration from the
-// hardware's estimate (each step doubles its bits; a last residual step for
-// the rounding): a pivot waits for one of these, and the full-range division
-// took four times as long.  Pivots near the ends of the range take the
-// library's.
-constexpr double kPivotLo = 0x1p-900, kPivotHi = 0x1p900;
+// 1 / v and 1 / sqrt(v) of a positive, finite v: Newton's iteration on the
+// mantissa from the hardware's estimate (24 bits; each step doubles them), the
+// exponent put back, so that the whole FP64 range goes one branch-free way and
+// a pivot's wait can be filled with the updates of the step before (the
+// full-range division took four times as long).
 __device__ __forceinline__ double recip(double v) {
-  if (!(v > kPivotLo && v < kPivotHi)) return 1.0 / v;
-  double r = __builtin_amdgcn_rcp(v);
-  r = fma(fma(-v, r, 1.0), r, r);
-  r = fma(fma(-v, r, 1.0), r, r);
-  return fma(fma(-v, r, 1.0), r, r);
+  const double m = __builtin_amdgcn_frexp_mant(v);
+  double r = __builtin_amdgcn_rcp(m);
+  r = fma(fma(-m, r, 1.0), r, r);
+  return __builtin_amdgcn_ldexp(fma(fma(-m, r, 1.0), r, r), -__builtin_amdgcn_frexp_exp(v));
 }
 __device__ __forceinline__ double recip_sqrt(double v) {
-  if (!(v > kPivotLo && v < kPivotHi)) return 1.0 / sqrt(v);
-  double r = __builtin_amdgcn_rsq(v);
+  const int e = __builtin_amdgcn_frexp_exp(v);
+  // an even exponent: mantissa in [1/2, 2)
+  const double m = __builtin_amdgcn_ldexp(__builtin_amdgcn_frexp_mant(v), e & 1);
+  double r = __builtin_amdgcn_rsq(m);
 #pragma unroll
-  for (int i = 0; i < 3; ++i) r = fma(0.5 * r, fma(-v * r, r, 1.0), r);
-  return r;
+  for (int i = 0; i < 2; ++i) r = fma(0.5 * r, fma(-m * r, r, 1.0), r);
+  return __builtin_amdgcn_ldexp(r, -((e - (e & 1)) / 2));
 }
 
 // Products of this kernel are accumulated transposed: register e of lane l
@@ -146,42 +157,45 @@ __device__ __forceinline__ double recip_sqrt(double v) {
 // at once the B operand of K step e of a following product with X^T, so
 // chained products need no move between lanes.
 
-// Rows row0 .. row0 + 15 of panel k, 64 columns: z[jb] = A - (update by panel k - 1).
-__device__ __forceinline__ void kkt_block(const KktArgs& g, int b, int k, int row0, int lane, doublex4 (&z)[4]) {
+// Rows row0 .. row0 + 15 of panel k, column blocks 0 .. nj - 1 of 16: z[jb] =
+// A - (update by panel k - 1).  xr: the rows' own elements of panel k - 1
+// (kkt_row), Pk: those of rows 64 k .. 64 k + 63.  Lane group q takes columns
+// 16 q .. 16 q + 15 of panel k - 1 in both (a fixed order of the sum).
+__device__ __forceinline__ void kkt_row(const KktArgs& g, int b, int k, int row0, int lane, double2 (&xr)[8]) {
+  const double* p = g.L + ((long long)b * g.np + row0 + (lane & 15)) * g.ld + (k - 1) * KB + 16 * (lane >> 4);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) xr[t] = *(const double2*)(p + 2 * t);
+}
+
+__device__ __forceinline__ void kkt_block(const KktArgs& g, int b, int k, int row0, int nj, int lane,
+                                          const double (*Pk)[KP], const double2 (&xr)[8], const double (&av)[16],
+                                          doublex4 (&z)[4]) {
   const int c16 = lane & 15, q = lane >> 4;
-  const double* Lb = g.L + (long long)b * g.np * g.ld;
-  const int kb = k * KB;
-  int ii[16], jj[16];
-  double av[16];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    ii[e] = row0 + c16;
-    jj[e] = kb + 4 * e + q;
-  }
-  kkt_load<16>(g, b, k, ii, jj, av);
-  doublex4 acc[4];
+  for (int jb = 0; jb < 4; ++jb) {
+    doublex4 acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    if (k > 0 && jb < nj) {
 #pragma unroll
-  for (int jb = 0; jb < 4; ++jb) acc[jb] = doublex4{0, 0, 0, 0};
-  if (k > 0) {
-    // lane group q takes columns 16 q .. 16 q + 15 of panel k - 1, the same for
-    // both operands (a fixed order of the sum), so each lane reads whole lines
-    const double* pr = Lb + (long long)(row0 + c16) * g.ld + kb - KB + 16 * q;
-    const double* pk = Lb + (long long)(kb + c16) * g.ld + kb - KB + 16 * q;
-#pragma unroll
-    for (int t = 0; t < 16; t += 2) {
-      const double2 xr = *(const double2*)(pr + t);
-#pragma unroll
-      for (int jb = 0; jb < 4; ++jb) {
-        const double2 xk = *(const double2*)(pk + (long long)jb * 16 * g.ld + t);
-        acc[jb] = mma64(xk.x, xr.x, acc[jb]);
-        acc[jb] = mma64(xk.y, xr.y, acc[jb]);
+      for (int t = 0; t < 8; ++t) {
+        const double2 xk = *(const double2*)&Pk[jb * 16 + c16][16 * q + 2 * t];
+        acc[0] = mma64(xk.x, xr[t].x, acc[0]);
+        acc[1] = mma64(xk.y, xr[t].y, acc[1]);
       }
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[jb][e] = av[4 * jb + e] - (acc[0][e] + acc[1][e]);
   }
+}
+
+// A's entries of 16 rows from row0, 64 columns of panel k, in z's layout.
+__device__ __forceinline__ void kkt_rows_of_a(const KktArgs& g, int b, int k, int row0, int lane, double (&av)[16]) {
+  int ii[16], jj[16];
 #pragma unroll
-  for (int jb = 0; jb < 4; ++jb)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) z[jb][e] = av[4 * jb + e] - acc[jb][e];
+  for (int e = 0; e < 16; ++e) {
+    ii[e] = row0 + (lane & 15);
+    jj[e] = k * KB + 4 * e + (lane >> 4);
+  }
+  kkt_load<16>(g, b, k, ii, jj, av);
 }
 
 // Factor the 16 x 16 block at columns 16 s of S by one wave: lane c < 16 holds
@@ -196,17 +210,25 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
 #pragma unroll
   for (int i = 0; i < 16; ++i)
     a[i] = lane < 16 ? S[16 * s + max(i, c)][16 * s + min(i, c)] : (lane < 32 && i == c ? 1.0 : 0.0);
-  int fail = 0;
-  double piv = 1.0;  // lane j: pivot j
+  // the next pivot is brought up to date first, and the multipliers are all
+  // read before the first is used: its reciprocal, the chain, runs beside them
+  double r = recip(readlane_d(a[0], 0));
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const double dj = readlane_d(a[j], j);
-    if (!fail && (!(dj > 0.0) || !isfinite(dj))) fail = j + 1;
-    if (lane == j) piv = dj;
-    const double p = a[j] * recip(dj);
+  for (int j = 0; j < 15; ++j) {
+    double u[16];
 #pragma unroll
-    for (int i = j + 1; i < 16; ++i) a[i] = fma(-readlane_d(a[i], j), p, a[i]);
+    for (int i = j + 1; i < 16; ++i) u[i] = readlane_d(a[i], j);
+    const double p = a[j] * r;
+    a[j + 1] = fma(-u[j + 1], p, a[j + 1]);
+    r = recip(readlane_d(a[j + 1], j + 1));
+#pragma unroll
+    for (int i = j + 2; i < 16; ++i) a[i] = fma(-u[i], p, a[i]);
   }
+  double piv = a[0];  // lane j: pivot j
+#pragma unroll
+  for (int j = 1; j < 16; ++j) piv = lane == j ? a[j] : piv;
+  piv = lane < 16 ? piv : 1.0;
+  const unsigned long long bad = __ballot(!(piv > 0.0) || !isfinite(piv));
   const double rs = recip_sqrt(piv);
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
@@ -217,15 +239,54 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
       inv[j][c] = j >= c ? v : 0.0;
     }
   }
-  return fail;
+  return bad ? __ffsll(bad) : 0;
+}
+
+// L^T x = y of one panel's diagonal block by one wave, 16 unknowns at a time:
+// lane l holds unknown l.  at(i, s): row 16 s + i of the block in this lane's
+// column, the inverted 16 x 16 blocks on the diagonal.
+template <typename At>
+__device__ __forceinline__ void kkt_back_block(At at, int lane, double& yi) {
+#pragma unroll
+  for (int s = 3; s >= 0; --s) {
+    double xs[16];  // y of sub-block s, then x
+#pragma unroll
+    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
+    if (lane >> 4 == s) {
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i & 3] = fma(at(i, s), xs[i], v[i & 3]);
+      yi = (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    if (s == 0) break;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
+    if (lane < 16 * s) {
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i & 3] = fma(at(i, s), xs[i], v[i & 3]);
+      yi -= (v[0] + v[1]) + (v[2] + v[3]);
+    }
+  }
 }
 
 // Launch k (see the head of the file).  gridDim = (B, P + tiles): the first
 // P = max(1, panels below k) workgroups of a system factor panel k (workgroup
 // y owns row block k + 1 + y), the others take the lower block triangle of
 // tiles (I, J), I >= J > k, row by row.
-__global__ void __launch_bounds__(256) kkt_panel_kernel(KktArgs g, int k) {
+//
+// A panel's workgroup: wave 0 factors the diagonal block 16 columns at a time,
+// a chain of 64 pivots that everything waits for; waves 1 to 4 (16 rows of the
+// diagonal block and 16 of the workgroup's own block each) work beside it:
+// the own block's update by panel k - 1 during the first 16 pivots, its
+// columns of L during the others'.  Wave 0 brings the next 16 x 16 block up to
+// date itself, so that only the solve with the block just factored stands
+// between two runs of pivots.  16 systems of 784: 42 us a panel when four waves
+// did both in turn, 34 us now.
+constexpr int kPanelThreads = 320;
+__global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, int k, double* __restrict__ x) {
   __shared__ __attribute__((aligned(16))) double S[KB + 1][KP];
+  __shared__ __attribute__((aligned(16))) double Pk[KB][KP];
   __shared__ double inv[4][16][18];
   __shared__ int s_fail;
   const int b = blockIdx.x;
@@ -240,6 +301,7 @@ __global__ void __launch_bounds__(256) kkt_panel_kernel(KktArgs g, int k) {
   const int kb = k * KB;
 
   if ((int)blockIdx.y >= P) {  // A_IJ -= L_I,k-1 L_J,k-1^T, a 32 x 32 quadrant per wave
+    if (wave == 4) return;
     const int t = blockIdx.y - P;
     int ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
     while (ti > 0 && ti * (ti + 1) / 2 > t) --ti;
@@ -289,100 +351,151 @@ __global__ void __launch_bounds__(256) kkt_panel_kernel(KktArgs g, int k) {
     return;
   }
 
-  // the diagonal block and the right-hand side's block (row 64) into LDS
-  {
-    doublex4 z[4];
-    kkt_block(g, b, k, kb + 16 * wave, lane, z);
+  // rows 64 k .. 64 k + 63 of panel k - 1, the diagonal block's and the
+  // right-hand side's entries: all loads before the first wait
+  const int gw = wave - 1;  // row group of waves 1 to 4
+  double2 pre[7], xr[8];
+  double av[16];
+  if (k > 0) {
+#pragma unroll
+    for (int u = 0; u < 7; ++u) {
+      const int t = tid + u * kPanelThreads;  // row t / 32, elements 2 (t % 32) and the next
+      if (t < KB * 32) pre[u] = *(const double2*)(Lb + (long long)(kb + t / 32) * g.ld + kb - KB + 2 * (t % 32));
+    }
+  }
+  if (wave > 0) {
+    if (k > 0) kkt_row(g, b, k, kb + 16 * gw, lane, xr);
+    kkt_rows_of_a(g, b, k, kb + 16 * gw, lane, av);
+  } else {
+    const int i = kb + lane;
+    S[KB][lane] = k > 0 ? g.R[(long long)b * g.np + i] : (i < g.n ? g.r[(long long)b * g.n + i] : 0.0);
+    if (lane == 0) s_fail = 0;
+  }
+  if (k > 0) {
+#pragma unroll
+    for (int u = 0; u < 7; ++u) {
+      const int t = tid + u * kPanelThreads;
+      if (t < KB * 32) *(double2*)&Pk[t / 32][2 * (t % 32)] = pre[u];
+    }
+  }
+  __syncthreads();
+  doublex4 z[4];
+  if (wave > 0) {
+    kkt_block(g, b, k, kb + 16 * gw, gw + 1, lane, Pk, xr, av, z);
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb)
+      if (jb <= gw) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) S[16 * wave + c16][16 * jb + 4 * e + q] = z[jb][e];
-    if (tid < KB) {
-      const int i = kb + tid;
-      S[KB][tid] = k > 0 ? g.R[(long long)b * g.np + i] : (i < g.n ? g.r[(long long)b * g.n + i] : 0.0);
-    }
-    if (tid == 0) s_fail = 0;
+        for (int e = 0; e < 4; ++e) S[16 * gw + c16][16 * jb + 4 * e + q] = z[jb][e];
+      }
   }
-  // this workgroup's own block, taken meanwhile
-  const int row0 = (k + 1 + blockIdx.y) * KB + 16 * wave;
-  doublex4 z[4];
-  if (below > 0) kkt_block(g, b, k, row0, lane, z);
   __syncthreads();
+  const int row0 = (k + 1 + blockIdx.y) * KB + 16 * gw;  // this wave's rows of the own block
+  double dot = 0.0;                                      // this lane's part of (L_ik y_k)
+  // X_s^T = L_ss^-1 (A_s^T - sum_{t < s} L_st X_t^T) of the own rows
+  auto own_columns = [&](int s) {
+    doublex4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < s) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = mma64(S[16 * s + c16][16 * t + 4 * e + q], z[t][e], acc);
+      }
+    const doublex4 w = (s == 0 ? z[0] : s == 1 ? z[1] : s == 2 ? z[2] : z[3]) - acc;
+    doublex4 xs = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xs = mma64(inv[s][c16][4 * e + q], w[e], xs);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (t == s) z[t] = xs;
+    double* o = Lb + (long long)(row0 + c16) * g.ld + kb + 16 * s + q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[4 * e] = xs[e];
+      dot = fma(xs[e], S[KB][16 * s + 4 * e + q], dot);
+    }
+  };
+  // S[row][16 j ..] -= (column block s of row) (column block s of block row j)^T
+  auto trail = [&](int s, int i, int j) {
+    const bool rhs = i == 4;
+    const int row = rhs ? KB : 16 * i + c16;
+    doublex4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double bv = !rhs || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
+      acc = mma64(S[16 * j + c16][16 * s + 4 * e + q], bv, acc);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (!rhs || c16 == 0) S[row][16 * j + 4 * e + q] -= acc[e];
+  };
+#pragma unroll
   for (int s = 0; s < 4; ++s) {
     if (wave == 0) {
       const int f = kkt_factor16(S, s, inv[s], lane);
       if (f && lane == 0) s_fail = kb + 16 * s + f;
+    } else if (below > 0) {
+      if (s == 0) {
+        if (k > 0) kkt_row(g, b, k, row0, lane, xr);
+        kkt_rows_of_a(g, b, k, row0, lane, av);
+        kkt_block(g, b, k, row0, 4, lane, Pk, xr, av, z);
+      } else {
+        own_columns(s - 1);
+      }
     }
     __syncthreads();
     if (s_fail) {
       if (blockIdx.y == 0 && tid == 0) g.info[b] = s_fail;
+      if (nblk == 1 && tid < g.n) x[(long long)b * g.n + tid] = 0.0;
       return;
     }
-    // blocks below (wave i: block row i > s; wave 0: the right-hand side): X = A L_ss^-T
+    // blocks below (row group i > s; wave 0: the right-hand side): X = A L_ss^-T
     const bool rhs = wave == 0;
-    if (rhs || wave > s) {
-      const int row = rhs ? KB : 16 * wave + c16;
-      doublex4 x = {0, 0, 0, 0};
+    if (rhs || gw > s) {
+      const int row = rhs ? KB : 16 * gw + c16;
+      doublex4 xs = {0, 0, 0, 0};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const double bv = !rhs || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
-        x = mma64(inv[s][c16][4 * e + q], bv, x);
+        xs = mma64(inv[s][c16][4 * e + q], bv, xs);
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (!rhs || c16 == 0) S[row][16 * s + 4 * e + q] = x[e];
+        if (!rhs || c16 == 0) S[row][16 * s + 4 * e + q] = xs[e];
     }
     __syncthreads();
-    // trailing blocks (i, j), s < j <= i <= 3, and (right-hand side, j)
-    int id = 0;
-    for (int j = s + 1; j < 4; ++j)
-      for (int i = j; i <= 4; ++i, ++id) {
-        if ((id & 3) != wave) continue;
-        const bool r = i == 4;
-        const int row = r ? KB : 16 * i + c16;
-        doublex4 acc = {0, 0, 0, 0};
+    if (s == 3) break;
+    // block (s + 1, s + 1) by wave 0, the others (i = 4: the right-hand side) by the row groups
+    if (wave == 0) {
+      trail(s, s + 1, s + 1);
+    } else {
+      int id = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const double bv = !r || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
-          acc = mma64(S[16 * j + c16][16 * s + 4 * e + q], bv, acc);
+      for (int j = s + 1; j < 4; ++j)
+#pragma unroll
+        for (int i = j; i <= 4; ++i) {
+          if (i == s + 1 && j == s + 1) continue;
+          if ((id++ & 3) == gw) trail(s, i, j);
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (!r || c16 == 0) S[row][16 * j + 4 * e + q] -= acc[e];
-      }
-    __syncthreads();
+    }
   }
   if (blockIdx.y == 0) {
-    double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
-    for (int idx = tid; idx < KB * KB; idx += 256) {
-      const int i = idx / KB, j = idx % KB;
-      Dk[idx] = i / 16 == j / 16 ? inv[i / 16][i % 16][j % 16] : S[i][j];
+    if (below > 0 || k > 0) {
+      double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
+      for (int idx = tid; idx < KB * KB; idx += kPanelThreads) {
+        const int i = idx / KB, j = idx % KB;
+        Dk[idx] = i / 16 == j / 16 ? inv[i / 16][i % 16][j % 16] : S[i][j];
+      }
+      if (tid < KB) g.Y[(long long)b * g.np + kb + tid] = S[KB][tid];
+    } else if (wave == 0) {  // one panel: L^T x = y here
+      double yi = S[KB][lane];
+      kkt_back_block([&](int i, int s) { return lane >> 4 == s ? inv[s][i][c16] : S[16 * s + i][lane]; }, lane, yi);
+      if (lane < g.n) x[(long long)b * g.n + lane] = yi;
     }
-    if (tid < KB) g.Y[(long long)b * g.np + kb + tid] = S[KB][tid];
     if (k == 0 && tid == 0) g.info[b] = 0;
   }
-  if (below == 0) return;
-  // X_s^T = L_ss^-1 (A_s^T - sum_{t < s} L_st X_t^T), 16 rows per wave
-  double dot = 0.0;  // this lane's part of (L_ik y_k)
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    doublex4 acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int t = 0; t < s; ++t)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc = mma64(S[16 * s + c16][16 * t + 4 * e + q], z[t][e], acc);
-    const doublex4 w = z[s] - acc;
-    doublex4 x = {0, 0, 0, 0};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x = mma64(inv[s][c16][4 * e + q], w[e], x);
-    z[s] = x;
-    double* o = Lb + (long long)(row0 + c16) * g.ld + kb + 16 * s + q;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[4 * e] = x[e];
-      dot = fma(x[e], S[KB][16 * s + 4 * e + q], dot);
-    }
-  }
+  if (wave == 0 || below == 0) return;
+  own_columns(3);
   dot += __shfl_xor(dot, 16, 64);
   dot += __shfl_xor(dot, 32, 64);
   if (q == 0) {
@@ -433,28 +546,7 @@ __global__ void __launch_bounds__(1024) kkt_back_kernel(KktArgs g, double* __res
     for (int i = 0; i < PF; ++i) pre[i] = tid < kb ? p[(long long)i * g.ld] : 0.0;
     if (tid < 64) {
       double yi = y[kb + lane];
-#pragma unroll
-      for (int s = 3; s >= 0; --s) {
-        double xs[16];  // y of sub-block s, then x
-#pragma unroll
-        for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
-        if (lane >> 4 == s) {
-          double v[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int i = 0; i < 16; ++i) v[i & 3] = fma(D[16 * s + i][lane], xs[i], v[i & 3]);
-          yi = (v[0] + v[1]) + (v[2] + v[3]);
-        }
-        if (s > 0) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
-          if (lane < 16 * s) {
-            double v[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[i & 3] = fma(D[16 * s + i][lane], xs[i], v[i & 3]);
-            yi -= (v[0] + v[1]) + (v[2] + v[3]);
-          }
-        }
-      }
+      kkt_back_block([&](int i, int s) { return D[16 * s + i][lane]; }, lane, yi);
       y[kb + lane] = yi;
       if (kb + lane < g.n) xb[kb + lane] = yi;
     }
@@ -578,9 +670,10 @@ int nnc_kkt_solve(nnc_ctx ctx, int kkt, int B, const double* H, const double* d,
   for (int p = 0; p < nblk; ++p) {
     const int below = nblk - p - 1;
     const int tiles = p > 0 ? below * (below + 1) / 2 : 0;
-    hipLaunchKernelGGL(kkt_panel_kernel, dim3(B, (below > 0 ? below : 1) + tiles), dim3(256), 0, c->stream, g, p);
+    hipLaunchKernelGGL(kkt_panel_kernel, dim3(B, (below > 0 ? below : 1) + tiles), dim3(kPanelThreads), 0, c->stream, g, p,
+                       dx);
   }
-  hipLaunchKernelGGL(kkt_back_kernel, dim3(B), dim3(1024), 0, c->stream, g, dx);
+  if (nblk > 1) hipLaunchKernelGGL(kkt_back_kernel, dim3(B), dim3(1024), 0, c->stream, g, dx);
   const hipError_t e = hipGetLastError();
   prof_end(c, &pr);
   if (e != hipSuccess) {

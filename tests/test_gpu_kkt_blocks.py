@@ -74,3 +74,23 @@ def test_pivots_over_the_fp64_range(ctx):
     dx, info = solve(ctx, np.zeros((1, n, n)), d, None, None, r)
     assert info[0] == 0
     assert np.max(np.abs(dx[0] / np.linspace(1.0, 2.0, n) - 1.0)) < 8 * 2.0 ** -53
+
+
+@pytest.mark.parametrize("n,bad", [(1, 0), (1, None), (16, 15), (17, 16), (64, 0), (64, 63), (64, None), (65, 64)])
+def test_one_panel_solved_or_zeroed(ctx, n, bad):
+    """Up to 64 unknowns are factored and solved in one launch."""
+    rng = np.random.default_rng(100 + n)
+    G = rng.standard_normal((2, n, n)) / np.sqrt(n)
+    H = 0.5 * (G + G.transpose(0, 2, 1))
+    d = 3.0 + rng.random((2, n))
+    if bad is not None:
+        d[1, bad] = -50.0
+    r = rng.standard_normal((2, n))
+    dx, info = solve(ctx, H, d, None, None, r)
+    assert info.tolist() == [0, 0 if bad is None else bad + 1]
+    for b in range(2 if bad is None else 1):
+        M = H[b] + np.diag(d[b])
+        res = np.linalg.norm(M @ dx[b] - r[b])
+        assert res < 1e-15 * max(n, 8) * (np.linalg.norm(M, 2) * np.linalg.norm(dx[b]) + np.linalg.norm(r[b]))
+    if bad is not None:
+        assert np.all(dx[1] == 0.0)
