@@ -35,6 +35,7 @@ struct GroupLaunch {
   int cfg = 0;
   bool acc64 = false;
   bool pk = false;  // packed products
+  int edge = 0;     // > 0: their symmetric ones, of this tile edge
   int ngroups = 0;
   int grid = 0;
   GemmArgs* dargs = nullptr;
@@ -99,13 +100,14 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     }
   }
   const DType ct = nets.empty() ? DT_F32 : nets[0]->ct;
-  auto add_launch = [&](int phase, int idx, bool pk) -> int {
+  // (edge: the symmetric packed products of that tile edge; 0 for all others)
+  auto add_launch = [&](int phase, int idx, bool pk, int edge) -> int {
     std::vector<std::pair<GemmArgs, int>> groups;  // (args, splits)
     bool acc64 = false, sym = false;
     long long work = 0;
     for (int i = 0; i < njobs; ++i)
       for (const PlannedGemm& p : per[i])
-        if (p.phase == phase && p.idx == idx && p.pk == pk) {
+        if (p.phase == phase && p.idx == idx && p.pk == pk && (!edge || p.g.sym == edge)) {
           groups.push_back({p.g, p.splits});
           acc64 = p.acc64;
           sym = sym || p.g.sym > 0;
@@ -128,7 +130,7 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
       cfg = c->forced_cfg[ct];
     if (!gemm_grouped_supports(ct, cfg, acc64)) cfg = 3;
     // packed products: the tiling their largest one would take alone
-    if (pk) {
+    if (pk && !edge) {
       const GemmArgs* big = &groups[0].first;
       for (const auto& gr : groups)
         if ((long long)gr.first.M * gr.first.N * gr.first.K > (long long)big->M * big->N * big->K) big = &gr.first;
@@ -136,7 +138,7 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     }
     // symmetric layer-sum products need square tiles of their own edge
     // (the 64 x 64 tiling also serves any other H product of the launch)
-    if (sym) cfg = kSymCfg;
+    if (sym) cfg = edge ? 0 : kSymCfg;
     long long total = 0;
     std::vector<int> offs(1, 0);
     // cost per tile ~ K / splits: most expensive groups first
@@ -148,7 +150,9 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     std::vector<GemmArgs> args;
     for (auto& gr : groups) {
       GemmArgs g = gr.first;
-      if (pk)
+      if (edge)
+        g.tiles_m = g.tiles_n = (g.M + edge - 1) / edge;
+      else if (pk)
         pk_set_tiles(ct, cfg, g);
       else
         gemm_set_tiles(cfg, g);
@@ -160,8 +164,9 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     L.cfg = cfg;
     L.acc64 = acc64;
     L.pk = pk;
+    L.edge = edge;
     L.ngroups = (int)args.size();
-    const int occ = pk ? pk_grouped_occupancy(ct, cfg) : gemm_grouped_occupancy(cfg);
+    const int occ = edge ? pk_sym_occupancy(edge) : pk ? pk_grouped_occupancy(ct, cfg) : gemm_grouped_occupancy(cfg);
     L.grid = (int)std::min<long long>(total, (long long)kCUs * occ);
     void* a = nullptr;
     void* o = nullptr;
@@ -177,15 +182,19 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     return NNC_OK;
   };
   for (int s = 0; s < maxf; ++s) {
-    int rc = add_launch(0, s, true);  // networks on packed operands, then the others
-    if (!rc) rc = add_launch(0, s, false);
+    int rc = add_launch(0, s, true, 0);  // networks on packed operands, then the others
+    if (!rc) rc = add_launch(0, s, false, 0);
     if (rc) return rc;
   }
   for (int r = 0; r < maxr; ++r) {
-    int rc = add_launch(1, r, false);
+    int rc = add_launch(1, r, false, 0);
     if (rc) return rc;
   }
-  return add_launch(2, 0, false);
+  for (int edge : {128, 64}) {
+    int rc = add_launch(2, 0, true, edge);
+    if (rc) return rc;
+  }
+  return add_launch(2, 0, false, 0);
 }
 
 // The captured sequence.
@@ -203,7 +212,9 @@ int record(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, int njobs
   for (const GroupLaunch& L : plan->launches) {
     ProfRec pr;
     prof_begin(c, NNC_KC_GEMM, &pr);
-    if (L.pk)
+    if (L.edge)
+      B_HIP(c, launch_gemm_pk_sym_grouped(nets[0]->ct, L.edge, L.dargs, L.doffs, L.ngroups, L.grid, c->stream));
+    else if (L.pk)
       B_HIP(c, launch_gemm_pk_grouped(nets[0]->ct, L.cfg, L.dargs, L.doffs, L.ngroups, L.grid, c->stream));
     else
       B_HIP(c, launch_gemm_grouped(nets[0]->ct, L.cfg, L.acc64, L.dargs, L.doffs, L.ngroups, L.grid, c->stream));

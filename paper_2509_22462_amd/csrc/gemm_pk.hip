@@ -14,7 +14,7 @@
 // FP32 (NP = 3): x = hi + mid + lo, each the leading 8 significant bits of
 // what is left, so the three parts hold all 24 bits (cut_parts below), and
 //   x y = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + O(2^-24 x y),
-// six BF16 products accumulated in FP32, smallest first: at 16x the rate of
+// six BF16 products accumulated in FP32: at 16x the rate of
 // the FP32 instruction they cost 6/16 of its time.  The dropped terms are a
 // quarter ulp of each product.  The five smaller products have accumulators of
 // their own, so the large ones are rounded by one product in six: on normally
@@ -24,7 +24,7 @@
 // What bounds it: the matrix cores and the LDS reads that feed them (each
 // three-part fragment pair feeds six MFMAs, a BF16 pair one).  Measured with
 // the sweep's epilogue, against the tuned tilings of the row-major kernels:
-// FP32 25,088 x 8192 x 8192 24.2 -> 15.0 ms (139 -> 225 TF/s), 784 x 8192 x 8192
+// FP32 25,088 x 8192 x 8192 24.2 -> 14.1 ms (139 -> 239 TF/s), 784 x 8192 x 8192
 // 0.83 -> 0.55 ms; BF16 the same shapes 3.67 -> 3.15 ms and 0.118 -> 0.106 ms;
 // FP64 784 x 8192 x 8192 1.93 -> 1.75 ms.
 #include <algorithm>
@@ -79,6 +79,35 @@ __device__ __forceinline__ void put4(T* o, const A (&x)[4]) {
   }
 }
 
+// Four consecutive elements of T (row i of point b) as U = sqrt|s| T and, from
+// the point's first row, the signs of s.
+template <typename T, typename A>
+__device__ __forceinline__ void put_u(const PackedU& u, int b, int i, int col, const double* s, const A (&v)[4]) {
+  const double2 s0 = *(const double2*)s;
+  const double2 s1 = *(const double2*)(s + 2);
+  const double sd[4] = {s0.x, s0.y, s1.x, s1.y};
+  A x[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(A) == 8)
+      x[e] = v[e] * sqrt(fabs(sd[e]));
+    else
+      x[e] = v[e] * sqrtf(fabsf((float)sd[e]));
+  }
+  put_packed<T>(u.U, b * u.np16 + i, col, u.kt, x);
+  if (i != 0) return;
+  char* o = (char*)u.sgn + (long long)b * u.kt * 64;
+  uint32_t h[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) h[e] = (uint32_t)__double2hiint(sd[e]) & 0x80000000u;
+  if constexpr (sizeof(T) == 8) {
+    *(uint4*)(o + (long long)col * 8) = make_uint4(0u, h[0], 0u, h[1]);
+    *(uint4*)(o + (long long)col * 8 + 16) = make_uint4(0u, h[2], 0u, h[3]);
+  } else {
+    *(uint2*)(o + (long long)col * 2) = make_uint2((h[0] >> 16) | h[1], (h[2] >> 16) | h[3]);
+  }
+}
+
 // Four consecutive results of one row through the epilogue of g.epi.
 template <typename T>
 __device__ __forceinline__ void pk_epilogue(const GemmArgs& g, int row, int col, int b,
@@ -88,14 +117,16 @@ __device__ __forceinline__ void pk_epilogue(const GemmArgs& g, int row, int col,
     put4<A, A>((A*)g.out0 + (long long)split * g.split_stride + (long long)row * g.ldo + col, v);
     return;
   }
-  const long long o = (long long)row * g.ldo + col;
   const long long vi = (long long)b * g.ldv + col;
-  put4<T, A>((T*)g.out0 + o, v);
+  if (g.out0) put4<T, A>((T*)g.out0 + (long long)row * g.ldo + col, v);
   if (g.out2) {
-    const double2 s0 = *(const double2*)((const double*)g.v1 + vi);
-    const double2 s1 = *(const double2*)((const double*)g.v1 + vi + 2);
-    const A x[4] = {v[0] * (A)s0.x, v[1] * (A)s0.y, v[2] * (A)s1.x, v[3] * (A)s1.y};
-    put4<T, A>((T*)g.out2 + o, x);
+    const double* sv = (const double*)g.v1 + vi;
+    if constexpr (sizeof(T) == 2) {  // BF16: S_l, row-major
+      const A x[4] = {v[0] * (A)sv[0], v[1] * (A)sv[1], v[2] * (A)sv[2], v[3] * (A)sv[3]};
+      put4<T, A>((T*)g.out2 + (long long)row * g.ldo + col, x);
+    } else {
+      put_u<T>(g.u, b, row - b * g.u.n, g.ucol + col, sv, v);
+    }
   }
   if (g.out1) {
     const A* d = (const A*)g.v0 + vi;
@@ -179,45 +210,72 @@ __device__ __forceinline__ void pk_tile(const GemmArgs& g, int t, int split, cha
     for (int j = 0; j < FM; ++j) acc[i][j] = low[i][j] = V{0, 0, 0, 0};
   const int wbase = wn * FN * KS * NP * 1024 + lane * 16;
   const int pbase = S::PBASE + wm * FM * KS * NP * 1024 + lane * 16;
+  using Frag = typename std::conditional<sizeof(T) == 8, double2, bf16x8>::type;
+  struct Frags {
+    Frag w[NP][FN], x[NP][FM];
+  };
+  // one K block's fragments, in the order the products below want them: the
+  // first product waits for two of the six groups (all planes of one operand
+  // first: 6 % slower.  Two halves of the workgroup taking turns at reading and
+  // multiplying, a barrier between: 12 % slower)
+  auto load = [&](const char* sb, int ks, Frags& f) {
+    auto lw = [&](int p) {
+#pragma unroll
+      for (int i = 0; i < FN; ++i) f.w[p][i] = *(const Frag*)(sb + wbase + ((i * KS + ks) * NP + p) * 1024);
+    };
+    auto lx = [&](int p) {
+#pragma unroll
+      for (int j = 0; j < FM; ++j) f.x[p][j] = *(const Frag*)(sb + pbase + ((j * KS + ks) * NP + p) * 1024);
+    };
+    if constexpr (NP == 3) {
+      lx(0);
+      lw(2);
+      lw(1);
+      lx(1);
+      lw(0);
+      lx(2);
+    } else {
+      lw(0);
+      lx(0);
+    }
+  };
+  auto mul = [&](const Frags& f) {
+    if constexpr (sizeof(T) == 8) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < FN; ++i)
+#pragma unroll
+          for (int j = 0; j < FM; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? f.w[0][i].y : f.w[0][i].x,
+                                                             h ? f.x[0][j].y : f.x[0][j].x, acc[i][j], 0, 0, 0);
+    } else {
+      auto prod = [&](int a, int b, V(&to)[FN][FM]) {
+#pragma unroll
+        for (int i = 0; i < FN; ++i)
+#pragma unroll
+          for (int j = 0; j < FM; ++j)
+            to[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[a][i], f.x[b][j], to[i][j], 0, 0, 0);
+      };
+      if constexpr (NP == 3) {
+        prod(2, 0, low);
+        prod(1, 0, low);
+        prod(1, 1, low);
+        prod(0, 1, low);
+        prod(0, 0, acc);
+        prod(0, 2, low);
+      } else {
+        prod(0, 0, acc);
+      }
+    }
+  };
   auto compute = [&](const char* sb) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      using Frag = typename std::conditional<sizeof(T) == 8, double2, bf16x8>::type;
-      Frag w[NP][FN], x[NP][FM];
-#pragma unroll
-      for (int p = NP - 1; p >= 0; --p) {
-#pragma unroll
-        for (int i = 0; i < FN; ++i) w[p][i] = *(const Frag*)(sb + wbase + ((i * KS + ks) * NP + p) * 1024);
-#pragma unroll
-        for (int j = 0; j < FM; ++j) x[p][j] = *(const Frag*)(sb + pbase + ((j * KS + ks) * NP + p) * 1024);
-      }
-      if constexpr (sizeof(T) == 8) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int i = 0; i < FN; ++i)
-#pragma unroll
-            for (int j = 0; j < FM; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? w[0][i].y : w[0][i].x, h ? x[0][j].y : x[0][j].x,
-                                                               acc[i][j], 0, 0, 0);
-      } else {
-        auto prod = [&](int a, int b, V(&to)[FN][FM]) {
-#pragma unroll
-          for (int i = 0; i < FN; ++i)
-#pragma unroll
-            for (int j = 0; j < FM; ++j)
-              to[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[a][i], x[b][j], to[i][j], 0, 0, 0);
-        };
-        if constexpr (NP == 3) {
-          prod(2, 0, low);
-          prod(0, 2, low);
-          prod(1, 1, low);
-          prod(1, 0, low);
-          prod(0, 1, low);
-        }
-        prod(0, 0, acc);
-        if constexpr (NP == 1) __builtin_amdgcn_sched_barrier(0);  // one K block's fragments at a time in registers
-      }
+      Frags f;
+      load(sb, ks, f);
+      mul(f);
+      if constexpr (NP == 1 && sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);  // one K block in registers
     }
   };
 #pragma unroll
@@ -290,16 +348,28 @@ gemm_pk_grouped_kernel(const GemmArgs* __restrict__ groups, const int* __restric
 #undef PK_STAGES
 
 // Sum of the K slices in slice order through the product's epilogue, four
-// columns per thread.
+// columns per lane.  FP32 and FP64: a wave takes 16 rows x 16 columns as in the
+// tiles, so that the packed results leave in half KiB blocks (lanes along a row
+// wrote an eighth of each: 784 x 4096 in FP32, two slices: 19.7 -> 12.0 us).
+// BF16, whose row-major results are as many bytes as the packed ones: along a
+// row (15 us, against 24).
 template <typename T>
 __global__ void __launch_bounds__(256) pk_reduce_kernel(GemmArgs g, const void* __restrict__ part, int splits) {
   using A = typename PkAcc<T>::A;
   using V = typename PkAcc<T>::V;
-  const int q = g.N / 4;
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)g.M * q) return;
-  const int row = (int)(i / q);
-  const int col = (int)(i - (long long)row * q) * 4;
+  const int lane = threadIdx.x & 63;
+  int row, col;
+  if constexpr (sizeof(T) == 2) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    row = (int)(i / (g.N / 4));
+    col = (int)(i % (g.N / 4)) * 4;
+  } else {
+    const int wc = g.N / 16;
+    const long long w = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    row = (int)(w / wc) * 16 + (lane & 15);
+    col = (int)(w % wc) * 16 + (lane >> 4) * 4;
+  }
+  if (row >= g.M) return;
   const long long MN = (long long)g.M * g.N;
   const A* p = (const A*)part + (long long)row * g.N + col;
   V t = *(const V*)p;
@@ -325,6 +395,261 @@ __global__ void __launch_bounds__(256) pack_operand_kernel(const T* __restrict__
   put_packed<T>(out, prow, col, K / PkElem<T>::KB, v);
 }
 
+// ---------------------------------------------------------------- symmetric product
+// H_b = sum_k sign(s_k) U_ik U_jk over all layers' columns: the lower block
+// triangle of square tiles, both operands from the one packed U; a stage holds
+// the tile's row blocks, its column blocks and the K blocks' signs, which are
+// XORed into the column fragments.  FP32 sums are added into FP64 every 64
+// elements of K, as the row-major kernel does.  One operand is written by the
+// sweep and read here where T and S = diag(s) T were.  137M network, FP32: 229
+// -> 150 us at one point, 5.8 -> 4.0 ms at 32; the surrogate batch's 5.2 -> 3.8.
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+struct SymTile {
+  static constexpr int NP = PkElem<T>::NP;
+  static constexpr int NW = WN * WM;
+  static constexpr int EB = WN * FN;  // 16-row blocks of the tile's edge
+  static_assert(EB == WM * FM, "square tiles");
+  static constexpr int CW = EB * KS * NP;             // KiB per stage and operand
+  static constexpr int LW = (CW + NW - 1) / NW;       // loads per wave and operand
+  static constexpr int CPT = 2 * LW + 1;              // and one of signs
+  static constexpr int PBASE = LW * NW * 1024;
+  static constexpr int SBASE = 2 * PBASE;
+  static constexpr int STAGE = SBASE + NW * 1024;
+};
+
+// (GROUPED only names the caller.)
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS, bool GROUPED>
+__device__ __forceinline__ void sym_tile(const GemmArgs& g, int t, int split, char* st0, char* st1, char* st2) {
+  using S = SymTile<T, WN, WM, FN, FM, KS, NS>;
+  constexpr int NP = S::NP, KB = PkElem<T>::KB;
+  constexpr int FOLD = 2;  // K blocks per fold into FP64 (FP32)
+  static_assert(KS <= S::NW && FOLD % KS == 0, "one K block of signs per wave; whole stages per fold");
+  auto st = [&](int i) -> char* { return i == 0 ? st0 : i == 1 ? st1 : st2; };
+  const int per = g.tiles_m * (g.tiles_m + 1) / 2;
+  const int b = t / per;
+  t -= b * per;
+  int ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (ti > 0 && ti * (ti + 1) / 2 > t) --ti;
+  while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+  const int tj = t - ti * (ti + 1) / 2;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave % WN, wm = wave / WN;
+  const int kt = g.u.kt;
+  const int k0 = split * (g.kper / KB);
+  const int nk = (min(kt, k0 + g.kper / KB) - k0) / KS;
+  const int nb = g.u.np16 >> 4;
+  const unsigned rowb = (unsigned)kt * NP * 1024u;
+  const char* U = (const char*)g.u.U + (long long)b * nb * rowb;
+  const int nvi = min(S::EB, nb - ti * S::EB), nvj = min(S::EB, nb - tj * S::EB);
+  const __amdgpu_buffer_rsrc_t rsI = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(U + (long long)ti * S::EB * rowb), (short)0, (int)(nvi * rowb), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsJ = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(U + (long long)tj * S::EB * rowb), (short)0, (int)(nvj * rowb), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)((const char*)g.u.sgn + (long long)b * kt * 64), (short)0, kt * 64, 0x00020000);
+  const int vofs = lane * 16;
+  const int sofs = (lane >> 4) * 16;
+  int so0[2 * S::LW];  // as in pk_tile: what lies past the last block reads it again
+#pragma unroll
+  for (int p = 0; p < 2 * S::LW; ++p) {
+    const bool isi = p < S::LW;
+    const int c = (isi ? p : p - S::LW) * S::NW + wave;
+    so0[p] = (int)(min(c / (KS * NP), (isi ? nvi : nvj) - 1) * rowb + (unsigned)(c % (KS * NP)) * 1024u);
+  }
+  auto dma = [&](int s, char* dst) {
+    const int kb = k0 + min(s, nk - 1) * KS;
+#pragma unroll
+    for (int p = 0; p < 2 * S::LW; ++p) {
+      const lds_ptr d = (lds_ptr)(dst + (p * S::NW + wave) * 1024);
+      if (p < S::LW)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsI, d, 16, vofs, so0[p] + kb * NP * 1024, 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsJ, d, 16, vofs, so0[p] + kb * NP * 1024, 0, 0);
+    }
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsS, (lds_ptr)(dst + S::SBASE + wave * 1024), 16, sofs,
+                                             (kb + wave % KS) * 64, 0, 0);
+  };
+  using V = typename PkAcc<T>::V;
+  V acc[FN][FM];
+  double sum[sizeof(T) == 8 ? 1 : FN][sizeof(T) == 8 ? 1 : FM][4];
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+      acc[i][j] = V{0, 0, 0, 0};
+      if constexpr (sizeof(T) < 8) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[i][j][e] = 0.0;
+      }
+    }
+  auto fold = [&]() {
+    if constexpr (sizeof(T) < 8) {
+#pragma unroll
+      for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[i][j][e] += (double)acc[i][j][e];
+          acc[i][j] = V{0, 0, 0, 0};
+        }
+    }
+  };
+  const int ibase = wn * FN * KS * NP * 1024 + lane * 16;
+  const int jbase = S::PBASE + wm * FM * KS * NP * 1024 + lane * 16;
+  auto compute = [&](const char* sb) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 w[NP][FN], x[NP][FM];
+      const uint4 sg = *(const uint4*)(sb + S::SBASE + ks * 1024 + lane * 16);
+      auto lw = [&](int p) {
+#pragma unroll
+        for (int i = 0; i < FN; ++i) w[p][i] = *(const uint4*)(sb + ibase + ((i * KS + ks) * NP + p) * 1024);
+      };
+      auto lx = [&](int p) {
+#pragma unroll
+        for (int j = 0; j < FM; ++j) {
+          const uint4 v = *(const uint4*)(sb + jbase + ((j * KS + ks) * NP + p) * 1024);
+          x[p][j] = make_uint4(v.x ^ sg.x, v.y ^ sg.y, v.z ^ sg.z, v.w ^ sg.w);
+        }
+      };
+      if constexpr (NP == 3) {  // in the order the products want them
+        lx(0);
+        lw(2);
+        lw(1);
+        lx(1);
+        lw(0);
+        lx(2);
+      } else {
+        lw(0);
+        lx(0);
+      }
+      if constexpr (sizeof(T) == 8) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j) {
+              const double2 wd = __builtin_bit_cast(double2, w[0][i]), xd = __builtin_bit_cast(double2, x[0][j]);
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? wd.y : wd.x, h ? xd.y : xd.x, acc[i][j], 0, 0, 0);
+            }
+      } else {
+        auto prod = [&](int pa, int pb) {
+#pragma unroll
+          for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[pa][i]),
+                                                                  __builtin_bit_cast(bf16x8, x[pb][j]), acc[i][j], 0, 0, 0);
+        };
+        if constexpr (NP == 3) {
+          prod(2, 0);
+          prod(1, 0);
+          prod(1, 1);
+          prod(0, 1);
+          prod(0, 0);
+          prod(0, 2);
+        } else {
+          prod(0, 0);
+        }
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) dma(s, st(s));
+  for (int s0 = 0;; s0 += NS) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      wait_vm<(NS - 2) * S::CPT>();
+      barrier_nofence();
+      dma(s0 + u + NS - 1, st((u + NS - 1) % NS));
+      compute(st(u));
+      if ((s0 + u + 1) % (FOLD / KS) == 0) fold();
+      if (s0 + u + 1 >= nk) goto done;
+    }
+  }
+done:
+  wait_vm<0>();
+  fold();
+  double* H = (double*)g.out0 + (long long)split * g.split_stride + b * g.bsO;
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = (ti * S::EB + wn * FN + i) * 16 + (sizeof(T) == 8 ? (lane >> 4) + 4 * e : (lane >> 4) * 4 + e);
+      if (row >= g.M) continue;
+#pragma unroll
+      for (int j = 0; j < FM; ++j) {
+        const int col = (tj * S::EB + wm * FM + j) * 16 + (lane & 15);
+        if (col < g.N) {
+          if constexpr (sizeof(T) == 8)
+            H[(long long)row * g.ldo + col] = acc[i][j][e];
+          else
+            H[(long long)row * g.ldo + col] = sum[i][j][e];
+        }
+      }
+    }
+}
+
+#define SYM_STAGES                                                                \
+  using S = SymTile<T, WN, WM, FN, FM, KS, NS>;                                   \
+  static_assert(NS >= 2 && NS <= 3 && S::STAGE * NS <= 160 * 1024, "LDS");        \
+  __shared__ __attribute__((aligned(16))) char st0[S::STAGE];                     \
+  __shared__ __attribute__((aligned(16))) char st1[S::STAGE];                     \
+  __shared__ __attribute__((aligned(16))) char st2[NS > 2 ? S::STAGE : 16]
+
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+__global__ void __launch_bounds__(WN * WM * 64) gemm_pk_sym_kernel(GemmArgs g) {
+  SYM_STAGES;
+  sym_tile<T, WN, WM, FN, FM, KS, NS, false>(g, pk_xcd(blockIdx.x, gemm_tiles_per_split(g)), blockIdx.y, st0, st1, st2);
+}
+
+template <typename T, int WN, int WM, int FN, int FM, int KS, int NS>
+__global__ void __launch_bounds__(WN * WM * 64)
+gemm_pk_sym_grouped_kernel(const GemmArgs* __restrict__ groups, const int* __restrict__ offsets, int ngroups) {
+  SYM_STAGES;
+  const int total = offsets[ngroups];
+  for (int w = blockIdx.x; w < total; w += gridDim.x) {
+    int gi = 0;
+    while (gi + 1 < ngroups && offsets[gi + 1] <= w) ++gi;
+    const GemmArgs g = groups[gi];
+    const int local = w - offsets[gi];
+    const int tiles = gemm_tiles_per_split(g);
+    sym_tile<T, WN, WM, FN, FM, KS, NS, true>(g, pk_xcd(local % tiles, tiles), local / tiles, st0, st1, st2);
+    __syncthreads();
+  }
+}
+#undef SYM_STAGES
+
+// U from row-major T: a wave takes 16 rows of a point and 32 columns of a
+// layer, lane l row l % 16 and columns 4 (l / 16) .. + 3 of each half.
+template <typename T>
+__global__ void __launch_bounds__(256) pack_u_kernel(PackUArgs a) {
+  using A = typename PkAcc<T>::A;
+  const int lane = threadIdx.x & 63;
+  const int nb = a.u.np16 >> 4;
+  const int b = blockIdx.x / nb;
+  const int i = (blockIdx.x - b * nb) * 16 + (lane & 15);
+  int cx = blockIdx.y, l = 0;  // blocks of 128 columns, layer by layer
+  for (; l < a.layers; ++l) {
+    const int nch = (a.dp[l] + 127) / 128;
+    if (cx < nch) break;
+    cx -= nch;
+  }
+  if (l >= a.layers || i >= a.u.n) return;
+  const int dp = a.dp[l];
+  const T* t = l == 0 && a.T1 ? (const T*)a.T1 + (long long)i * a.ld1
+                              : (const T*)a.Tc + (long long)(b * a.u.n + i) * a.ld + a.koff[l];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int c = cx * 128 + (threadIdx.x >> 6) * 32 + h * 16 + (lane >> 4) * 4;
+    if (c >= dp) return;
+    const A v[4] = {(A)t[c], (A)t[c + 1], (A)t[c + 2], (A)t[c + 3]};
+    put_u<T>(a.u, b, i, a.koff[l] + c, a.s[l] + (long long)b * dp + c, v);
+  }
+}
+
 // The tilings.  us1 / us2: time 32 elements of K take a CU for one tile,
 // with one workgroup on it and (us2) with several in turn or at once, measured
 // at 25088 x 8192 x 8192 and 784 x 8192 x 8192 (us2, us1 of the large tiles)
@@ -335,7 +660,7 @@ struct PkCfg {
 };
 constexpr int kPkCfgs = 4;
 constexpr PkCfg kPkF32[kPkCfgs] = {
-    {128, 256, 32, 1, 2.05, 2.28},  // 8 waves of 64 x 64
+    {128, 256, 32, 1, 2.00, 2.20},  // 8 waves of 64 x 64
     {112, 256, 32, 1, 1.87, 2.04},  // 8 waves of 32 x 112: whole tiles of 784 rows
     {64, 128, 32, 2, 1.00, 0.70},   // 4 waves of 64 x 32
     {64, 64, 32, 2, 0.75, 0.45},    // 4 waves of 32 x 32
@@ -470,6 +795,7 @@ int pk_grouped_occupancy(DType t, int cfg) { return pk_cfg(t, cfg).occ; }
 
 hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (t != DT_BF16 && g.out2 && (!g.u.U || !g.u.sgn || g.u.n <= 0)) return hipErrorInvalidValue;
   if (ch.cfg < 0 || ch.cfg >= kPkCfgs || g.K <= 0 || g.K % 64 != 0 || g.N % 16 != 0 ||
       (ch.ksplit > 1 && !part))
     return hipErrorInvalidValue;
@@ -487,13 +813,107 @@ hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStrea
                  : t == DT_BF16 ? pk_launch<bf16>(ch.cfg, p, splits, s)
                                 : pk_launch<double>(ch.cfg, p, splits, s);
   if (e != hipSuccess || splits == 1) return e;
-  const long long blocks = ((long long)g.M * (g.N / 4) + 255) / 256;
+  const long long blocks = ((long long)((g.M + 15) / 16) * (g.N / 16) + 3) / 4;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
   switch (t) {
     case DT_F32: hipLaunchKernelGGL(pk_reduce_kernel<float>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
     case DT_BF16: hipLaunchKernelGGL(pk_reduce_kernel<bf16>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
     case DT_F64: hipLaunchKernelGGL(pk_reduce_kernel<double>, grid, dim3(256), 0, s, g, (const void*)part, splits); break;
+  }
+  return hipGetLastError();
+}
+
+// Tile edge: 128 where its tiles, at two thirds of the 64-wide ones' time per
+// area, take less than those.
+int pk_sym_edge(int n) {
+  const double t64 = (n + 63) / 64, t128 = (n + 127) / 128;
+  return t128 * (t128 + 1) * 128 * 128 * 0.67 < t64 * (t64 + 1) * 64 * 64 ? 128 : 64;
+}
+
+int pk_sym_occupancy(int edge) { return edge == 128 ? 1 : 2; }
+
+size_t pk_u_bytes(DType t, int n, int B, int K) {
+  return pk_operand_bytes(t, (long long)B * ((n + 15) / 16 * 16), K);
+}
+
+#define SYM_DISPATCH(CALL)                                                     \
+  do {                                                                         \
+    if (edge == 128) {                                                         \
+      switch (t) {                                                             \
+        case DT_F32: CALL(float, 2, 4, 4, 2, 1, 2);                            \
+        case DT_F64: CALL(double, 2, 4, 4, 2, 2, 3);                           \
+        default: break;                                                        \
+      }                                                                        \
+    } else if (edge == 64) {                                                   \
+      switch (t) {                                                             \
+        case DT_F32: CALL(float, 2, 2, 2, 2, 1, 2);                            \
+        case DT_F64: CALL(double, 2, 2, 2, 2, 2, 3);                           \
+        default: break;                                                        \
+      }                                                                        \
+    }                                                                          \
+    return hipErrorInvalidValue;                                               \
+  } while (0)
+
+hipError_t launch_gemm_pk_sym(DType t, GemmArgs g, int splits, hipStream_t s) {
+  if (g.M <= 0 || g.nbat <= 0) return hipSuccess;
+  if (g.M != g.N || g.kper <= 0 || g.kper % 64 != 0 || g.u.kt <= 0) return hipErrorInvalidValue;
+  const int edge = g.sym;
+  g.tiles_m = g.tiles_n = edge > 0 ? (g.M + edge - 1) / edge : 0;
+  const dim3 grid(gemm_tiles_per_split(g), splits);
+#define SYM_CALL(T, WN, WM, FN, FM, KS, NS)                                                                     \
+  hipLaunchKernelGGL((gemm_pk_sym_kernel<T, WN, WM, FN, FM, KS, NS>), grid, dim3(WN * WM * 64), 0, s, g); \
+  return hipGetLastError()
+  SYM_DISPATCH(SYM_CALL);
+#undef SYM_CALL
+}
+
+hipError_t launch_gemm_pk_sym_grouped(DType t, int edge, const GemmArgs* groups, const int* offsets, int ngroups,
+                                      int grid, hipStream_t s) {
+  if (grid <= 0) return hipErrorInvalidValue;
+#define SYM_CALL(T, WN, WM, FN, FM, KS, NS)                                                                      \
+  hipLaunchKernelGGL((gemm_pk_sym_grouped_kernel<T, WN, WM, FN, FM, KS, NS>), dim3(grid), dim3(WN * WM * 64), 0, \
+                     s, groups, offsets, ngroups);                                                              \
+  return hipGetLastError()
+  SYM_DISPATCH(SYM_CALL);
+#undef SYM_CALL
+}
+
+// Time of a round of tiles (32 elements of K: 1.1 / 3.6 us at edge 128 in
+// FP32 / FP64, 0.37 of it per tile at edge 64) against the partials
+// written and read back.  A slice keeps 512 elements or more.
+int pk_sym_splits(DType t, int n, int B, int K) {
+  const int edge = pk_sym_edge(n);
+  const double tt = (n + edge - 1) / edge;
+  const double tiles = B * tt * (tt + 1) / 2;
+  const double us = (t == DT_F32 ? 1.1 : 3.6) * (edge == 128 ? 1.0 : 0.37);
+  int best = 1;
+  double best_us = 1e30;
+  for (int sp = 1; sp <= 256 && (sp == 1 || K / sp >= 512); ++sp) {
+    const double rounds = (double)(((long long)(tiles * sp) + 255) / 256);
+    const double c = rounds * (K / 32.0 / sp) * us + sp * (0.1 + (double)B * n * n * 16.0 / 4.5e6) + (sp > 16 ? 5.0 : 0.0);
+    if (c < best_us) {
+      best_us = c;
+      best = sp;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_pack_u(DType t, const PackUArgs& a, hipStream_t s) {
+  if (a.B <= 0 || a.layers <= 0) return hipSuccess;
+  if (a.layers > kMaxScaleLayers || a.ld % 4 != 0 || a.ld1 % 4 != 0) return hipErrorInvalidValue;
+  long long chunks = 0;
+  for (int l = 0; l < a.layers; ++l) {
+    if (a.dp[l] % 64 != 0 || a.koff[l] % 64 != 0) return hipErrorInvalidValue;
+    chunks += (a.dp[l] + 127) / 128;
+  }
+  if (chunks > 65535) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(a.B * (a.u.np16 / 16)), (unsigned)chunks);
+  switch (t) {
+    case DT_F32: hipLaunchKernelGGL(pack_u_kernel<float>, grid, dim3(256), 0, s, a); break;
+    case DT_BF16: return hipErrorInvalidValue;
+    case DT_F64: hipLaunchKernelGGL(pack_u_kernel<double>, grid, dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }

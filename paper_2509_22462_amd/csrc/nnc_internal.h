@@ -45,6 +45,18 @@ enum GemmEpi {
   EPI_FWD_LT = 15,
 };
 
+// The layer-sum product's packed operand (gemm_pk.hip): per point, rows = its n
+// tangent columns padded to np16 (a multiple of 16), K = the layers' padded
+// widths side by side (kt blocks).  U = sqrt|s_l| T_l, so that H = sum over k
+// of sign(s_k) U_ik U_jk reads one operand; sgn holds 64 bytes per point and K
+// block: the sign bits of s where an element's own sign bits are (16 bits per
+// BF16 part, 64 per FP64 element).
+struct PackedU {
+  void* U;
+  void* sgn;
+  int n, np16, kt;
+};
+
 struct GemmArgs {
   const void* A;
   const void* B;
@@ -79,6 +91,10 @@ struct GemmArgs {
   int nbat;
   int sym;
   long long bsA, bsB, bsO;
+  // Packed sweep products in FP32 and FP64: with out2 set, U_l = sqrt|s_l| T_l
+  // goes into u (in place of S_l, which BF16 writes to out2) at column ucol.
+  int ucol;
+  PackedU u;
 };
 
 // Output tiles of one K split of a product (all its batches).
@@ -131,6 +147,32 @@ size_t pk_operand_bytes(DType t, long long rows, int K);
 hipError_t launch_pack_operand(DType t, const void* W, long long ldw, int rows, int K, void* out, hipStream_t s);
 // One product in ksplit K slices (partials in part, added in slice order).
 hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStream_t s);
+// Symmetric layer-sum product on a PackedU (g.u; g.M = g.N = n, g.K, g.kper,
+// out0, ldo, split_stride, nbat, bsO and sym = pk_sym_edge(n) set): the lower
+// block triangle of tiles of edge sym, FP64 across chunks of K.
+int pk_sym_edge(int n);
+constexpr int kPkSymUnit = 64;  // slices are multiples of this many K elements
+int pk_sym_splits(DType t, int n, int B, int K);  // K slices of the least estimated time
+hipError_t launch_gemm_pk_sym(DType t, GemmArgs g, int splits, hipStream_t s);
+hipError_t launch_gemm_pk_sym_grouped(DType t, int edge, const GemmArgs* groups, const int* offsets, int ngroups,
+                                      int grid, hipStream_t s);
+int pk_sym_occupancy(int edge);
+// U and its signs from T and s: entry 0 is layer 1 when T1 is given (T_1 =
+// W_1^T, row-major [n][ld1], the same at every point); the other layers' T are
+// columns koff[l] .. of Tc (one row per point and tangent column, ld).
+constexpr int kMaxScaleLayers = 64;
+struct PackUArgs {
+  const void* T1;
+  long long ld1;
+  const void* Tc;
+  long long ld;
+  int B, layers;
+  const double* s[kMaxScaleLayers];  // [B][dp]
+  int koff[kMaxScaleLayers], dp[kMaxScaleLayers];
+  PackedU u;
+};
+hipError_t launch_pack_u(DType t, const PackUArgs& a, hipStream_t s);
+size_t pk_u_bytes(DType t, int n, int B, int K);
 // Persistent grouped launch, as launch_gemm_grouped.
 int pk_grouped_occupancy(DType t, int cfg);
 void pk_set_tiles(DType t, int cfg, GemmArgs& g);
@@ -179,7 +221,6 @@ struct SkinnyArgs {
 // forward sweep wrote T without S (the sweep then needs no adjoint):
 // row r = b * n + i of Tc / Sc (ld Ktot), layer l's columns koff[l] ..
 // koff[l] + dp[l], s_l = s[l] ([B][dp[l]] doubles).
-constexpr int kMaxScaleLayers = 64;
 struct LsScaleArgs {
   const void* Tc;
   void* Sc;
@@ -231,7 +272,8 @@ hipError_t launch_jac_seed(DType at, const double* WL, int m, int K, int Kp, con
 // diagonal (edge symtile): below it H[i][j] = sum_s P[s][i][j], above it
 // sum_s P[s][j][i], within a diagonal tile the symmetrised sum.
 // u, v [B][n] (or NULL): subtract u_i v_j + v_i u_j (a SoftMax output's rank-two term).
-hipError_t launch_finalize_h(const double* part, int splits, long long split_stride, int B, int n,
+// (part is overwritten where there are more than 16 splits)
+hipError_t launch_finalize_h(double* part, int splits, long long split_stride, int B, int n,
                              double obj, const double* q, double* H, int symtile, const double* u,
                              const double* v, hipStream_t s);
 // Layer-sum seeds of layer 1 (T_1 = W_1): for tangent row r = b*n + j and
@@ -292,7 +334,8 @@ struct Net {
   // weights, P_l large enough), pk they are used (no forced tiling or K split).
   bool pk_bufs = false, pk = false;
   void* TC = nullptr;  // layer-sum T_l of all layers, [maxB*n][Ktot], layer l at column koff[l]
-  void* SC = nullptr;  // layer-sum S_l = diag(s_l) T_l, same layout
+  void* SC = nullptr;  // layer-sum S_l = diag(s_l) T_l, same layout; the packed U_l when pk
+  void* sgn = nullptr;  // signs of s beside the packed U_l (PackedU)
   int Ktot = 0;
   std::vector<int> koff;  // column offset of layer l (1..Lt) in TC / SC
   size_t hpart_bytes = 0;
@@ -371,7 +414,7 @@ struct PlannedGemm {
   bool acc64;
   int splits;
   int slot;  // index in the network's tuning table
-  bool pk = false;  // launch_gemm_pk's operands
+  bool pk = false;  // launch_gemm_pk's (phase 2: launch_gemm_pk_sym's) operands
 };
 
 // Tile edge of the symmetric (lower block triangle) layer-sum H product.

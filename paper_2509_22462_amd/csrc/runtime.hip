@@ -219,7 +219,7 @@ void layersum_layout(Net* net) {
   net->Ktot = k;
 }
 
-// K splits of the symmetric layer-sum product at B points: enough work items
+// K splits of the row-major symmetric layer-sum product at B points: enough work items
 // for about four workgroups per CU, at most 8 slices, whole K tiles.  Fewer
 // than 64 tiles (one point of up to 640 inputs) would leave most CUs without
 // a workgroup at 8 slices: they take as many as make about two per CU, each of
@@ -254,7 +254,10 @@ size_t hpart_need(const Net* net) {
   size_t need = 0;
   if (net->for_bufs) need = (size_t)net->hsplit * net->maxB * nn8;
   if (net->ls_bufs)
-    for (int B = 1; B <= net->maxB; ++B) need = std::max(need, (size_t)ls_hsplits(net, B) * B * nn8);
+    for (int B = 1; B <= net->maxB; ++B) {
+      need = std::max(need, (size_t)ls_hsplits(net, B) * B * nn8);
+      if (net->pk_bufs && net->ct != DT_BF16) need = std::max(need, (size_t)pk_sym_splits(net->ct, net->n, B, net->Ktot) * B * nn8);
+    }
   return need;
 }
 
@@ -269,10 +272,10 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
     if (!p) ok = false;
     return p;
   };
-  // Packed sweep operands: weights, and P_l large enough for the packed form
-  // as well.  Without the memory for them the sweep stays on the row-major
-  // operands below.
-  if (method == NNC_HESS_LAYERSUM && !net->pk_bufs && Lt >= 2) {
+  // Packed operands: weights, P_l large enough for the packed form as well, and
+  // U in the place of S with its signs.  Without the memory for them the sweep
+  // stays on the row-major operands below.
+  if (method == NNC_HESS_LAYERSUM && !net->ls_bufs && Lt >= 2) {
     std::vector<void*> got;
     auto G = [&](size_t bytes) -> void* {
       void* p = nullptr;
@@ -291,7 +294,15 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
       W[l + 1] = P[l] ? G(pk_operand_bytes(net->ct, nx.doutp, nx.dinp)) : nullptr;
       have = W[l + 1] != nullptr;
     }
+    void *U = nullptr, *sgn = nullptr;
+    if (have && net->ct != DT_BF16) {
+      U = G(std::max(N * net->Ktot * net->csz, pk_u_bytes(net->ct, net->n, net->maxB, net->Ktot)));
+      sgn = U ? G((size_t)net->maxB * net->Ktot * (net->ct == DT_F64 ? 8 : 2)) : nullptr;
+      have = sgn != nullptr;
+    }
     if (have) {
+      net->SC = U;
+      net->sgn = sgn;
       for (int l = 1; l < Lt; ++l) {
         if (net->P[l]) {  // the smaller buffer of the other method
           free_batch(c);
@@ -318,7 +329,7 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
   if (method == NNC_HESS_LAYERSUM && !net->ls_bufs) {
     if (Lt >= 1) {
       net->TC = A(N * net->Ktot * net->csz);
-      net->SC = A(N * net->Ktot * net->csz);
+      if (!net->SC) net->SC = A(N * net->Ktot * net->csz);
     }
     net->ls_bufs = true;
   }
@@ -379,8 +390,21 @@ int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kin
   return NNC_OK;
 }
 
+// Whether the layer-sum product reads the packed U (FP32 and FP64).  BF16 keeps
+// T and S: T_1 = W_1 is exact there, where sqrt|s| T_1 would be rounded once
+// more (error of H of the 137M network 0.0062 -> 0.0065), for no time gained.
+bool packed_h(const Net* net) { return net->pk && net->ct != DT_BF16; }
+
+PackedU packed_u(const Net* net) {
+  return PackedU{net->SC, net->sgn, net->n, round_up(net->n, 16), net->Ktot / (net->ct == DT_F64 ? 8 : 32)};
+}
+
 // One planned product.
 int run_product(Ctx* c, Net* net, const PlannedGemm& p) {
+  if (p.pk && p.phase == 2) {
+    NNC_LAUNCH(c, NNC_KC_GEMM_H, launch_gemm_pk_sym(net->ct, p.g, p.splits, c->stream));
+    return NNC_OK;
+  }
   if (p.pk) {
     const PkChoice ch = pk_choose(net->ct, p.g.M, p.g.N, p.g.K, kPkPartBytes);
     NNC_LAUNCH(c, NNC_KC_GEMM, launch_gemm_pk(net->ct, ch, p.g, net->part, c->stream));
@@ -750,7 +774,29 @@ int plan_layersum(Net* net, int B, std::vector<PlannedGemm>& out, bool defer_s =
     g.v0 = nx.d1;
     g.v1 = nx.s;
     g.ldv = nx.doutp;
+    if (packed_h(net)) {
+      // T_l itself only where U is formed later, and for a SoftMax's u and v
+      if (!defer_s && !(net->softmax_out && l + 1 == net->L)) g.out0 = nullptr;
+      if (!defer_s) g.out2 = net->SC;
+      g.ucol = net->koff[l + 1];
+      g.u = packed_u(net);
+    }
     out.push_back(PlannedGemm{0, l - 1, g, false, 1, slot, net->pk});
+  }
+  if (packed_h(net)) {
+    GemmArgs h = gemm_args(nullptr, 0, nullptr, 0, n, n, net->Ktot);
+    h.epi = EPI_H64;
+    h.out0 = net->Hpart;
+    h.ldo = n;
+    h.split_stride = (long long)N * n;
+    h.nbat = B;
+    h.sym = pk_sym_edge(n);
+    h.bsO = (long long)n * n;
+    h.u = packed_u(net);
+    const int sp = pk_sym_splits(net->ct, n, B, net->Ktot);
+    h.kper = round_up((net->Ktot + sp - 1) / sp, kPkSymUnit);
+    out.push_back(PlannedGemm{2, 0, h, !fp64, (net->Ktot + h.kper - 1) / h.kper, slot, true});
+    return NNC_OK;
   }
   GemmArgs g = gemm_args(net->TC, net->Ktot, net->SC, net->Ktot, n, n, net->Ktot);
   g.epi = EPI_H64;
@@ -840,11 +886,37 @@ int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out) {
   return NNC_OK;
 }
 
+// U of the packed layer sum from T: layer 1's (T_1 = W_1^T) when the sweep
+// writes the others', or all layers'.
+int run_pack_u(Ctx* c, Net* net, int B, bool all) {
+  PackUArgs a;
+  memset(&a, 0, sizeof(a));
+  a.T1 = net->ly[0].WT;
+  a.ld1 = net->ly[0].doutp;
+  a.Tc = net->TC;
+  a.ld = net->Ktot;
+  a.B = B;
+  a.layers = all ? net->Lt : 1;
+  for (int l = 1; l <= a.layers; ++l) {
+    a.s[l - 1] = net->ly[l - 1].s;
+    a.koff[l - 1] = net->koff[l];
+    a.dp[l - 1] = net->ly[l - 1].doutp;
+  }
+  a.u = packed_u(net);
+  NNC_LAUNCH(c, NNC_KC_OTHER, launch_pack_u(net->ct, a, c->stream));
+  return NNC_OK;
+}
+
 // First tangent seed: P_1 = D_1 W_1 (or G_1 = diag(s_1) W_1 when Lt = 1).
 int run_seed(Ctx* c, Net* net, int B, bool defer_s = false) {
   const int n = net->n;
   Layer& l1 = net->ly[0];
   if (net->Lt == 0) return NNC_OK;
+  if (packed_h(net)) {
+    NNC_LAUNCH(c, NNC_KC_OTHER, launch_seed_layersum(net->ct, l1.WT, n, l1.doutp, l1.d1, l1.s, B, nullptr, nullptr,
+                                                      net->Ktot, net->P[1], true, c->stream));
+    return defer_s ? NNC_OK : run_pack_u(c, net, B, false);
+  }
   if (net->hess_method == NNC_HESS_LAYERSUM) {
     NNC_LAUNCH(c, NNC_KC_OTHER, launch_seed_layersum(net->ct, l1.WT, n, l1.doutp, l1.d1, l1.s, B, net->TC,
                                                       defer_s ? nullptr : net->SC, net->Ktot,
@@ -932,6 +1004,7 @@ bool sweep_overlap_ok(const Ctx* c, const Net* net, int B, bool jac) {
 // S_l = diag(s_l) T_l of every layer, once the sweep (T) and the adjoint (s)
 // are both done.
 int run_scale(Ctx* c, Net* net, int B) {
+  if (packed_h(net)) return run_pack_u(c, net, B, true);
   LsScaleArgs a;
   memset(&a, 0, sizeof(a));
   a.Tc = net->TC;

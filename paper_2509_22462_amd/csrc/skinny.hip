@@ -806,6 +806,10 @@ __global__ void skinny_slice_reduce_kernel(SkinnyArgs a, SkinnyArgs d, int kslic
 
 // Row blocks for `rows` rows (at most kStreamRows).
 constexpr int kStreamRows = 64;
+// Row-major and FP64 streams are staged (skinny_rows_lds_kernel,
+// skinny_rows64_kernel) where that still gives this many workgroups; a smaller
+// layer has more of skinny_mfma_kernel's, one per 16 weight rows.
+constexpr int kStageGroups = 96;
 
 // Launch rules for the 5..64-row streams.  FP32 rows go to
 // skinny_rows_lds_kernel (rows staged in LDS), except one row block on a
@@ -827,18 +831,21 @@ static hipError_t skinny_mfma_launch_p(SkinnyArgs c, SkinnyArgs d, hipStream_t s
       while (ksw > 1 && (!c.part || (long long)ksw * c.rows * c.N > c.part_elems)) --ksw;
       const int cper = (nchunks + ksw - 1) / ksw;
       ksw = (nchunks + cper - 1) / cper;
-      hipLaunchKernelGGL((skinny_rows64_kernel<TW, RB, PACKED>), dim3(groups, ksw), dim3(512), 0, s, c);
-      if (ksw > 1) {
-        const long long work = (long long)c.rows * c.N;
-        hipLaunchKernelGGL(skinny_slice_reduce_kernel<A>, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, c, d,
-                           ksw, c.rows, 0);
+      if (groups * ksw >= kStageGroups) {
+        hipLaunchKernelGGL((skinny_rows64_kernel<TW, RB, PACKED>), dim3(groups, ksw), dim3(512), 0, s, c);
+        if (ksw > 1) {
+          const long long work = (long long)c.rows * c.N;
+          hipLaunchKernelGGL(skinny_slice_reduce_kernel<A>, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, c,
+                             d, ksw, c.rows, 0);
+        }
+        return hipGetLastError();
       }
-      return hipGetLastError();
     }
   }
   if constexpr (JAC && sizeof(A) == 4 && std::is_same<TX, float>::value && (PACKED || !ADJ)) {
    const int groups = (blocks + 7) / 8;
-   if (RB >= 2 || groups >= 16) {
+   const int most = groups * std::max(1, std::min(256 / groups, c.K / (2 * 128)));  // workgroups with K slices
+   if ((RB >= 2 || groups >= 16) && (PACKED || most >= kStageGroups)) {
     // FP32 Jacobian rows: rows staged in LDS per workgroup of 8 weight
     // blocks (skinny_rows_lds_kernel), K sliced so that the launch is about
     // one workgroup per CU (256; more measured slower, as did a last partial
@@ -1233,7 +1240,7 @@ __global__ void __launch_bounds__(256) seed_layersum_kernel(const T* W1T, int n,
   const long long o = (long long)r * ldts + k0;
 #pragma unroll
   for (int v = 0; v < LANE / V; ++v) {
-    *(uint4*)(Tc + o + v * V) = w.u[v];
+    if (Tc) *(uint4*)(Tc + o + v * V) = w.u[v];
     if (Sc) *(uint4*)(Sc + o + v * V) = sv.u[v];
   }
   if (!P) return;
@@ -1391,19 +1398,22 @@ hipError_t launch_adj_seed(const double* lam, const double* zL, int act, int B, 
   return hipGetLastError();
 }
 
-// SoftMax of the FP64 output pre-activations, one thread per point: the
-// largest entry is subtracted before exponentiating (it cancels).
-__global__ void softmax_out_kernel(const double* zL, int B, int m, int mp, const double* y, double* g,
-                                   double* p) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
+// SoftMax of the FP64 output pre-activations, one wave per point: the
+// largest entry is subtracted before exponentiating (it cancels).  (One thread
+// per point took 9.7 us for 10 outputs: three passes of dependent exponentials.)
+__global__ void __launch_bounds__(64) softmax_out_kernel(const double* zL, int m, int mp, const double* y, double* g,
+                                                         double* p) {
+  const int b = blockIdx.x;
+  const int lane = threadIdx.x;
   const double* z = zL + (long long)b * mp;
-  double mx = z[0];
-  for (int i = 1; i < m; ++i) mx = fmax(mx, z[i]);
+  double mx = z[min(lane, m - 1)];
+  for (int i = lane + 64; i < m; i += 64) mx = fmax(mx, z[i]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
   double sum = 0.0;
-  for (int i = 0; i < m; ++i) sum += exp(z[i] - mx);
-  const double r = 1.0 / sum;
-  for (int i = 0; i < mp; ++i) {
+  for (int i = lane; i < m; i += 64) sum += exp(z[i] - mx);
+  const double r = 1.0 / wave_sum(sum);
+  for (int i = lane; i < mp; i += 64) {
     const double pi = i < m ? exp(z[i] - mx) * r : 0.0;
     p[(long long)b * mp + i] = pi;
     if (g && i < m) g[(long long)b * m + i] = y ? y[(long long)b * m + i] - pi : pi;
@@ -1413,7 +1423,7 @@ __global__ void softmax_out_kernel(const double* zL, int B, int m, int mp, const
 hipError_t launch_softmax_out(const double* zL, int B, int m, int mp, const double* y, double* g, double* p,
                               hipStream_t s) {
   if (B == 0) return hipSuccess;
-  hipLaunchKernelGGL(softmax_out_kernel, dim3((B + 63) / 64), dim3(64), 0, s, zL, B, m, mp, y, g, p);
+  hipLaunchKernelGGL(softmax_out_kernel, dim3(B), dim3(64), 0, s, zL, m, mp, y, g, p);
   return hipGetLastError();
 }
 
@@ -1571,11 +1581,123 @@ __global__ void finalize_h_kernel(const double* part, int splits, long long sstr
   }
 }
 
-hipError_t launch_finalize_h(const double* part, int splits, long long split_stride, int B, int n,
+// The same where only the tiles on or below the block diagonal (edge symtile, a
+// multiple of 32) hold partials: one workgroup per 32 x 32 block of the lower
+// triangle sums it once and writes it and its mirror image (the kernel above
+// read every partial twice: 7 points of 784 inputs, 8 slices, 39 -> 16 us).  Blocks within one diagonal tile have
+// both triangles and are symmetrised.
+__global__ void __launch_bounds__(256) finalize_sym_kernel(const double* part, int splits, long long sstride, int n,
+                                                           double obj, const double* q, double* H, int symtile,
+                                                           const double* u, const double* vv) {
+  __shared__ double ta[32][33];
+  __shared__ double tb[32][33];
+  const int t = blockIdx.x;
+  int bi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (bi > 0 && bi * (bi + 1) / 2 > t) --bi;
+  while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+  const int I = bi * 32, J = (t - bi * (bi + 1) / 2) * 32;
+  const long long base = (long long)blockIdx.y * n * n;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const bool both = I / symtile == J / symtile;
+  auto sums = [&](int r0, int c0, double (&out)[4]) {
+    const int c = c0 + tx;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = 0.0;
+    const int sp4 = splits & ~3;  // four loaded back to back, all added in split order
+    for (int sp0 = 0; sp0 < sp4; sp0 += 4) {
+      double v[4][4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = r0 + ty + 8 * e;
+          v[k][e] = r < n && c < n ? part[(sp0 + k) * sstride + base + (long long)r * n + c] : 0.0;
+        }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] += v[k][e];
+    }
+    for (int sp = sp4; sp < splits; ++sp)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = r0 + ty + 8 * e;
+        out[e] += r < n && c < n ? part[sp * sstride + base + (long long)r * n + c] : 0.0;
+      }
+  };
+  double a[4], m[4];
+  sums(I, J, a);
+  if (both) {
+    sums(J, I, m);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tb[ty + 8 * e][tx] = m[e];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int y = ty + 8 * e;
+    const int r = I + y, c = J + tx;
+    double v = both ? 0.5 * (a[e] + tb[tx][y]) : a[e];
+    if (r < n && c < n) {
+      if (r == c && q) v += obj * q[r];
+      if (u) {
+        // rounded product by product, the same for (r, c) and its mirror image
+#pragma clang fp contract(off)
+        const long long rb = (long long)blockIdx.y * n;
+        const double t1 = u[rb + r] * vv[rb + c];
+        const double t2 = vv[rb + r] * u[rb + c];
+        v -= r <= c ? t1 + t2 : t2 + t1;
+      }
+      H[base + (long long)r * n + c] = v;
+    }
+    ta[y][tx] = v;
+  }
+  if (I == J) return;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int y = ty + 8 * e;
+    const int r = J + y, c = I + tx;
+    if (r < n && c < n) H[base + (long long)r * n + c] = ta[tx][y];
+  }
+}
+
+// part[8 c] = sum of part[8 c .. 8 c + 7] in split order, one thread per entry
+// and group c: a product of one or two tiles has a hundred slices and more, which
+// the few workgroups of the kernel above would add 8 at a time (117 inputs, 185
+// slices: 5.8 us and then 14.5 for the rest).
+__global__ void __launch_bounds__(256) finalize_reduce8_kernel(double* part, int splits, long long sstride) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= sstride) return;
+  const int s0 = blockIdx.y * 8;
+  double* p = part + (long long)s0 * sstride + i;
+  double v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = s0 + k < splits ? p[k * sstride] : 0.0;
+  double t = v[0];
+#pragma unroll
+  for (int k = 1; k < 8; ++k) t += v[k];
+  *p = t;
+}
+
+hipError_t launch_finalize_h(double* part, int splits, long long split_stride, int B, int n,
                              double obj, const double* q, double* H, int symtile, const double* u,
                              const double* v, hipStream_t s) {
   if (B == 0 || n == 0) return hipSuccess;
-  dim3 grid((n + 31) / 32, (n + 31) / 32, B);
+  if (splits > 16) {
+    const int groups = (splits + 7) / 8;
+    hipLaunchKernelGGL(finalize_reduce8_kernel, dim3((unsigned)((split_stride + 255) / 256), groups), dim3(256), 0, s,
+                       part, splits, split_stride);
+    splits = groups;
+    split_stride *= 8;
+  }
+  const int nb = (n + 31) / 32;
+  if (symtile > 0 && symtile % 32 == 0 && splits > 0 && B <= 65535) {
+    hipLaunchKernelGGL(finalize_sym_kernel, dim3(nb * (nb + 1) / 2, B), dim3(256), 0, s, (const double*)part, splits,
+                       split_stride, n, obj, q, H, symtile, u, v);
+    return hipGetLastError();
+  }
+  dim3 grid(nb, nb, B);
   hipLaunchKernelGGL(finalize_h_kernel, grid, dim3(32, 8), 0, s, part, splits, split_stride, n,
                      obj, q, H, symtile, u, v);
   return hipGetLastError();
