@@ -253,6 +253,20 @@ hipError_t launch_seed_tangent(DType t, const void* W1T, int n, int dp1, const v
 // (SoftMax output: p [B][mp] holds softmax(z_L); zbar = s = p * (lambda - p^T lambda))
 hipError_t launch_adj_seed(const double* lam, const double* zL, int act, int B, int m, int mp,
                            double* zbar, double* sv, const double* p, hipStream_t s);
+// One point's reverse seeds (m <= kRevSeedRows outputs): zbar_L, s_L, the
+// adjoint's zbar_{L-1}, s_{L-1} and, unless R is null, the Jacobian seed rows
+// [m][Kp] for the layer before the output.
+constexpr int kRevSeedRows = 64;
+struct RevSeedArgs {
+  const double *lam, *zL, *dL;  // dL: sigma_L'(z_L), SoftMax: p
+  const double* WL;             // [m][Kp]
+  const double* zp;             // z_{L-1}
+  const void* d1p;              // sigma_{L-1}'
+  int act, actp, m, mp, K, Kp;
+  double *zbarL, *sL, *zbarp, *sp;
+  void* R;
+};
+hipError_t launch_reverse_seed(DType at, const RevSeedArgs& a, hipStream_t s);
 // SoftMax output layer: p = softmax(z_L) per point (FP64, into p [B][mp],
 // padding 0) and g = y - p, or p when y is NULL (g may be NULL).
 hipError_t launch_softmax_out(const double* zL, int B, int m, int mp, const double* y, double* g, double* p,

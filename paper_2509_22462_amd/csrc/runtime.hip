@@ -9,8 +9,9 @@
 //     the output layer also in FP64 (W_L and W_L^T) for the FP64 residual and
 //     the FP64 lambda-weighted adjoint;
 //   * per point and layer: z_l (FP64), a_l, sigma'_l, zbar_l and s_l;
-//   * layer-sum networks in FP32 and BF16: W_l (l >= 2) once more as packed
-//     MFMA operands (gemm_pk.hip), three BF16 parts per FP32 element;
+//   * layer-sum networks: W_l (l >= 2) once more as packed MFMA operands
+//     (gemm_pk.hip), three BF16 parts per FP32 element; their P_l are packed
+//     too and, but for BF16, the final product's U = sqrt|s| T;
 //   * tangents stored "transposed", one row per tangent column (b, j):
 //     [B*n][d_l'] so that rows are feature-contiguous; G_l of the reverse
 //     sweep overwrites P_l (consumed by the forward sweep) in place;
@@ -179,6 +180,7 @@ int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out);
 // Most that the K-split partials of one packed product may take: the choice
 // of the split, and so the rounding of a result, must not depend on what the
 // network has allocated for other shapes.
+constexpr long long kFillTiles = 128;  // fill_ksplit
 constexpr size_t kPkPartBytes = (size_t)64 << 20;
 
 // Workspace for the K splits the tuned table (or a forced split) asks for at
@@ -197,6 +199,9 @@ int size_part(Ctx* c, Net* net) {
       if (ks > 1) need = std::max(need, (size_t)ks * p.g.M * p.g.N * part_size(net));
     }
   }
+  // Jacobian GEMMs of few tiles (fill_ksplit): 8 slices of fewer than 128 tiles
+  if ((long long)net->maxB * net->m >= 64 && net->ct == net->at)
+    need = std::max<size_t>(need, (size_t)8 * kFillTiles * 64 * 64 * part_size(net));
   if (net->pk_bufs)
     for (int B = 1; B <= net->maxB; ++B)
       for (int l = 1; l < net->Lt; ++l) {
@@ -371,6 +376,17 @@ void update_pk(Ctx* c, Net* net, bool allow) {
             c->forced_ksplit[net->ct] < 1;
 }
 
+// K slices of a product without a row in the tuned table: a few 64 x 64 tiles
+// run their K tiles one after the other on a few CUs, so below 128 tiles K is
+// split until there are about 256 workgroups, every slice keeping 128 elements
+// or more.  (70 Jacobian rows of the 784-1000-500-250-10 classifier, FP32: three
+// products 56 -> 33 us with their reductions.)
+int fill_ksplit(const GemmArgs& g) {
+  const long long tiles = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  if (tiles >= kFillTiles) return 1;
+  return (int)std::max<long long>(1, std::min<long long>({8, 256 / tiles, g.K / 128}));
+}
+
 int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kind = NNC_KC_GEMM) {
   int cfg = -1, ks = 1;
   (void)slot;
@@ -385,7 +401,10 @@ int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kin
   }
   if (!acc64 && c->forced_cfg[net->ct] >= 0) cfg = c->forced_cfg[net->ct];
   if (!acc64 && c->forced_ksplit[net->ct] >= 1) ks = c->forced_ksplit[net->ct];
-  if (cfg < 0 || !gemm_cfg_supports(net->ct, cfg, acc64)) cfg = pick_cfg(net, g.M, g.N, acc64);
+  if (cfg < 0 || !gemm_cfg_supports(net->ct, cfg, acc64)) {
+    cfg = pick_cfg(net, g.M, g.N, acc64);
+    if (ks == 1 && c->forced_ksplit[net->ct] < 1) ks = fill_ksplit(g);
+  }
   NNC_LAUNCH(c, kind, launch_gemm_ks(net, g, acc64, splits, cfg, ks, c->stream));
   return NNC_OK;
 }
@@ -592,6 +611,37 @@ size_t carve_fwd_bufs(const Net* net, int B, char* base, FwdBufs* fb) {
   return off;
 }
 
+// One point's seeds of the reverse passes (reverse_seed_ok), with R the
+// Jacobian's too.
+bool reverse_seed_ok(const Net* net, int B) {
+  return reverse_stream_ok(net, B) && net->L >= 2 && net->m <= kRevSeedRows;
+}
+
+int run_reverse_seed(Ctx* c, Net* net, const double* lam, void* R) {
+  Layer& lo = net->ly[net->L - 1];
+  Layer& lp = net->ly[net->L - 2];
+  RevSeedArgs a;
+  a.lam = lam;
+  a.zL = lo.z;
+  a.dL = (const double*)lo.d1;
+  a.WL = net->WL64;
+  a.zp = lp.z;
+  a.d1p = lp.d1;
+  a.act = lo.act;
+  a.actp = lp.act;
+  a.m = net->m;
+  a.mp = lo.doutp;
+  a.K = lp.dout;
+  a.Kp = lo.dinp;
+  a.zbarL = lo.zbar;
+  a.sL = lo.s;
+  a.zbarp = lp.zbar;
+  a.sp = lp.s;
+  a.R = R;
+  NNC_LAUNCH(c, NNC_KC_OTHER, launch_reverse_seed(net->at, a, c->stream));
+  return NNC_OK;
+}
+
 // a4 + a5 at one point (reverse_fusable): each hidden layer's W^T is streamed
 // once for the Jacobian rows and the FP64 adjoint row together.  Launch for
 // launch the same arguments, kernels and rounding as run_jacobian followed
@@ -600,16 +650,7 @@ int run_jacobian_adjoint(Ctx* c, Net* net, double* J, const double* lam) {
   const int L = net->L, m = net->m, n = net->n;
   Layer& lo = net->ly[L - 1];
   Layer& lp = net->ly[L - 2];
-  NNC_LAUNCH(c, NNC_KC_OTHER, launch_jac_seed(net->at, net->WL64, m, lp.dout, lo.dinp, lo.d1, lo.doutp, lp.d1,
-                             lp.doutp, 1, net->R0, false, net->softmax_out, c->stream));
-  NNC_LAUNCH(c, NNC_KC_OTHER, launch_adj_seed(lam, lo.z, lo.act, 1, m, lo.doutp, lo.zbar, lo.s, (const double*)lo.d1,
-                                              c->stream));
-  {
-    SkinnyArgs a = adjoint_args(net, L, 1);
-    a.W = net->WLT64;  // the output layer's adjoint step stays in FP64 weights
-    a.Wp = nullptr;
-    NNC_LAUNCH(c, NNC_KC_SKINNY, launch_skinny(DT_F64, DT_F64, DT_F64, a, c->stream));
-  }
+  NNC_TRY(run_reverse_seed(c, net, lam, net->R0));
   void* cur = net->R0;
   void* nxt = net->R1;
   for (int l = L - 1; l >= 2; --l) {
@@ -705,11 +746,15 @@ int run_jacobian(Ctx* c, Net* net, int B, double* J) {
 int run_adjoint(Ctx* c, Net* net, int B, const double* lam) {
   const int L = net->L;
   Layer& lo = net->ly[L - 1];
-  NNC_LAUNCH(c, NNC_KC_OTHER, launch_adj_seed(lam, lo.z, lo.act, B, net->m, lo.doutp, lo.zbar, lo.s,
-                                              (const double*)lo.d1, c->stream));
+  const bool seeded = reverse_seed_ok(net, B);  // through the output layer already
+  if (seeded)
+    NNC_TRY(run_reverse_seed(c, net, lam, nullptr));
+  else
+    NNC_LAUNCH(c, NNC_KC_OTHER, launch_adj_seed(lam, lo.z, lo.act, B, net->m, lo.doutp, lo.zbar, lo.s,
+                                                (const double*)lo.d1, c->stream));
   // many points: FP64 MFMA GEMMs against FP64 copies of W^T
   const bool gemm_adj = B >= kGemmRows;  // (copies exist whenever max_points >= kGemmRows)
-  for (int l = L; l >= 2; --l) {
+  for (int l = seeded ? L - 1 : L; l >= 2; --l) {
     Layer& ly = net->ly[l - 1];
     Layer& lp = net->ly[l - 2];
     const bool out_layer = (l == L);

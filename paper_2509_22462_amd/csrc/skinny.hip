@@ -1398,6 +1398,85 @@ hipError_t launch_adj_seed(const double* lam, const double* zL, int act, int B, 
   return hipGetLastError();
 }
 
+// One point's reverse seeds in one launch: zbar_L and s_L from lambda (the
+// first block), the adjoint through the output layer (zbar_{L-1}, s_{L-1}: FP64
+// W_L, m of it per column, added in order) and, with R, the Jacobian seed rows
+// as jac_seed_kernel forms them.  Three launches' work for a few kilobytes:
+// what they cost is their launching.
+template <typename OT>
+__global__ void __launch_bounds__(kRevSeedRows) reverse_seed_kernel(RevSeedArgs a) {
+  __shared__ double zb[kRevSeedRows], p[kRevSeedRows];
+  const int tid = threadIdx.x;
+  const bool softmax = a.act == ACT_SOFTMAX;
+  if (tid < a.m) p[tid] = a.dL[tid];
+  __syncthreads();
+  if (tid < a.m) {
+    const double l = a.lam[tid];
+    double z, s2;
+    if (softmax) {
+      double c = 0.0;
+      for (int j = 0; j < a.m; ++j) c += p[j] * a.lam[j];
+      z = p[tid] * (l - c);
+      s2 = z;
+    } else {
+      const ActVal av = act_eval(a.act, a.zL[tid]);
+      z = l * av.d1;
+      s2 = l * av.d2;
+    }
+    zb[tid] = z;
+    if (blockIdx.x == 0) {
+      a.zbarL[tid] = z;
+      a.sL[tid] = s2;
+    }
+  }
+  if (blockIdx.x == 0)
+    for (int i = a.m + tid; i < a.mp; i += kRevSeedRows) {
+      a.zbarL[i] = 0.0;
+      a.sL[i] = 0.0;
+    }
+  __syncthreads();
+  const int k = blockIdx.x * kRevSeedRows + tid;
+  if (k >= a.Kp) return;
+  const bool in = k < a.K;
+  double abar = 0.0, wbar = 0.0;
+#pragma unroll 8
+  for (int i = 0; i < a.m; ++i) {
+    const double w = a.WL[(long long)i * a.Kp + k];
+    abar = fma(w, zb[i], abar);
+    if (softmax) wbar += p[i] * w;
+  }
+  double z = 0.0, s2 = 0.0;
+  if (in) {
+    const ActVal av = act_eval(a.actp, a.zp[k]);
+    z = abar * av.d1;
+    s2 = abar * av.d2;
+  }
+  a.zbarp[k] = z;
+  a.sp[k] = s2;
+  if (!a.R) return;
+  const double d = in ? (double)((const OT*)a.d1p)[k] : 0.0;
+#pragma unroll 8
+  for (int i = 0; i < a.m; ++i) {
+    double v = 0.0;
+    if (in) {
+      const double w = a.WL[(long long)i * a.Kp + k];
+      v = softmax ? p[i] * (w - wbar) : p[i] * w;
+      v *= d;
+    }
+    ((OT*)a.R)[(long long)i * a.Kp + k] = (OT)v;
+  }
+}
+
+hipError_t launch_reverse_seed(DType at, const RevSeedArgs& a, hipStream_t s) {
+  if (a.m < 1 || a.m > kRevSeedRows) return hipErrorInvalidValue;
+  const dim3 grid((a.Kp + kRevSeedRows - 1) / kRevSeedRows);
+  if (at == DT_F64)
+    hipLaunchKernelGGL(reverse_seed_kernel<double>, grid, dim3(kRevSeedRows), 0, s, a);
+  else
+    hipLaunchKernelGGL(reverse_seed_kernel<float>, grid, dim3(kRevSeedRows), 0, s, a);
+  return hipGetLastError();
+}
+
 // SoftMax of the FP64 output pre-activations, one wave per point: the
 // largest entry is subtracted before exponentiating (it cancels).  (One thread
 // per point took 9.7 us for 10 outputs: three passes of dependent exponentials.)
