@@ -24,9 +24,12 @@ template <> struct PkElem<double> {
   static constexpr int KB = 8;
 };
 
-// The parts of four consecutive elements.
+// The parts of four consecutive elements.  (Never contracted with the product
+// that an element comes from: its parts are then those of the rounded element
+// in every kernel, and a result does not depend on which of them wrote it.)
 template <int NP>
 __device__ __forceinline__ void cut_parts(const float (&v)[4], uint2 (&o)[NP]) {
+#pragma clang fp contract(off)
   if constexpr (NP == 1) {
     bf16x4 t;
 #pragma unroll
