@@ -623,7 +623,9 @@ gemm_pk_sym_grouped_kernel(const GemmArgs* __restrict__ groups, const int* __res
 #undef SYM_STAGES
 
 // U from row-major T: a wave takes 16 rows of a point and 32 columns of a
-// layer, lane l row l % 16 and columns 4 (l / 16) .. + 3 of each half.
+// layer, lane l row l % 16 and columns 4 (l / 16) .. + 3 of each half.  With P
+// also the first product's operand, of the elements it holds already: a launch
+// and a read of W_1 less than seeding it apart.
 template <typename T>
 __global__ void __launch_bounds__(256) pack_u_kernel(PackUArgs a) {
   using A = typename PkAcc<T>::A;
@@ -647,23 +649,31 @@ __global__ void __launch_bounds__(256) pack_u_kernel(PackUArgs a) {
     if (c >= dp) return;
     const A v[4] = {(A)t[c], (A)t[c + 1], (A)t[c + 2], (A)t[c + 3]};
     put_u<T>(a.u, b, i, a.koff[l] + c, a.s[l] + (long long)b * dp + c, v);
+    if (a.P && l == 0) {
+      const A* d = (const A*)a.d1 + (long long)b * dp + c;
+      const A x[4] = {v[0] * d[0], v[1] * d[1], v[2] * d[2], v[3] * d[3]};
+      put_packed<T>(a.P, b * a.u.n + i, c, dp / PkElem<T>::KB, x);
+    }
   }
 }
 
 // The tilings.  us1 / us2: time 32 elements of K take a CU for one tile,
 // with one workgroup on it and (us2) with several in turn or at once, measured
-// at 25088 x 8192 x 8192 and 784 x 8192 x 8192 (us2, us1 of the large tiles)
-// and 117 x 4032 x 4032 (us1 of the small ones).
+// at 25088 x 8192 x 8192 and 784 x 8192 x 8192 (us2, us1 of the large tiles),
+// 117 x 4032 x 4032 (us1 of the small ones) and 5488 x 512 x 1024 (the last of
+// FP32: 172 tiles in 38 us, where 64 x 128 and 64 x 64 take 47 and 49).
 struct PkCfg {
   int bm, bn, ks, occ;
   double us1, us2;
 };
-constexpr int kPkCfgs = 4;
-constexpr PkCfg kPkF32[kPkCfgs] = {
+constexpr int kPkCfgs = 4;   // BF16, FP64
+constexpr int kPkCfgs32 = 5;  // FP32
+constexpr PkCfg kPkF32[kPkCfgs32] = {
     {128, 256, 32, 1, 2.00, 2.20},  // 8 waves of 64 x 64
     {112, 256, 32, 1, 1.87, 2.04},  // 8 waves of 32 x 112: whole tiles of 784 rows
     {64, 128, 32, 2, 1.00, 0.70},   // 4 waves of 64 x 32
     {64, 64, 32, 2, 0.75, 0.45},    // 4 waves of 32 x 32
+    {128, 128, 32, 1, 1.20, 1.30},  // 8 waves of 32 x 64: about one round of tiles
 };
 constexpr PkCfg kPkBf16[kPkCfgs] = {
     {256, 256, 32, 1, 0.80, 0.97},  // 8 waves of 64 x 128
@@ -678,6 +688,7 @@ constexpr PkCfg kPkF64[kPkCfgs] = {
     {64, 64, 16, 3, 1.30, 0.95},    // 4 waves of 32 x 32
 };
 
+inline int pk_cfgs(DType t) { return t == DT_F32 ? kPkCfgs32 : kPkCfgs; }
 inline const PkCfg& pk_cfg(DType t, int cfg) {
   return t == DT_F32 ? kPkF32[cfg] : t == DT_BF16 ? kPkBf16[cfg] : kPkF64[cfg];
 }
@@ -691,6 +702,7 @@ inline const PkCfg& pk_cfg(DType t, int cfg) {
         case 1: CALL(float, 8, 1, 2, 7, 1, 2);      \
         case 2: CALL(float, 2, 2, 4, 2, 1, 2);      \
         case 3: CALL(float, 2, 2, 2, 2, 1, 3);      \
+        case 4: CALL(float, 4, 2, 2, 4, 1, 3);      \
         default: return hipErrorInvalidValue;       \
       }                                             \
     } else if constexpr (sizeof(T) == 2) {          \
@@ -740,12 +752,13 @@ inline int pk_kper(const PkCfg& c, int K, int ks) {
 
 // The tiling and K split of the least estimated time: the rounds of tiles a CU
 // takes, each K / ksplit long, and with a split the partials written and read
-// at 4.5 TB/s by one more launch.
+// at 4.5 TB/s by one more launch (7 us: at 4 a 302 x 256 x 256 product was split
+// for no gain and a call of 28 such launches took 236 instead of 219 us).
 PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes) {
   PkChoice best{0, 1};
   double best_us = 1e30;
   const double psz = t == DT_F64 ? 8.0 : 4.0;  // bytes of a partial
-  for (int i = 0; i < kPkCfgs; ++i) {
+  for (int i = 0; i < pk_cfgs(t); ++i) {
     const PkCfg& c = pk_cfg(t, i);
     const long long tiles = (long long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
     for (int ks = 1; ks <= 8; ++ks) {
@@ -754,7 +767,7 @@ PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes) {
       if (ks > 1 && ks * psz * M * N > (double)part_bytes) break;
       const long long rounds = (tiles * ks + 255) / 256;
       double us = kper / 32.0 * (rounds == 1 ? c.us1 : rounds * c.us2) + 4.0;
-      if (ks > 1) us += 4.0 + 2.0 * psz * ks * M * N / 4.5e6;
+      if (ks > 1) us += 7.0 + 2.0 * psz * ks * M * N / 4.5e6;
       if (us < best_us) {
         best_us = us;
         best = PkChoice{i, ks};
@@ -796,7 +809,7 @@ int pk_grouped_occupancy(DType t, int cfg) { return pk_cfg(t, cfg).occ; }
 hipError_t launch_gemm_pk(DType t, PkChoice ch, GemmArgs g, void* part, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (t != DT_BF16 && g.out2 && (!g.u.U || !g.u.sgn || g.u.n <= 0)) return hipErrorInvalidValue;
-  if (ch.cfg < 0 || ch.cfg >= kPkCfgs || g.K <= 0 || g.K % 64 != 0 || g.N % 16 != 0 ||
+  if (ch.cfg < 0 || ch.cfg >= pk_cfgs(t) || g.K <= 0 || g.K % 64 != 0 || g.N % 16 != 0 ||
       (ch.ksplit > 1 && !part))
     return hipErrorInvalidValue;
   pk_set_tiles(t, ch.cfg, g);
@@ -881,7 +894,7 @@ hipError_t launch_gemm_pk_sym_grouped(DType t, int edge, const GemmArgs* groups,
 
 // Time of a round of tiles (32 elements of K: 1.1 / 3.6 us at edge 128 in
 // FP32 / FP64, 0.37 of it per tile at edge 64) against the partials
-// written and read back.  A slice keeps 512 elements or more.
+// written and read back.  A slice keeps 128 elements or more.
 int pk_sym_splits(DType t, int n, int B, int K) {
   const int edge = pk_sym_edge(n);
   const double tt = (n + edge - 1) / edge;
@@ -889,7 +902,7 @@ int pk_sym_splits(DType t, int n, int B, int K) {
   const double us = (t == DT_F32 ? 1.1 : 3.6) * (edge == 128 ? 1.0 : 0.37);
   int best = 1;
   double best_us = 1e30;
-  for (int sp = 1; sp <= 256 && (sp == 1 || K / sp >= 512); ++sp) {
+  for (int sp = 1; sp <= 256 && (sp == 1 || K / sp >= 128); ++sp) {
     const double rounds = (double)(((long long)(tiles * sp) + 255) / 256);
     const double c = rounds * (K / 32.0 / sp) * us + sp * (0.1 + (double)B * n * n * 16.0 / 4.5e6) + (sp > 16 ? 5.0 : 0.0);
     if (c < best_us) {

@@ -170,6 +170,8 @@ struct PackUArgs {
   const double* s[kMaxScaleLayers];  // [B][dp]
   int koff[kMaxScaleLayers], dp[kMaxScaleLayers];
   PackedU u;
+  const void* d1;  // with P: P_1 = D_1 T_1 as the packed operand [B n][dp[0]]
+  void* P;
 };
 hipError_t launch_pack_u(DType t, const PackUArgs& a, hipStream_t s);
 size_t pk_u_bytes(DType t, int n, int B, int K);

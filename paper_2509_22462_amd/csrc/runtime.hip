@@ -932,8 +932,9 @@ int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out) {
 }
 
 // U of the packed layer sum from T: layer 1's (T_1 = W_1^T) when the sweep
-// writes the others', or all layers'.
-int run_pack_u(Ctx* c, Net* net, int B, bool all) {
+// writes the others', or all layers'.  With P the first product's operand
+// P_1 = D_1 W_1^T as well, of the same elements.
+int run_pack_u(Ctx* c, Net* net, int B, bool all, void* P = nullptr) {
   PackUArgs a;
   memset(&a, 0, sizeof(a));
   a.T1 = net->ly[0].WT;
@@ -948,6 +949,8 @@ int run_pack_u(Ctx* c, Net* net, int B, bool all) {
     a.dp[l - 1] = net->ly[l - 1].doutp;
   }
   a.u = packed_u(net);
+  a.d1 = net->ly[0].d1;
+  a.P = P;
   NNC_LAUNCH(c, NNC_KC_OTHER, launch_pack_u(net->ct, a, c->stream));
   return NNC_OK;
 }
@@ -958,9 +961,10 @@ int run_seed(Ctx* c, Net* net, int B, bool defer_s = false) {
   Layer& l1 = net->ly[0];
   if (net->Lt == 0) return NNC_OK;
   if (packed_h(net)) {
+    if (!defer_s) return run_pack_u(c, net, B, false, net->P[1]);
     NNC_LAUNCH(c, NNC_KC_OTHER, launch_seed_layersum(net->ct, l1.WT, n, l1.doutp, l1.d1, l1.s, B, nullptr, nullptr,
                                                       net->Ktot, net->P[1], true, c->stream));
-    return defer_s ? NNC_OK : run_pack_u(c, net, B, false);
+    return NNC_OK;
   }
   if (net->hess_method == NNC_HESS_LAYERSUM) {
     NNC_LAUNCH(c, NNC_KC_OTHER, launch_seed_layersum(net->ct, l1.WT, n, l1.doutp, l1.d1, l1.s, B, net->TC,
