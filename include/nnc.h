@@ -94,11 +94,13 @@ const char* nnc_last_error(nnc_ctx ctx);
  *               caller keeps ownership and may free them after the call.
  *   prec        enum nnc_prec of the bulk GEMMs.
  *   max_points  largest point count B any eval call on this net will use;
- *               the tangent workspace (about B*n*sum(d_l)*2 elements) is
- *               allocated here.  From 64 points on, calls run the primal
- *               pass and the FP64 adjoint as MFMA GEMMs, so a net created
- *               with max_points >= 64 also holds FP64 copies of its hidden
- *               layers' transposed weights (none extra for NNC_FP64).
+ *               the tangent workspace (about B*n*sum(d_l)*2 elements; FP32
+ *               layer-sum networks hold one and a half times that, and their
+ *               hidden weights once more at 6 bytes each) is allocated here.
+ *               From 64 points on, calls run the primal pass and the FP64
+ *               adjoint as MFMA GEMMs, so a net created with max_points >= 64
+ *               also holds FP64 copies of its hidden layers' transposed weights
+ *               (none extra for NNC_FP64).
  *   *net        receives a handle >= 0.
  * Errors: NNC_E_ARG, NNC_E_SHAPE, NNC_E_NOMEM, NNC_E_HIP. */
 int nnc_net_create(nnc_ctx ctx, int L, const int* dims, const int* acts,
@@ -193,7 +195,8 @@ int nnc_eval(nnc_ctx ctx, int net, int B, const double* x, const double* y, doub
  * right-looking, 64-column panels) and two triangular solves.
  *
  * nnc_kkt_create: a solver for n x n systems (1 <= n <= 2048), at most max_B
- *   per call; allocates the factor workspace (max_B * n * n doubles) now.
+ *   per call; allocates the factor workspace now: about max_B * n' * (n' + 80)
+ *   doubles, n' = n rounded up to 64.
  * nnc_kkt_solve: all pointers DEVICE, FP64 unless noted, caller-owned:
  *   H [B][n][n] (read only; e.g. the output of nnc_eval_hess_lag), d [B][n]
  *   or NULL, a [B][n] and s [B] (both or neither), delta [B] or NULL,
@@ -240,10 +243,12 @@ int nnc_eval_batch(nnc_ctx ctx, int njobs, const nnc_job* jobs);
 /* nnc_autotune: time every candidate GEMM tiling on each tangent-sweep GEMM
  * shape of this net at B points (synthetic inputs x = 0.5, lambda = 1; HIP
  * events, 3 launches each), keep the fastest per shape in the context's
- * tuning table, and append the choices as JSON lines to the file named by
- * NNC_AUTOTUNE_CACHE when set (read back by nnc_create).  A set-up call: it
- * allocates temporary device buffers and blocks until done; it overwrites
- * the net's sweep workspace (the next eval recomputes everything).
+ * tuning table (used by the row-major kernels: forward-over-reverse sweeps,
+ * and layer-sum networks without the packed workspace), and append the
+ * choices as JSON lines to the file named by NNC_AUTOTUNE_CACHE when set (read
+ * back by nnc_create).  A set-up call: it allocates temporary device buffers
+ * and blocks until done; it overwrites the net's sweep workspace (the next
+ * eval recomputes everything).
  * nnc_autotune_query: the tuned configuration id of one GEMM shape
  * (dtype = enum nnc_prec), or -1 when the shape is untuned. */
 int nnc_autotune(nnc_ctx ctx, int net, int B);
@@ -255,7 +260,9 @@ int nnc_autotune_query(nnc_ctx ctx, int prec, int M, int N, int K, int acc64, in
  * that type -- the LDS-DMA tilings for FP64 -- falls back to the heuristic
  * choice; batched launches take it when their grouped kernel supports the
  * tiling, and re-plan on the next nnc_eval_batch); config = -1 restores
- * tuned/heuristic selection.
+ * tuned/heuristic selection.  Layer-sum sweeps otherwise run on packed
+ * operands with a tiling and split of their own; while a tiling or a K split
+ * is forced they take these kernels.
  * Errors: NNC_E_ARG (unknown config). */
 int nnc_set_gemm_config(nnc_ctx ctx, int prec, int config);
 int nnc_gemm_config_count(void);
