@@ -1597,74 +1597,14 @@ hipError_t launch_jac_seed(DType at, const double* WL, int m, int K, int Kp, con
   return hipGetLastError();
 }
 
-// H = 0.5 * (P + P^T) summed over split partials, plus obj * diag(q).  With
-// symtile > 0 only the partial tiles on or below the block diagonal were
-// written: entries below it come from P[r][c], above it from P[c][r], and
-// diagonal tiles are symmetrised; the unwritten tiles are never read.
-__global__ void finalize_h_kernel(const double* part, int splits, long long sstride, int n,
-                                  double obj, const double* q, double* H, int symtile, const double* u,
-                                  const double* vv) {
-  __shared__ double ta[32][33];
-  __shared__ double tb[32][33];
-  const int b = blockIdx.z;
-  const int I = blockIdx.y * 32;
-  const int J = blockIdx.x * 32;
-  const int tx = threadIdx.x;
-  const long long base = (long long)b * n * n;
-  for (int yy = threadIdx.y; yy < 32; yy += 8) {
-    double sa = 0.0, sb = 0.0;
-    const int ra = I + yy, ca = J + tx;
-    const int rb = J + yy, cb = I + tx;
-    const bool la = ra < n && ca < n && (symtile <= 0 || ra / symtile >= ca / symtile);
-    const bool lb = rb < n && cb < n && (symtile <= 0 || rb / symtile >= cb / symtile);
-    // up to 8 split partials loaded back to back, then added in split order
-    for (int sp0 = 0; sp0 < splits; sp0 += 8) {
-      double va[8], vb[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double* P = part + (long long)(sp0 + u) * sstride + base;
-        va[u] = la && sp0 + u < splits ? P[(long long)ra * n + ca] : 0.0;
-        vb[u] = lb && sp0 + u < splits ? P[(long long)rb * n + cb] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (la && sp0 + u < splits) sa += va[u];
-        if (lb && sp0 + u < splits) sb += vb[u];
-      }
-    }
-    ta[yy][tx] = sa;
-    tb[yy][tx] = sb;
-  }
-  __syncthreads();
-  for (int yy = threadIdx.y; yy < 32; yy += 8) {
-    const int r = I + yy, c = J + tx;
-    if (r < n && c < n) {
-      double v;
-      if (symtile > 0 && r / symtile != c / symtile)
-        v = r / symtile > c / symtile ? ta[yy][tx] : tb[tx][yy];
-      else
-        v = 0.5 * (ta[yy][tx] + tb[tx][yy]);
-      if (r == c && q) v += obj * q[r];
-      if (u) {
-        // products rounded on their own (contraction into fused multiply-adds
-        // off), so that (r, c) and (c, r) round the same two products and H
-        // stays exactly symmetric
-#pragma clang fp contract(off)
-        const long long rb = (long long)b * n;
-        const double t1 = u[rb + r] * vv[rb + c];
-        const double t2 = vv[rb + r] * u[rb + c];
-        v -= r <= c ? t1 + t2 : t2 + t1;
-      }
-      H[base + (long long)r * n + c] = v;
-    }
-  }
-}
-
-// The same where only the tiles on or below the block diagonal (edge symtile, a
-// multiple of 32) hold partials: one workgroup per 32 x 32 block of the lower
-// triangle sums it once and writes it and its mirror image (the kernel above
-// read every partial twice: 7 points of 784 inputs, 8 slices, 39 -> 16 us).  Blocks within one diagonal tile have
-// both triangles and are symmetrised.
+// H = 0.5 * (P + P^T) summed over split partials, plus obj * diag(q).  Only the
+// tiles on or below the block diagonal (edge symtile, a multiple of 32; one tile
+// where both triangles were written) hold partials: one workgroup per 32 x 32
+// block of the lower triangle sums it once and writes it and its mirror image;
+// blocks within one diagonal tile have both triangles and are symmetrised.
+// Bound by the partials and H in HBM.  (A workgroup per block of H, which reads
+// every partial twice: 7 points of 784 inputs, 8 slices, 39 -> 16 us; one point,
+// both triangles and 2 slices, 8.8 -> 6.9 us.)
 __global__ void __launch_bounds__(256) finalize_sym_kernel(const double* part, int splits, long long sstride, int n,
                                                            double obj, const double* q, double* H, int symtile,
                                                            const double* u, const double* vv) {
@@ -1771,14 +1711,10 @@ hipError_t launch_finalize_h(double* part, int splits, long long split_stride, i
     split_stride *= 8;
   }
   const int nb = (n + 31) / 32;
-  if (symtile > 0 && symtile % 32 == 0 && splits > 0 && B <= 65535) {
-    hipLaunchKernelGGL(finalize_sym_kernel, dim3(nb * (nb + 1) / 2, B), dim3(256), 0, s, (const double*)part, splits,
-                       split_stride, n, obj, q, H, symtile, u, v);
-    return hipGetLastError();
-  }
-  dim3 grid(nb, nb, B);
-  hipLaunchKernelGGL(finalize_h_kernel, grid, dim3(32, 8), 0, s, part, splits, split_stride, n,
-                     obj, q, H, symtile, u, v);
+  const int edge = symtile > 0 ? symtile : nb * 32;
+  if (edge % 32 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(finalize_sym_kernel, dim3(nb * (nb + 1) / 2, B), dim3(256), 0, s, (const double*)part, splits,
+                     split_stride, n, obj, q, H, edge, u, v);
   return hipGetLastError();
 }
 
