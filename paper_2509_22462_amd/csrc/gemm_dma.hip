@@ -21,26 +21,9 @@
 //     range check (offset 2^31, as in gemm.hip), so no branch surrounds a
 //     load and every wave issues the same number of loads per tile.
 #include "gemm_common.h"
+#include "lds_dma.h"
 
 namespace nnc {
-
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-// s_waitcnt immediate that waits until at most n vector-memory operations of
-// this wave are outstanding (expcnt and lgkmcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
-// Workgroup barrier without a memory fence (the compiler barriers keep LDS
-// accesses on their side of it).
-__device__ __forceinline__ void barrier_nofence() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // LDS bytes of one stage of a tiling
 template <typename T, int WM, int WN, int FM, int FN>
@@ -174,8 +157,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g0, int t, int split, c
     for (int kt = 0;; kt += U) {
 #pragma unroll
       for (int s = 0; s < U; ++s) {
-        wait_vm<(NS - 2) * CPT>();
-        barrier_nofence();
+        wait_stage<(NS - 2) * CPT>();
         dma(kt + s + NS - 1, stage((s + NS - 1) % NS));
         compute(stage(s % NS));
         if (kt + s + 1 >= nk) goto done;
@@ -183,7 +165,7 @@ __device__ __forceinline__ void dma_tile(const GemmArgs& g0, int t, int split, c
     }
   }
 done:
-  wait_vm<0>();  // the trailing out-of-range loads
+  wait_loads<0>();  // the trailing out-of-range loads
 
   const double acc64[1][1][4] = {};
   finish_tile<T, WM, WN, FM, FN, false, SWEEP>(g, acc, acc64, m0, n0, wm, wn, lane, split);

@@ -30,28 +30,14 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lds_dma.h"
 #include "nnc_device.h"
 #include "nnc_internal.h"
 #include "pk_device.h"
 
 namespace nnc {
 
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
 namespace {
-
-// s_waitcnt until at most N vector-memory operations of this wave are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
-
-__device__ __forceinline__ void barrier_nofence() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // MFMA accumulators: FP32 for BF16 parts, FP64 for FP64.
 template <typename T> struct PkAcc {
@@ -283,15 +269,14 @@ __device__ __forceinline__ void pk_tile(const GemmArgs& g, int t, int split, cha
   for (int s0 = 0;; s0 += NS) {
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      wait_vm<(NS - 2) * S::CPT>();
-      barrier_nofence();
+      wait_stage<(NS - 2) * S::CPT>();
       dma(s0 + u + NS - 1, st((u + NS - 1) % NS));
       compute(st(u));
       if (s0 + u + 1 >= nk) goto done;
     }
   }
 done:
-  wait_vm<0>();
+  wait_loads<0>();
 #pragma unroll
   for (int j = 0; j < FM; ++j) {
     const int row = (mb0 + wm * FM + j) * 16 + (lane & 15);
@@ -561,8 +546,7 @@ __device__ __forceinline__ void sym_tile(const GemmArgs& g, int t, int split, ch
   for (int s0 = 0;; s0 += NS) {
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      wait_vm<(NS - 2) * S::CPT>();
-      barrier_nofence();
+      wait_stage<(NS - 2) * S::CPT>();
       dma(s0 + u + NS - 1, st((u + NS - 1) % NS));
       compute(st(u));
       if ((s0 + u + 1) % (FOLD / KS) == 0) fold();
@@ -570,7 +554,7 @@ __device__ __forceinline__ void sym_tile(const GemmArgs& g, int t, int split, ch
     }
   }
 done:
-  wait_vm<0>();
+  wait_loads<0>();
   fold();
   double* H = (double*)g.out0 + (long long)split * g.split_stride + b * g.bsO;
 #pragma unroll
