@@ -211,13 +211,16 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
   for (int i = 0; i < 16; ++i)
     a[i] = lane < 16 ? S[16 * s + max(i, c)][16 * s + min(i, c)] : (lane < 32 && i == c ? 1.0 : 0.0);
   // the next pivot is brought up to date first, and the multipliers are all
-  // read before the first is used: its reciprocal, the chain, runs beside them
+  // read before the first is used: its reciprocal, the chain, runs beside them.
+  // Multipliers and factor come from the same entries, row j from the diagonal
+  // on: (i, c) and (c, i) round differently, and a factor other than the one
+  // that was eliminated with is off by the block's condition number.
   double r = recip(readlane_d(a[0], 0));
 #pragma unroll
   for (int j = 0; j < 15; ++j) {
     double u[16];
 #pragma unroll
-    for (int i = j + 1; i < 16; ++i) u[i] = readlane_d(a[i], j);
+    for (int i = j + 1; i < 16; ++i) u[i] = readlane_d(a[j], i);
     const double p = a[j] * r;
     a[j + 1] = fma(-u[j + 1], p, a[j + 1]);
     r = recip(readlane_d(a[j + 1], j + 1));
