@@ -28,7 +28,7 @@
 //
 // What bounds it: the chain of n / 64 panels, each with 64 dependent pivots;
 // the products (n^3 / 3 flops per system) run on v_mfma_f64_16x16x4_f64
-// beside it.  16 systems of 784: 509 us, where assembling M and three launches
+// beside it.  16 systems of 784: 564 us, where assembling M and three launches
 // per panel took 3,370 us.
 #include <math.h>
 
@@ -45,7 +45,8 @@ constexpr int KP = KB + 2;      // LDS row pitch (doubles) of the diagonal block
 // One call's arguments.  The workspace holds the matrix padded to whole
 // panels with an identity (np = n rounded up to 64; rows ld apart), so no
 // block is ragged; L the factor's blocks below the diagonal ones, D per panel
-// the factored diagonal block with its 16 x 16 diagonal blocks inverted, R the
+// the factored diagonal block with its 16 x 16 diagonal blocks inverted (and as
+// they are in blocks above the diagonal, kkt_diag_row / kkt_diag_col), R the
 // right-hand side as it is reduced and Y its solved blocks.
 struct KktArgs {
   const double *H, *d, *a, *s, *delta, *r;
@@ -124,6 +125,10 @@ __device__ __forceinline__ void kkt_load(const KktArgs& g, int b, int k, const i
 __device__ __forceinline__ doublex4 mma64(double a, double b, doublex4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+
+// Where a panel's stored diagonal block keeps its diagonal sub-block s.
+__device__ __forceinline__ constexpr int kkt_diag_row(int s) { return s == 3 ? 16 : 0; }
+__device__ __forceinline__ constexpr int kkt_diag_col(int s) { return s == 3 ? 32 : 16 * (s + 1); }
 
 __device__ __forceinline__ double readlane_d(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
@@ -204,6 +209,13 @@ __device__ __forceinline__ void kkt_rows_of_a(const KktArgs& g, int b, int k, in
 // D L_u^T and L_u^-1 of the unit-triangular factor L_u.  Writes L = L_u sqrt(D)
 // to S and L^-1 to inv; returns 0 or the 1-based order of the first pivot that
 // is not positive and finite.
+//
+// A product with L^-1 is off by L's condition number, which a substitution is
+// not.  Whoever multiplies by it corrects the product once with what L leaves of
+// the right-hand side, x += L^-1 (b - L x), and has the substitution's residual
+// again at the price of two more short products: 256 unknowns of condition
+// 1e9, residual relative to |M| |x| 6e-15 without, 4e-17 with (a row-wise
+// substitution: 4e-17).  16 systems of 784: 511 -> 564 us.
 __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv)[18], int lane) {
   const int c = lane & 15;
   double a[16];
@@ -237,7 +249,7 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
   for (int j = 0; j < 16; ++j) {
     const double v = a[j] * readlane_d(rs, j);
     if (lane < 16) {
-      if (j <= c) S[16 * s + c][16 * s + j] = v;
+      S[16 * s + c][16 * s + j] = j <= c ? v : 0.0;
     } else if (lane < 32) {
       inv[j][c] = j >= c ? v : 0.0;
     }
@@ -247,29 +259,34 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
 
 // L^T x = y of one panel's diagonal block by one wave, 16 unknowns at a time:
 // lane l holds unknown l.  at(i, s): row 16 s + i of the block in this lane's
-// column, the inverted 16 x 16 blocks on the diagonal.
-template <typename At>
-__device__ __forceinline__ void kkt_back_block(At at, int lane, double& yi) {
+// column, the inverted 16 x 16 blocks on the diagonal; diag(i, s): row i of the
+// diagonal sub-block s itself in this lane's column of it.
+template <typename At, typename Diag>
+__device__ __forceinline__ void kkt_back_block(At at, Diag diag, int lane, double& yi) {
 #pragma unroll
   for (int s = 3; s >= 0; --s) {
-    double xs[16];  // y of sub-block s, then x
-#pragma unroll
-    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
-    if (lane >> 4 == s) {
+    double xs[16];  // y of sub-block s, x as its product with the inverse, what that leaves of y, then x
+    auto dot = [&](auto m) {
       double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i & 3] = fma(at(i, s), xs[i], v[i & 3]);
-      yi = (v[0] + v[1]) + (v[2] + v[3]);
-    }
+      for (int i = 0; i < 16; ++i) v[i & 3] = fma(m(i, s), xs[i], v[i & 3]);
+      return (v[0] + v[1]) + (v[2] + v[3]);
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
+    double x0 = 0.0;
+    if (lane >> 4 == s) x0 = dot(at);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(x0, 16 * s + i);
+    double left = 0.0;
+    if (lane >> 4 == s) left = yi - dot(diag);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) xs[i] = readlane_d(left, 16 * s + i);
+    if (lane >> 4 == s) yi = x0 + dot(at);
     if (s == 0) break;
 #pragma unroll
     for (int i = 0; i < 16; ++i) xs[i] = readlane_d(yi, 16 * s + i);
-    if (lane < 16 * s) {
-      double v[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v[i & 3] = fma(at(i, s), xs[i], v[i & 3]);
-      yi -= (v[0] + v[1]) + (v[2] + v[3]);
-    }
+    if (lane < 16 * s) yi -= dot(at);
   }
 }
 
@@ -395,6 +412,18 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
   __syncthreads();
   const int row0 = (k + 1 + blockIdx.y) * KB + 16 * gw;  // this wave's rows of the own block
   double dot = 0.0;                                      // this lane's part of (L_ik y_k)
+  // X^T = L_ss^-1 B^T for 16 rows of B in z's layout, corrected once
+  auto solve16 = [&](int s, const doublex4& w) {
+    doublex4 xs = {0, 0, 0, 0}, lx = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xs = mma64(inv[s][c16][4 * e + q], w[e], xs);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) lx = mma64(S[16 * s + c16][16 * s + 4 * e + q], xs[e], lx);
+    const doublex4 left = w - lx;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xs = mma64(inv[s][c16][4 * e + q], left[e], xs);
+    return xs;
+  };
   // X_s^T = L_ss^-1 (A_s^T - sum_{t < s} L_st X_t^T) of the own rows
   auto own_columns = [&](int s) {
     doublex4 acc = {0, 0, 0, 0};
@@ -405,9 +434,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
         for (int e = 0; e < 4; ++e) acc = mma64(S[16 * s + c16][16 * t + 4 * e + q], z[t][e], acc);
       }
     const doublex4 w = (s == 0 ? z[0] : s == 1 ? z[1] : s == 2 ? z[2] : z[3]) - acc;
-    doublex4 xs = {0, 0, 0, 0};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) xs = mma64(inv[s][c16][4 * e + q], w[e], xs);
+    const doublex4 xs = solve16(s, w);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
       if (t == s) z[t] = xs;
@@ -456,12 +483,10 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     const bool rhs = wave == 0;
     if (rhs || gw > s) {
       const int row = rhs ? KB : 16 * gw + c16;
-      doublex4 xs = {0, 0, 0, 0};
+      doublex4 bv;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double bv = !rhs || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
-        xs = mma64(inv[s][c16][4 * e + q], bv, xs);
-      }
+      for (int e = 0; e < 4; ++e) bv[e] = !rhs || c16 == 0 ? S[row][16 * s + 4 * e + q] : 0.0;
+      const doublex4 xs = solve16(s, bv);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (!rhs || c16 == 0) S[row][16 * s + 4 * e + q] = xs[e];
@@ -487,12 +512,18 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
       double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
       for (int idx = tid; idx < KB * KB; idx += kPanelThreads) {
         const int i = idx / KB, j = idx % KB;
-        Dk[idx] = i / 16 == j / 16 ? inv[i / 16][i % 16][j % 16] : S[i][j];
+        if (i / 16 == j / 16) {
+          Dk[idx] = inv[i / 16][i % 16][j % 16];
+          Dk[(kkt_diag_row(i / 16) + i % 16) * KB + kkt_diag_col(i / 16) + j % 16] = S[i][j];
+        } else if (i > j) {
+          Dk[idx] = S[i][j];
+        }
       }
       if (tid < KB) g.Y[(long long)b * g.np + kb + tid] = S[KB][tid];
     } else if (wave == 0) {  // one panel: L^T x = y here
       double yi = S[KB][lane];
-      kkt_back_block([&](int i, int s) { return lane >> 4 == s ? inv[s][i][c16] : S[16 * s + i][lane]; }, lane, yi);
+      kkt_back_block([&](int i, int s) { return lane >> 4 == s ? inv[s][i][c16] : S[16 * s + i][lane]; },
+                     [&](int i, int s) { return S[16 * s + i][16 * s + c16]; }, lane, yi);
       if (lane < g.n) x[(long long)b * g.n + lane] = yi;
     }
     if (k == 0 && tid == 0) g.info[b] = 0;
@@ -549,7 +580,8 @@ __global__ void __launch_bounds__(1024) kkt_back_kernel(KktArgs g, double* __res
     for (int i = 0; i < PF; ++i) pre[i] = tid < kb ? p[(long long)i * g.ld] : 0.0;
     if (tid < 64) {
       double yi = y[kb + lane];
-      kkt_back_block([&](int i, int s) { return D[16 * s + i][lane]; }, lane, yi);
+      kkt_back_block([&](int i, int s) { return D[16 * s + i][lane]; },
+                     [&](int i, int s) { return D[kkt_diag_row(s) + i][kkt_diag_col(s) + (lane & 15)]; }, lane, yi);
       y[kb + lane] = yi;
       if (kb + lane < g.n) xb[kb + lane] = yi;
     }
