@@ -1,7 +1,8 @@
 """Device KKT solve of matrices whose neighbouring unknowns are strongly coupled:
 a smooth (Gaussian) kernel on [0, 1] plus a small multiple of the identity, whose
 16 x 16 diagonal blocks are as badly conditioned as the whole.  Cholesky factors
-them without trouble, and its residual does not know the condition number."""
+them without trouble, and its residual does not know the condition number.  Also
+pivots below the range in which their reciprocals are finite."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,13 @@ def test_residual_is_independent_of_the_condition(ctx, n, B):
     assert np.all(info == 0)
     for b in range(B):
         assert backward_error(M[b], x[b], r[b]) < 4 * np.sqrt(n / 16) * 2.0 ** -53, eps[b]
+
+
+@pytest.mark.parametrize("n", [1, 20, 70])
+def test_subnormal_pivots(ctx, n):
+    """Diagonal systems down to the least normal numbers and below: x = r / d, d
+    and r exact, to a few roundings."""
+    d = np.logspace(-307, -314, n)
+    x, info = solve(ctx, np.diag(d)[None], 3.0 * d[None])
+    assert info.tolist() == [0]
+    assert np.max(np.abs(x / ((3.0 * d) / d) - 1.0)) < 8 * 2.0 ** -53
