@@ -195,8 +195,9 @@ int nnc_eval(nnc_ctx ctx, int net, int B, const double* x, const double* y, doub
  * right-looking, 64-column panels) and two triangular solves.
  *
  * nnc_kkt_create: a solver for n x n systems (1 <= n <= 2048), at most max_B
- *   per call; allocates the factor workspace now: about max_B * n' * (n' + 80)
- *   doubles, n' = n rounded up to 64.
+ *   per call; allocates the factor workspace now: none up to 64 unknowns, else
+ *   about max_B * n' * (n' + 80) doubles, n' = n rounded up to 64 (where that
+ *   does not fit, for fewer systems, which a call then takes in turn).
  * nnc_kkt_solve: all pointers DEVICE, FP64 unless noted, caller-owned:
  *   H [B][n][n] (read only; e.g. the output of nnc_eval_hess_lag), d [B][n]
  *   or NULL, a [B][n] and s [B] (both or neither), delta [B] or NULL,

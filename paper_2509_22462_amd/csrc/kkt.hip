@@ -32,6 +32,8 @@
 // per panel took 3,370 us.
 #include <math.h>
 
+#include <algorithm>
+
 #include "../../include/nnc.h"
 #include "nnc_device.h"
 #include "nnc_internal.h"
@@ -216,7 +218,8 @@ __device__ __forceinline__ void kkt_rows_of_a(const KktArgs& g, int b, int k, in
 // again at the price of two more short products: 256 unknowns of condition
 // 1e9, residual relative to |M| |x| 6e-15 without, 4e-17 with (a row-wise
 // substitution: 4e-17).  16 systems of 784: 511 -> 564 us.
-__device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv)[18], int lane) {
+template <int PITCH>
+__device__ __forceinline__ int kkt_factor16(double (*S)[PITCH], int s, double (*inv)[18], int lane) {
   const int c = lane & 15;
   double a[16];
 #pragma unroll
@@ -276,11 +279,13 @@ __device__ __forceinline__ int kkt_factor16(double (*S)[KP], int s, double (*inv
 // L^T x = y of one panel's diagonal block by one wave, 16 unknowns at a time:
 // lane l holds unknown l.  at(i, s): row 16 s + i of the block in this lane's
 // column, the inverted 16 x 16 blocks on the diagonal; diag(i, s): row i of the
-// diagonal sub-block s itself in this lane's column of it.
+// diagonal sub-block s itself in this lane's column of it; only the first `subs`
+// sub-blocks hold unknowns.
 template <typename At, typename Diag>
-__device__ __forceinline__ void kkt_back_block(At at, Diag diag, int lane, double& yi) {
+__device__ __forceinline__ void kkt_back_block(At at, Diag diag, int subs, int lane, double& yi) {
 #pragma unroll
   for (int s = 3; s >= 0; --s) {
+    if (s >= subs) continue;
     double xs[16];  // y of sub-block s, x as its product with the inverse, what that leaves of y, then x
     auto dot = [&](auto m) {
       double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -319,15 +324,19 @@ __device__ __forceinline__ void kkt_back_block(At at, Diag diag, int lane, doubl
 // date itself, so that only the solve with the block just factored stands
 // between two runs of pivots.  16 systems of 784: 42 us a panel when four waves
 // did both in turn, 34 us now.
+//
+// ONE: a single panel, solved here too (no panel before it to read).
 constexpr int kPanelThreads = 320;
-__global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, int k, double* __restrict__ x) {
+template <bool ONE>
+__global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, int panel, double* __restrict__ x) {
   __shared__ __attribute__((aligned(16))) double S[KB + 1][KP];
-  __shared__ __attribute__((aligned(16))) double Pk[KB][KP];
+  __shared__ __attribute__((aligned(16))) double Pk[ONE ? 1 : KB][KP];
   __shared__ double inv[4][16][18];
   __shared__ int s_fail;
   const int b = blockIdx.x;
+  const int k = ONE ? 0 : panel;
   if (k > 0 && g.info[b] != 0) return;
-  const int nblk = g.np / KB;
+  const int nblk = ONE ? 1 : g.np / KB;
   const int below = nblk - k - 1;
   const int P = max(1, below);
   const int tid = threadIdx.x;
@@ -336,7 +345,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
   double* Lb = g.L + (long long)b * g.np * g.ld;
   const int kb = k * KB;
 
-  if ((int)blockIdx.y >= P) {  // A_IJ -= L_I,k-1 L_J,k-1^T, a 32 x 32 quadrant per wave
+  if (!ONE && (int)blockIdx.y >= P) {  // A_IJ -= L_I,k-1 L_J,k-1^T, a 32 x 32 quadrant per wave
     if (wave == 4) return;
     const int t = blockIdx.y - P;
     int ti = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
@@ -475,6 +484,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     for (int e = 0; e < 4; ++e)
       if (!rhs || c16 == 0) S[row][16 * j + 4 * e + q] -= acc[e];
   };
+  const int subs = min(4, (g.n - kb + 15) / 16);  // sub-blocks that are not all padding
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     if (wave == 0) {
@@ -492,7 +502,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     __syncthreads();
     if (s_fail) {
       if (blockIdx.y == 0 && tid == 0) g.info[b] = s_fail;
-      if (nblk == 1 && tid < g.n) x[(long long)b * g.n + tid] = 0.0;
+      if (ONE && tid < g.n) x[(long long)b * g.n + tid] = 0.0;
       return;
     }
     // blocks below (row group i > s; wave 0: the right-hand side): X = A L_ss^-T
@@ -508,7 +518,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
         if (!rhs || c16 == 0) S[row][16 * s + 4 * e + q] = xs[e];
     }
     __syncthreads();
-    if (s == 3) break;
+    if (s == 3 || s + 1 == subs) break;
     // block (s + 1, s + 1) by wave 0, the others (i = 4: the right-hand side) by the row groups
     if (wave == 0) {
       trail(s, s + 1, s + 1);
@@ -524,12 +534,12 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     }
   }
   if (blockIdx.y == 0) {
-    if (below > 0 || k > 0) {
+    if constexpr (!ONE) {
       double* Dk = g.D + ((long long)b * nblk + k) * KB * KB;
       for (int idx = tid; idx < KB * KB; idx += kPanelThreads) {
         const int i = idx / KB, j = idx % KB;
         if (i / 16 == j / 16) {
-          Dk[idx] = inv[i / 16][i % 16][j % 16];
+          Dk[idx] = i / 16 < subs ? inv[i / 16][i % 16][j % 16] : i == j ? 1.0 : 0.0;
           Dk[(kkt_diag_row(i / 16) + i % 16) * KB + kkt_diag_col(i / 16) + j % 16] = S[i][j];
         } else if (i > j) {
           Dk[idx] = S[i][j];
@@ -539,7 +549,7 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     } else if (wave == 0) {  // one panel: L^T x = y here
       double yi = S[KB][lane];
       kkt_back_block([&](int i, int s) { return lane >> 4 == s ? inv[s][i][c16] : S[16 * s + i][lane]; },
-                     [&](int i, int s) { return S[16 * s + i][16 * s + c16]; }, lane, yi);
+                     [&](int i, int s) { return S[16 * s + i][16 * s + c16]; }, subs, lane, yi);
       if (lane < g.n) x[(long long)b * g.n + lane] = yi;
     }
     if (k == 0 && tid == 0) g.info[b] = 0;
@@ -554,6 +564,51 @@ __global__ void __launch_bounds__(kPanelThreads, 3) kkt_panel_kernel(KktArgs g, 
     const double rv = k > 0 ? *R : (i < g.n ? g.r[(long long)b * g.n + i] : 0.0);
     *R = rv - dot;
   }
+}
+
+// Up to 16 unknowns: a wave per system, four systems per workgroup.  A panel's
+// workgroup would factor one 16 x 16 block of its four with one wave of its five.
+// 20,000 systems of 2, 8 and 16 unknowns: 1,587 us each there, 51 here.
+constexpr int kKktSmall = 16;
+__global__ void __launch_bounds__(256) kkt_small_kernel(KktArgs g, int B, double* __restrict__ x) {
+  __shared__ double Sall[4][16][18], invall[4][16][18];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = lane & 15;
+  double (*S)[18] = Sall[wave];
+  double (*inv)[18] = invall[wave];
+  const bool live = (int)blockIdx.x * 4 + wave < B;
+  const int b = min((int)blockIdx.x * 4 + wave, B - 1);
+  int ii[4], jj[4];
+  double v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    ii[e] = 4 * e + (lane >> 4);
+    jj[e] = c;
+  }
+  kkt_entries<4>(g, b, ii, jj, v);
+  const double r = lane < g.n ? g.r[(long long)b * g.n + lane] : 0.0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) S[ii[e]][c] = v[e];
+  __syncthreads();
+  const int f = kkt_factor16(S, 0, inv, lane);
+  __syncthreads();
+  auto dot = [&](auto m, double y) {  // sum over i of m(i) and lane i's y
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t[i & 3] = fma(m(i), readlane_d(y, i), t[i & 3]);
+    return (t[0] + t[1]) + (t[2] + t[3]);
+  };
+  auto row = [&](int i) { return S[c][i]; };
+  auto col = [&](int i) { return S[i][c]; };
+  auto irow = [&](int i) { return inv[c][i]; };
+  auto icol = [&](int i) { return inv[i][c]; };
+  double y = dot(irow, r);
+  y += dot(irow, r - dot(row, y));
+  double xv = dot(icol, y);
+  xv += dot(icol, y - dot(col, xv));
+  if (!live) return;
+  if (lane == 0) g.info[b] = f;
+  if (lane < g.n) x[(long long)b * g.n + lane] = f ? 0.0 : xv;
 }
 
 // L^T x = y, one workgroup of 16 waves per system: wave 0 solves a panel's 64
@@ -597,7 +652,7 @@ __global__ void __launch_bounds__(1024) kkt_back_kernel(KktArgs g, double* __res
     if (tid < 64) {
       double yi = y[kb + lane];
       kkt_back_block([&](int i, int s) { return D[16 * s + i][lane]; },
-                     [&](int i, int s) { return D[kkt_diag_row(s) + i][kkt_diag_col(s) + (lane & 15)]; }, lane, yi);
+                     [&](int i, int s) { return D[kkt_diag_row(s) + i][kkt_diag_col(s) + (lane & 15)]; }, 4, lane, yi);
       y[kb + lane] = yi;
       if (kb + lane < g.n) xb[kb + lane] = yi;
     }
@@ -627,7 +682,8 @@ __global__ void __launch_bounds__(1024) kkt_back_kernel(KktArgs g, double* __res
 struct Kkt {
   int n = 0, maxB = 0;
   int np = 0, ld = 0;
-  double* L = nullptr;  // one allocation: L, D, R, Y of KktArgs
+  int wsB = 0;          // systems the workspace holds
+  double* L = nullptr;  // one allocation: L, D, R, Y of KktArgs (NULL for one panel)
 };
 
 // Doubles of one system's workspace (KktArgs): rows of L 16 doubles past a
@@ -667,9 +723,18 @@ int nnc_kkt_create(nnc_ctx ctx, int n, int max_B, int* kkt) {
   k->maxB = max_B;
   k->np = (n + KB - 1) / KB * KB;
   k->ld = k->np + 16;
-  if (hipMalloc(&k->L, (size_t)max_B * kkt_words(k) * sizeof(double)) != hipSuccess) {
-    delete k;
-    return kkt_fail(c, NNC_E_NOMEM, "KKT factor workspace");
+  // One panel is factored and solved in LDS.  Otherwise the workspace is up to
+  // six times H (65 unknowns): where it does not fit for all systems, it holds
+  // as many as do and a call takes them in turn.
+  k->wsB = max_B;
+  while (k->np > KB && hipMalloc(&k->L, (size_t)k->wsB * kkt_words(k) * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    k->L = nullptr;
+    if (k->wsB == 1) {
+      delete k;
+      return kkt_fail(c, NNC_E_NOMEM, "KKT factor workspace");
+    }
+    k->wsB = (k->wsB + 1) / 2;
   }
   c->kkts.push_back(k);
   *kkt = (int)c->kkts.size() - 1;
@@ -700,31 +765,43 @@ int nnc_kkt_solve(nnc_ctx ctx, int kkt, int B, const double* H, const double* d,
   const int n = k->n;
   const long long total = (long long)B * n * n;
   if ((total + 255) / 256 > 0x7fffffffLL) return kkt_fail(c, NNC_E_SHAPE, "B * n * n too large");
-  KktArgs g;
-  g.H = H;
-  g.d = d;
-  g.a = a;
-  g.s = s;
-  g.delta = delta;
-  g.r = r;
-  g.info = info;
-  g.n = n;
-  g.np = k->np;
-  g.ld = k->ld;
-  g.L = k->L;
-  g.D = g.L + (size_t)B * k->np * k->ld;
-  g.R = g.D + (size_t)B * k->np * KB;
-  g.Y = g.R + (size_t)B * k->np;
   ProfRec pr;
   prof_begin(c, NNC_KC_OTHER, &pr);
   const int nblk = k->np / KB;
-  for (int p = 0; p < nblk; ++p) {
-    const int below = nblk - p - 1;
-    const int tiles = p > 0 ? below * (below + 1) / 2 : 0;
-    hipLaunchKernelGGL(kkt_panel_kernel, dim3(B, (below > 0 ? below : 1) + tiles), dim3(kPanelThreads), 0, c->stream, g, p,
-                       dx);
+  for (int b0 = 0, nb = 0; b0 < B; b0 += nb) {
+    nb = std::min(k->wsB, B - b0);
+    const long long o = (long long)b0 * n;
+    KktArgs g;
+    g.H = H + o * n;
+    g.d = d ? d + o : nullptr;
+    g.a = a ? a + o : nullptr;
+    g.s = s ? s + b0 : nullptr;
+    g.delta = delta ? delta + b0 : nullptr;
+    g.r = r + o;
+    g.info = info + b0;
+    g.n = n;
+    g.np = k->np;
+    g.ld = k->ld;
+    g.L = k->L;
+    g.D = nblk > 1 ? g.L + (size_t)nb * k->np * k->ld : nullptr;
+    g.R = nblk > 1 ? g.D + (size_t)nb * k->np * KB : nullptr;
+    g.Y = nblk > 1 ? g.R + (size_t)nb * k->np : nullptr;
+    if (n <= kKktSmall) {
+      hipLaunchKernelGGL(kkt_small_kernel, dim3((nb + 3) / 4), dim3(256), 0, c->stream, g, nb, dx + o);
+      continue;
+    }
+    if (nblk == 1) {
+      hipLaunchKernelGGL(kkt_panel_kernel<true>, dim3(nb), dim3(kPanelThreads), 0, c->stream, g, 0, dx + o);
+      continue;
+    }
+    for (int p = 0; p < nblk; ++p) {
+      const int below = nblk - p - 1;
+      const int tiles = p > 0 ? below * (below + 1) / 2 : 0;
+      hipLaunchKernelGGL(kkt_panel_kernel<false>, dim3(nb, (below > 0 ? below : 1) + tiles), dim3(kPanelThreads), 0,
+                         c->stream, g, p, dx + o);
+    }
+    hipLaunchKernelGGL(kkt_back_kernel, dim3(nb), dim3(1024), 0, c->stream, g, dx + o);
   }
-  if (nblk > 1) hipLaunchKernelGGL(kkt_back_kernel, dim3(B), dim3(1024), 0, c->stream, g, dx);
   const hipError_t e = hipGetLastError();
   prof_end(c, &pr);
   if (e != hipSuccess) {
