@@ -11,15 +11,19 @@
 // a fragment read is 64 consecutive 16-byte lanes: no bank conflicts, no
 // swizzle, no address arithmetic per row.
 //
-// FP32 (NP = 3): x = hi + mid + lo, each the leading 8 significant bits of
-// what is left, so the three parts hold all 24 bits (cut_parts below), and
-//   x y = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + O(2^-24 x y),
-// six BF16 products accumulated in FP32: at 16x the rate of
-// the FP32 instruction they cost 6/16 of its time.  The dropped terms are a
-// quarter ulp of each product.  The five smaller products have accumulators of
-// their own, so the large ones are rounded by one product in six: on normally
-// distributed operands the error against FP64 sums is 5.9e-7 at K = 8192 and
-// 1.9e-7 at K = 1024, where the FP32 instruction's is 1.6e-6 and 5.7e-7.
+// FP32 (NP = 3): x = hi + mid + lo, each what is left rounded to 8 significant
+// bits, so the three parts hold all 24 (cut_parts in pk_device.h), and
+//   x y = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + what is left out,
+// six BF16 products accumulated in FP32: at 16x the rate of the FP32
+// instruction they cost 6/16 of its time.  What is left out, mid lo + lo mid +
+// lo lo, is at most 2^-23 of a product, 2e-8 of it in the root mean square and of
+// either sign: less than the rounding of one FP32 addition.  (Parts cut off
+// instead of rounded left out 4e-8 on average, always with the product's sign: H
+// of hidden widths up to 64 was off by 1.02 to 1.3 times the FP32 instruction's
+// error.)  The five smaller products have accumulators of their own, so the
+// large ones are rounded by one product in six.  Errors of H against FP64, this
+// and the FP32 instruction: hidden widths of 16 1.1-1.3e-7 and 1.3-1.6e-7, of 64
+// 1.3-1.6e-7 and 1.6-2.2e-7, of 512 1.4-1.7e-7 and 3.1-4.8e-7.
 //
 // What bounds it: the matrix cores and the LDS reads that feed them (each
 // three-part fragment pair feeds six MFMAs, a BF16 pair one).  Measured with
@@ -75,10 +79,7 @@ __device__ __forceinline__ void put_u(const PackedU& u, int b, int i, int col, c
   A x[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    if constexpr (sizeof(A) == 8)
-      x[e] = v[e] * sqrt(fabs(sd[e]));
-    else
-      x[e] = v[e] * sqrtf(fabsf((float)sd[e]));
+    x[e] = (A)((double)v[e] * sqrt(fabs(sd[e])));  // rounded once: an FP32 root is off alike in every row
   }
   put_packed<T>(u.U, b * u.np16 + i, col, u.kt, x);
   if (i != 0) return;

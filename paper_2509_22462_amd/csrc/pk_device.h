@@ -36,17 +36,20 @@ __device__ __forceinline__ void cut_parts(const float (&v)[4], uint2 (&o)[NP]) {
     for (int e = 0; e < 4; ++e) t[e] = (bf16)v[e];
     o[0] = __builtin_bit_cast(uint2, t);
   } else {
-    // Each part is the leading 8 significant bits of what is left (cut off,
-    // not rounded): the differences are exact, the third part leaves nothing,
-    // and no finite element becomes infinite.  An infinite element is its
-    // first part alone.
+    // Each of the first two parts is what is left rounded to 8 significant bits:
+    // the differences are exact, the third part leaves nothing, and what the
+    // products below leave out (gemm_pk.hip) has either sign.  An element that
+    // rounds past the largest finite one is cut off there instead; an infinite
+    // element is its first part alone.
     uint32_t w[3][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      w[0][e] = __float_as_uint(v[e]) & 0xffff0000u;
+      w[0][e] = __float_as_uint((float)(bf16)v[e]);
+      if ((w[0][e] & 0x7fffffffu) == 0x7f800000u) w[0][e] = __float_as_uint(v[e]) & 0xffff0000u;
       const float r = fabsf(v[e]) == INFINITY ? 0.f : v[e] - __uint_as_float(w[0][e]);
-      w[1][e] = __float_as_uint(r) & 0xffff0000u;
-      w[2][e] = __float_as_uint(r - __uint_as_float(w[1][e]));
+      const float m = (float)(bf16)r;
+      w[1][e] = __float_as_uint(m);
+      w[2][e] = __float_as_uint(r - m);
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p)
