@@ -53,6 +53,11 @@ template <> struct PkAcc<double> {
   using V = doublex4;
 };
 
+// The sum of an FP32 product's large and small parts' accumulators.  Products
+// that overflow take the large one to infinity; the small parts have either sign
+// and may overflow to the other one.
+__device__ __forceinline__ float with_low(float acc, float low) { return fabsf(acc) == INFINITY ? acc : acc + low; }
+
 // Four consecutive elements of a row-major FP32, BF16 or FP64 array (aligned
 // to the four).
 template <typename T, typename A>
@@ -69,24 +74,55 @@ __device__ __forceinline__ void put4(T* o, const A (&x)[4]) {
   }
 }
 
-// Four consecutive elements of T (row i of point b) as U = sqrt|s| T and, from
-// the point's first row, the signs of s.
-template <typename T, typename A>
-__device__ __forceinline__ void put_u(const PackedU& u, int b, int i, int col, const double* s, const A (&v)[4]) {
-  const double2 s0 = *(const double2*)s;
-  const double2 s1 = *(const double2*)(s + 2);
-  const double sd[4] = {s0.x, s0.y, s1.x, s1.y};
-  A x[4];
+// The square roots of four |s|.  FP32: each in two parts, the second one Newton
+// step, so that v sqrt|s| is rounded once (an FP32 root would be off alike in
+// every row).
+template <typename A>
+struct Roots {
+  A q[4];
+  float c[4];
+};
+__device__ __forceinline__ void load_roots(const double* s, Roots<double>& r) {
+  const double2 s0 = *(const double2*)s, s1 = *(const double2*)(s + 2);
+  r.q[0] = sqrt(fabs(s0.x));
+  r.q[1] = sqrt(fabs(s0.y));
+  r.q[2] = sqrt(fabs(s1.x));
+  r.q[3] = sqrt(fabs(s1.y));
+}
+__device__ __forceinline__ void load_roots(const double* s, Roots<float>& r) {
+  const double2 s0 = *(const double2*)s, s1 = *(const double2*)(s + 2);
+  const double a[4] = {fabs(s0.x), fabs(s0.y), fabs(s1.x), fabs(s1.y)};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    x[e] = (A)((double)v[e] * sqrt(fabs(sd[e])));  // rounded once: an FP32 root is off alike in every row
+    const float h = (float)a[e];
+    r.q[e] = __builtin_amdgcn_sqrtf(h);
+    r.c[e] = (fmaf(-r.q[e], r.q[e], h) + (float)(a[e] - (double)h)) * (0.5f * __builtin_amdgcn_rcpf(r.q[e]));
+    if (!(h > 0x1p-80f && h < 0x1p80f)) {  // zero, the ends of the range, NaN
+      const double d = sqrt(a[e]);
+      r.q[e] = (float)d;
+      r.c[e] = d < 0x1p100 ? (float)(d - (double)r.q[e]) : 0.f;
+    }
   }
+}
+__device__ __forceinline__ double times_root(double v, const Roots<double>& r, int e) { return v * r.q[e]; }
+__device__ __forceinline__ float times_root(float v, const Roots<float>& r, int e) {
+  return fmaf(v, r.q[e], fabsf(v) < INFINITY ? v * r.c[e] : 0.f);
+}
+
+// Four consecutive elements of T (row i of point b) as U = sqrt|s| T (r: the
+// roots) and, from the point's first row, the signs of s.
+template <typename T, typename A>
+__device__ __forceinline__ void put_u(const PackedU& u, int b, int i, int col, const double* s, const Roots<A>& r,
+                                      const A (&v)[4]) {
+  A x[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = times_root(v[e], r, e);
   put_packed<T>(u.U, b * u.np16 + i, col, u.kt, x);
   if (i != 0) return;
   char* o = (char*)u.sgn + (long long)b * u.kt * 64;
   uint32_t h[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) h[e] = (uint32_t)__double2hiint(sd[e]) & 0x80000000u;
+  for (int e = 0; e < 4; ++e) h[e] = (uint32_t)__double2hiint(s[e]) & 0x80000000u;
   if constexpr (sizeof(T) == 8) {
     *(uint4*)(o + (long long)col * 8) = make_uint4(0u, h[0], 0u, h[1]);
     *(uint4*)(o + (long long)col * 8 + 16) = make_uint4(0u, h[2], 0u, h[3]);
@@ -95,10 +131,12 @@ __device__ __forceinline__ void put_u(const PackedU& u, int b, int i, int col, c
   }
 }
 
-// Four consecutive results of one row through the epilogue of g.epi.
+// Four consecutive results of one row through the epilogue of g.epi; r: the roots
+// of point rb's columns, if that is this row's point.
 template <typename T>
 __device__ __forceinline__ void pk_epilogue(const GemmArgs& g, int row, int col, int b,
-                                            const typename PkAcc<T>::A (&v)[4], int split) {
+                                            const typename PkAcc<T>::A (&v)[4], int split,
+                                            Roots<typename PkAcc<T>::A>& r, int& rb) {
   using A = typename PkAcc<T>::A;
   if (g.epi == EPI_PART) {
     put4<A, A>((A*)g.out0 + (long long)split * g.split_stride + (long long)row * g.ldo + col, v);
@@ -112,7 +150,9 @@ __device__ __forceinline__ void pk_epilogue(const GemmArgs& g, int row, int col,
       const A x[4] = {v[0] * (A)sv[0], v[1] * (A)sv[1], v[2] * (A)sv[2], v[3] * (A)sv[3]};
       put4<T, A>((T*)g.out2 + (long long)row * g.ldo + col, x);
     } else {
-      put_u<T>(g.u, b, row - b * g.u.n, g.ucol + col, sv, v);
+      if (b != rb) load_roots(sv, r);
+      rb = b;
+      put_u<T>(g.u, b, row - b * g.u.n, g.ucol + col, sv, r, v);
     }
   }
   if (g.out1) {
@@ -278,19 +318,36 @@ __device__ __forceinline__ void pk_tile(const GemmArgs& g, int t, int split, cha
   }
 done:
   wait_loads<0>();
+  int pt[FM];  // the rows' points
 #pragma unroll
-  for (int j = 0; j < FM; ++j) {
+  for (int j = 0; j < FM; ++j) pt[j] = ((mb0 + wm * FM + j) * 16 + (lane & 15)) / g.rdiv;
+  Roots<typename PkAcc<T>::A> r;
+  int rb = -1;
+  auto out = [&](int i, int j) {
+    const int col = (nb0 + wn * FN + i) * 16 + (lane >> 4) * 4;
     const int row = (mb0 + wm * FM + j) * 16 + (lane & 15);
-    if (row >= g.M) continue;
-    const int b = row / g.rdiv;
+    if (row >= g.M || col >= g.N) return;
+    typename PkAcc<T>::A v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (NP == 3)
+        v[e] = with_low(acc[i][j][e], low[i][j][e]);
+      else
+        v[e] = acc[i][j][e];
+    }
+    pk_epilogue<T>(g, row, col, pt[j], v, split, r, rb);
+  };
+  if constexpr (sizeof(T) == 2) {  // row-major outputs: along the row
+#pragma unroll
+    for (int j = 0; j < FM; ++j)
+#pragma unroll
+      for (int i = 0; i < FN; ++i) out(i, j);
+  } else {  // a column's roots serve its rows
 #pragma unroll
     for (int i = 0; i < FN; ++i) {
-      const int col = (nb0 + wn * FN + i) * 16 + (lane >> 4) * 4;
-      if (col < g.N) {
-        const V a = NP == 3 ? acc[i][j] + low[i][j] : acc[i][j];
-        const typename PkAcc<T>::A v[4] = {a[0], a[1], a[2], a[3]};
-        pk_epilogue<T>(g, row, col, b, v, split);
-      }
+      rb = -1;
+#pragma unroll
+      for (int j = 0; j < FM; ++j) out(i, j);
     }
   }
 }
@@ -362,7 +419,9 @@ __global__ void __launch_bounds__(256) pk_reduce_kernel(GemmArgs g, const void* 
 #pragma unroll 4
   for (int s = 1; s < splits; ++s) t += *(const V*)(p + s * MN);
   const A v[4] = {t[0], t[1], t[2], t[3]};
-  pk_epilogue<T>(g, row, col, row / g.rdiv, v, 0);
+  Roots<A> r;
+  int rb = -1;
+  pk_epilogue<T>(g, row, col, row / g.rdiv, v, 0, r, rb);
 }
 
 template <typename T>
@@ -402,6 +461,32 @@ struct SymTile {
   static constexpr int SBASE = 2 * PBASE;
   static constexpr int STAGE = SBASE + NW * 1024;
 };
+
+// One entry of the product element by element, where the parts' products came to
+// NaN: past the FP32 range the small ones may overflow against the large ones,
+// which have one accumulator here (a second one, as in pk_tile, spills: 137M
+// network 2 % slower).  The entry of a NaN element is known at that element.
+__device__ double sym_entry(const GemmArgs& g, int b, int row, int col, int k0, int k1) {
+  auto elem = [&](int r, int k) {
+    const char* p = (const char*)g.u.U + packed_offset<float>(b * g.u.np16 + r, k, g.u.kt);
+    auto part = [&](int i) { return __uint_as_float((uint32_t) * (const uint16_t*)(p + i * 1024) << 16); };
+    const float lo = part(2);
+    return fabsf(lo) == INFINITY ? lo : part(0) + part(1) + lo;
+  };
+  const uint16_t* sgn = (const uint16_t*)((const char*)g.u.sgn + (long long)b * g.u.kt * 64);
+  double sum = 0.0;
+  float acc = 0.f;
+  for (int k = k0; k < k1; ++k) {
+    const float x = elem(row, k), y = elem(col, k);
+    if (x != x || y != y) return NAN;
+    acc = fmaf(sgn[k] ? -x : x, y, acc);
+    if ((k & 63) == 63) {
+      sum += (double)acc;
+      acc = 0.f;
+    }
+  }
+  return sum + (double)acc;
+}
 
 // (GROUPED only names the caller.)
 template <typename T, int WN, int WM, int FN, int FM, int KS, int NS, bool GROUPED>
@@ -571,7 +656,8 @@ done:
           if constexpr (sizeof(T) == 8)
             H[(long long)row * g.ldo + col] = acc[i][j][e];
           else
-            H[(long long)row * g.ldo + col] = sum[i][j][e];
+            H[(long long)row * g.ldo + col] =
+                sum[i][j][e] == sum[i][j][e] ? sum[i][j][e] : sym_entry(g, b, row, col, k0 * KB, min(kt * KB, k0 * KB + g.kper));
         }
       }
     }
@@ -633,7 +719,10 @@ __global__ void __launch_bounds__(256) pack_u_kernel(PackUArgs a) {
     const int c = cx * 128 + (threadIdx.x >> 6) * 32 + h * 16 + (lane >> 4) * 4;
     if (c >= dp) return;
     const A v[4] = {(A)t[c], (A)t[c + 1], (A)t[c + 2], (A)t[c + 3]};
-    put_u<T>(a.u, b, i, a.koff[l] + c, a.s[l] + (long long)b * dp + c, v);
+    const double* s = a.s[l] + (long long)b * dp + c;
+    Roots<A> r;
+    load_roots(s, r);
+    put_u<T>(a.u, b, i, a.koff[l] + c, s, r, v);
     if (a.P && l == 0) {
       const A* d = (const A*)a.d1 + (long long)b * dp + c;
       const A x[4] = {v[0] * d[0], v[1] * d[1], v[2] * d[2], v[3] * d[3]};

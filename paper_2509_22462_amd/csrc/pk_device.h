@@ -38,22 +38,47 @@ __device__ __forceinline__ void cut_parts(const float (&v)[4], uint2 (&o)[NP]) {
   } else {
     // Each of the first two parts is what is left rounded to 8 significant bits:
     // the differences are exact, the third part leaves nothing, and what the
-    // products below leave out (gemm_pk.hip) has either sign.  An element that
-    // rounds past the largest finite one is cut off there instead; an infinite
-    // element is its first part alone.
-    uint32_t w[3][4];
+    // products below leave out (gemm_pk.hip) has either sign.
+    typedef float float2v __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    uint32_t w[3][2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      w[0][e] = __float_as_uint((float)(bf16)v[e]);
-      if ((w[0][e] & 0x7fffffffu) == 0x7f800000u) w[0][e] = __float_as_uint(v[e]) & 0xffff0000u;
-      const float r = fabsf(v[e]) == INFINITY ? 0.f : v[e] - __uint_as_float(w[0][e]);
-      const float m = (float)(bf16)r;
-      w[1][e] = __float_as_uint(m);
-      w[2][e] = __float_as_uint(r - m);
+    for (int h = 0; h < 2; ++h) {
+      float r0 = v[2 * h], r1 = v[2 * h + 1];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        w[p][h] = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2v{r0, r1}, bf16x2));
+        r0 -= __uint_as_float(w[p][h] << 16);
+        r1 -= __uint_as_float(w[p][h] & 0xffff0000u);
+      }
+    }
+    // An element that rounds past the largest finite one is cut off there instead.
+    // An infinite one is 1, 0 and itself: the third part meets only first parts,
+    // which are zero or not as their elements are, so infinity times a number is
+    // infinite and times zero NaN, as for the elements themselves.  (As the first
+    // part it met the zero second and third parts of every short number.)
+    const float big = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+    if (__builtin_expect(big >= 0x1.ffp127f, 0)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t t[3] = {__float_as_uint(v[e]) & 0xffff0000u, 0u, 0u};
+        if (fabsf(v[e]) == INFINITY) {
+          t[2] = t[0];
+          t[0] = (t[0] & 0x80000000u) | 0x3f800000u;
+        } else if (fabsf(v[e]) >= 0x1.ffp127f) {
+          const float r = v[e] - __uint_as_float(t[0]);
+          t[1] = __float_as_uint(r) & 0xffff0000u;
+          t[2] = __float_as_uint(r - __uint_as_float(t[1]));
+        } else {
+          continue;
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          w[p][e / 2] = e & 1 ? (w[p][e / 2] & 0xffffu) | (t[p] & 0xffff0000u) : (w[p][e / 2] & 0xffff0000u) | t[p] >> 16;
+      }
     }
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-      o[p] = make_uint2((w[p][0] >> 16) | (w[p][1] & 0xffff0000u), (w[p][2] >> 16) | (w[p][3] & 0xffff0000u));
+    for (int p = 0; p < 3; ++p) o[p] = make_uint2(w[p][0], w[p][1]);
   }
 }
 
