@@ -177,7 +177,12 @@ int nnc_eval_hess_lag(nnc_ctx ctx, int net, int B, const double* x, double obj_f
  *   3.2 and Eq. 2: the Newton system needs all three). Each of g, J, H may be
  *   NULL to skip it (at least one must be given); y is used only with g and
  *   lambda only with H (then required). Outputs are the same bits as the
- *   separate calls. Buffers and shapes as for the separate calls.
+ *   separate calls' at the same points, but for two that agree to rounding:
+ *   J of an FP32 network with 64 outputs at one point (rows beside the adjoint
+ *   here, matrix products alone), and H of a BF16 network beside J of 64 rows
+ *   (B * m) or more (diag(s) T from the FP32 accumulators, where
+ *   nnc_eval_hess_lag may take it from the stored BF16 T). Buffers and shapes as
+ *   for the separate calls.
  * Errors: NNC_E_ARG (no output, or H without lambda), NNC_E_SHAPE, NNC_E_HIP,
  *   NNC_E_NONFINITE (debug checks). */
 int nnc_eval(nnc_ctx ctx, int net, int B, const double* x, const double* y, double obj_factor,

@@ -1405,10 +1405,12 @@ hipError_t launch_adj_seed(const double* lam, const double* zL, int act, int B, 
 // chain of loads down a column of W_L, so a workgroup's four waves take every
 // fourth row of its 64 columns each (sums added in wave order; 37 outputs beside
 // the sweep of 4000-wide layers: 43 -> 12 us; 10 of 64-wide ones: 5.2 -> 4.2).
-template <typename OT>
+// SMSEED: Jacobian seeds of a SoftMax output, which need W_L's columns whole.
+template <typename OT, bool SMSEED>
 __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
   __shared__ double zb[kRevSeedRows], p[kRevSeedRows];
-  __shared__ double red[2][4][64];
+  __shared__ double red[4][64];
+  __shared__ double wall[SMSEED ? kRevSeedRows : 1][64];
   const int tid = threadIdx.x;
   const bool softmax = a.act == ACT_SOFTMAX;
   if (tid < a.m) p[tid] = a.dL[tid];
@@ -1442,7 +1444,7 @@ __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
   const int k = blockIdx.x * 64 + lane;  // Kp is a multiple of 64
   const bool in = k < a.K;
   double w[kRevSeedRows / 4];
-  double abar = 0.0, wbar = 0.0;
+  double abar = 0.0;
 #pragma unroll
   for (int t = 0; t < kRevSeedRows / 4; ++t) {
     const int i = wave + 4 * t;
@@ -1451,16 +1453,14 @@ __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
 #pragma unroll
   for (int t = 0; t < kRevSeedRows / 4; ++t) {
     const int i = wave + 4 * t;
-    if (i < a.m) {
-      abar = fma(w[t], zb[i], abar);
-      if (softmax) wbar += p[i] * w[t];
-    }
+    if (i < a.m) abar = fma(w[t], zb[i], abar);
+    if constexpr (SMSEED)
+      if (i < a.m) wall[i][lane] = w[t];
   }
-  red[0][wave][lane] = abar;
-  red[1][wave][lane] = wbar;
+  red[wave][lane] = abar;
   __syncthreads();
   if (wave == 0) {
-    abar = ((red[0][0][lane] + red[0][1][lane]) + red[0][2][lane]) + red[0][3][lane];
+    abar = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     double z = 0.0, s2 = 0.0;
     if (in) {
       const ActVal av = act_eval(a.actp, a.zp[k]);
@@ -1471,7 +1471,9 @@ __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
     a.sp[k] = s2;
   }
   if (!a.R) return;
-  wbar = ((red[1][0][lane] + red[1][1][lane]) + red[1][2][lane]) + red[1][3][lane];
+  double wbar = 0.0;  // summed row by row, as jac_seed_kernel does: the same seeds to the last bit
+  if constexpr (SMSEED)
+    for (int j = 0; j < a.m; ++j) wbar = fma(p[j], wall[j][lane], wbar);
   const double d = in ? (double)((const OT*)a.d1p)[k] : 0.0;
 #pragma unroll
   for (int t = 0; t < kRevSeedRows / 4; ++t) {
@@ -1479,7 +1481,7 @@ __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
     if (i >= a.m) break;
     double v = 0.0;
     if (in) {
-      v = softmax ? p[i] * (w[t] - wbar) : p[i] * w[t];
+      v = SMSEED ? p[i] * (w[t] - wbar) : p[i] * w[t];
       v *= d;
     }
     ((OT*)a.R)[(long long)i * a.Kp + k] = (OT)v;
@@ -1489,10 +1491,18 @@ __global__ void __launch_bounds__(256) reverse_seed_kernel(RevSeedArgs a) {
 hipError_t launch_reverse_seed(DType at, const RevSeedArgs& a, hipStream_t s) {
   if (a.m < 1 || a.m > kRevSeedRows || a.Kp % 64 != 0) return hipErrorInvalidValue;
   const dim3 grid(a.Kp / 64);
-  if (at == DT_F64)
-    hipLaunchKernelGGL(reverse_seed_kernel<double>, grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(reverse_seed_kernel<float>, grid, dim3(256), 0, s, a);
+  const bool smseed = a.act == ACT_SOFTMAX && a.R;
+  if (at == DT_F64) {
+    if (smseed)
+      hipLaunchKernelGGL((reverse_seed_kernel<double, true>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((reverse_seed_kernel<double, false>), grid, dim3(256), 0, s, a);
+  } else {
+    if (smseed)
+      hipLaunchKernelGGL((reverse_seed_kernel<float, true>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((reverse_seed_kernel<float, false>), grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -1582,7 +1592,7 @@ __global__ void jac_seed_kernel(const double* WL, int m, int kcount, int ldw, co
     if (softmax) {
       // row mi of (diag(p) - p p^T) W_L: p_mi (W_L[mi][k] - sum_j p_j W_L[j][k])
       double wbar = 0.0;
-      for (int j = 0; j < m; ++j) wbar += pb[j] * WL[(long long)j * ldw + k];
+      for (int j = 0; j < m; ++j) wbar = fma(pb[j], WL[(long long)j * ldw + k], wbar);
       v = pb[mi] * (WL[(long long)mi * ldw + k] - wbar);
     } else {
       v = pb[mi] * WL[(long long)mi * ldw + k];
