@@ -199,9 +199,13 @@ int size_part(Ctx* c, Net* net) {
       if (ks > 1) need = std::max(need, (size_t)ks * p.g.M * p.g.N * part_size(net));
     }
   }
-  // Jacobian GEMMs of few tiles (fill_ksplit): 8 slices of fewer than 128 tiles
-  if ((long long)net->maxB * net->m >= 64 && net->ct == net->at)
-    need = std::max<size_t>(need, (size_t)8 * kFillTiles * 64 * 64 * part_size(net));
+  // Products of few tiles (fill_ksplit): 8 slices of the largest with fewer than
+  // 128 tiles.  Reserved for every network, so that whether a product is split
+  // depends on the product alone, not on max_points or on earlier tuning.
+  size_t widest = 0;
+  for (const Layer& ly : net->ly) widest = std::max<size_t>(widest, std::max(ly.dinp, ly.doutp));
+  const size_t rows = (size_t)net->maxB * std::max(net->n, net->m);
+  need = std::max(need, 8 * std::min<size_t>(rows * widest, (size_t)kFillTiles * 64 * 64) * part_size(net));
   if (net->pk_bufs)
     for (int B = 1; B <= net->maxB; ++B)
       for (int l = 1; l < net->Lt; ++l) {
@@ -386,11 +390,12 @@ void update_pk(Ctx* c, Net* net, bool allow) {
             c->forced_ksplit[net->ct] < 1;
 }
 
-// K slices of a product without a row in the tuned table: a few 64 x 64 tiles
+// K slices of a row-major product without a row in the tuned table: a few 64 x 64 tiles
 // run their K tiles one after the other on a few CUs, so below 128 tiles K is
 // split until there are about 256 workgroups, every slice keeping 128 elements
 // or more.  (70 Jacobian rows of the 784-1000-500-250-10 classifier, FP32: three
-// products 56 -> 33 us with their reductions.)
+// products 56 -> 33 us with their reductions.)  size_part reserves the most this
+// can ask for.
 int fill_ksplit(const GemmArgs& g) {
   const long long tiles = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64);
   if (tiles >= kFillTiles) return 1;
@@ -413,7 +418,11 @@ int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kin
   if (!acc64 && c->forced_ksplit[net->ct] >= 1) ks = c->forced_ksplit[net->ct];
   if (cfg < 0 || !gemm_cfg_supports(net->ct, cfg, acc64)) {
     cfg = pick_cfg(net, g.M, g.N, acc64);
-    if (ks == 1 && c->forced_ksplit[net->ct] < 1) ks = fill_ksplit(g);
+    if (ks == 1 && c->forced_ksplit[net->ct] < 1 && ksplit_ok(net, g, acc64, splits)) {
+      ks = fill_ksplit(g);
+      if ((size_t)ks * g.M * g.N * part_size(net) > net->part_bytes && ks > 1)
+        return fail(c, NNC_E_HIP, "K-split workspace smaller than planned");
+    }
   }
   NNC_LAUNCH(c, kind, launch_gemm_ks(net, g, acc64, splits, cfg, ks, c->stream));
   return NNC_OK;
