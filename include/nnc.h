@@ -147,8 +147,10 @@ int nnc_eval_g(nnc_ctx ctx, int net, int B, const double* x, const double* y, do
  *   that forbid hipMalloc).  Same arguments, kernels and bits as
  *   nnc_eval_g; the forward pass's per-point vectors (staged input, z_l,
  *   a_l, sigma'_l of every layer) live in a fixed 64 MiB device array that
- *   the library holds on each GPU from load to process exit instead of in
- *   the network's buffers, and the call allocates and frees nothing.  Every
+ *   the library holds on each GPU from load to process exit (16 MiB behind it
+ *   take partial sums) instead of in the network's buffers, so other calls on
+ *   the network may be under way on another stream, and the call allocates
+ *   and frees nothing.  Every
  *   vector is written before it is read, so nothing needs clearing; the
  *   array keeps the last call's contents.  All calls on one GPU share that
  *   array: calls that overlap on one GPU (several streams or host threads)

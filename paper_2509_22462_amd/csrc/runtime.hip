@@ -522,11 +522,14 @@ bool reverse_fusable(const Net* net, int B) {
 }
 
 
-// Per-point vectors the forward pass writes: the staged input [B][np] and,
-// per layer l, z_l (FP64), a_l and sigma'_l ([B][d_l'] each; sigma'_L in
-// FP64).  The network's own buffers, or a caller-provided carve-up.
+// What the forward pass writes: the staged input [B][np], per layer l z_l
+// (FP64), a_l and sigma'_l ([B][d_l'] each; sigma'_L in FP64), and the partial
+// sums of its weight streams' K slices.  The network's own buffers, or a
+// caller-provided carve-up.
 struct FwdBufs {
   void* xin = nullptr;
+  void* part = nullptr;
+  long long part_elems = 0;  // (of activations' type)
   std::vector<double*> z;
   std::vector<void*> a, d1;
 };
@@ -534,6 +537,8 @@ struct FwdBufs {
 FwdBufs net_fwd_bufs(Net* net) {
   FwdBufs f;
   f.xin = net->xin;
+  f.part = net->at == DT_F64 ? (void*)net->spart64 : (void*)net->spart;
+  f.part_elems = net->at == DT_F64 ? net->spart64_elems : net->spart_elems;
   for (Layer& ly : net->ly) {
     f.z.push_back(ly.z);
     f.a.push_back(ly.a);
@@ -569,8 +574,8 @@ int run_forward_bufs(Ctx* c, Net* net, int B, const double* x, const double* y, 
       continue;
     }
     SkinnyArgs a = skinny_args(ly.W, ly.dinp, ly.doutp, ly.dinp, X, ly.dinp, B, SK_PRIMAL);
-    a.part = net->at == DT_F64 ? (void*)net->spart64 : (void*)net->spart;
-    a.part_elems = net->at == DT_F64 ? net->spart64_elems : net->spart_elems;
+    a.part = fb.part;
+    a.part_elems = fb.part_elems;
     a.dtrue = ly.dout;
     a.act = ly.act;
     a.bias = ly.b;
@@ -1150,9 +1155,12 @@ int run_hess_overlapped(Ctx* c, Net* net, int B, const double* x, const double* 
 // a kernel (on the host it is only a stand-in symbol): its device address
 // is looked up once per device, with that device current, when a context
 // is created there, and kept per device.
+// Behind the vectors come the partial sums of the weight streams: at most 64
+// rows x 256 workgroups of 128 outputs, in FP64.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+constexpr size_t kStaticPartBytes = (size_t)64 * 256 * 128 * 8;
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticPartBytes];
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1509,6 +1517,11 @@ int nnc_eval_g_static(nnc_ctx ctx, int id, int B, const double* x, const double*
                                     " bytes of forward-pass vectors, above the 64 MiB static workspace");
   FwdBufs fb;
   carve_fwd_bufs(net, B, (char*)c->scratch, &fb);
+  // not the network's: another call on it may be under way on another stream.
+  // The same number of slices, so the same bits, as nnc_eval_g.
+  const FwdBufs own = net_fwd_bufs(net);
+  fb.part = (char*)c->scratch + kStaticScratchBytes;
+  fb.part_elems = std::min(own.part_elems, (long long)(kStaticPartBytes / net->asz));
   return run_forward_bufs(c, net, B, x, y, g, fb);
 }
 
