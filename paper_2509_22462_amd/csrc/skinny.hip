@@ -187,6 +187,20 @@ __global__ void __launch_bounds__(KSPLIT * 64) skinny_ksplit_kernel(SkinnyArgs a
 // scattered over the lanes while they are reduced (halving what each lane
 // keeps at every step), then added over the waves in wave order.  21 points, 10
 // outputs of 4,096 elements: 57.7 -> 12.1 us.
+// It reads W_L once per 4 points, where the stream reads it once per 64, so the
+// stream keeps the output layers that fill the chip with it, and the shortest
+// sums, which leave most of the 256 threads idle (whole call, one hidden layer
+// of K, stream / this: K = 64, 10 outputs 16 points 7.9 / 8.8 us, 32 points 8.9 /
+// 8.3; K = 512, 512 outputs 63 points 1.44 in its favour; 3,072 outputs 5 points
+// 0.94; K = 4,096, 4,096 outputs 16 points 53 / 85 us, 1,536 outputs 12 points
+// 1.17 in its favour).
+inline bool skinny_out_pays(int rows, int N, int K) {
+  if (rows <= 4) return false;
+  if (K < 128) return rows > 16 && N <= 256;
+  if (N <= 512 || (N <= 1024 && K >= 512)) return true;
+  return (long long)((rows + 3) / 4) * ((N + 7) / 8) <= (K >= 2048 ? 768 : 512);
+}
+
 template <typename TX>
 __global__ void __launch_bounds__(256) skinny_out_kernel(SkinnyArgs a) {
   constexpr int R = 4, JO = 8;
@@ -968,7 +982,7 @@ static hipError_t skinny_launch_r(SkinnyArgs a, hipStream_t s) {
 template <typename TW, typename TX, typename A>
 static hipError_t skinny_launch(SkinnyArgs a, hipStream_t s) {
   if constexpr (std::is_same<TW, double>::value) {
-    if (a.epi == SK_OUT && a.rows > 4) {
+    if (a.epi == SK_OUT && skinny_out_pays(a.rows, a.N, a.K)) {
       hipLaunchKernelGGL(skinny_out_kernel<TX>, dim3((a.rows + 3) / 4, (a.N + 7) / 8), dim3(256), 0, s, a);
       return hipGetLastError();
     }
