@@ -324,7 +324,8 @@ int nnc_profile_classes(nnc_ctx ctx, int class_mask);
  *     B <= batch.
  *   nnc_train_get/set_params: copy the FP32 master parameters to/from a
  *     HOST FP64 buffer laid out W_1, b_1, W_2, b_2, ... (row-major);
- *     set_params also restarts Adam (moments and step count to zero).
+ *     set_params also restarts Adam (moments and step count to zero).  A
+ *     trainer holds up to 32 MiB of pinned host memory for these copies.
  *   nnc_train_get_grads: the loss gradient of the last nnc_train_step (taken
  *     at the parameters before its update), same HOST layout. */
 int nnc_train_create(nnc_ctx ctx, int L, const int* dims, int batch, int prec,

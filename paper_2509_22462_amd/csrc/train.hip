@@ -21,6 +21,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <random>
 #include <string>
 #include <vector>
@@ -45,6 +46,10 @@ struct TrLayer {
   int tile0;       // first tile of the layer
 };
 
+// Most pinned host memory a trainer keeps.  Above it a copy's waits are a small
+// part of its time.
+constexpr size_t kStagingBytes = (size_t)32 << 20;
+
 struct Trainer {
   bool small = false;         // tr_mm_kernel / tr_wgrad_kernel path
   TrLayer* dlayers = nullptr;  // device table of the grouped launch
@@ -64,7 +69,8 @@ struct Trainer {
   int npartial = 0;
   int step = 0;
   // pinned host copy of one set of parameters or gradients as laid out on the
-  // device, for nnc_train_get_params / _get_grads (NULL: pageable copies)
+  // device, for nnc_train_get_params / _get_grads (NULL: pageable copies, also
+  // where it would be larger than kStagingBytes)
   float* staging = nullptr;
   std::vector<void*> allocs;
 };
@@ -741,7 +747,8 @@ int nnc_train_create(nnc_ctx ctx, int L, const int* dims, int batch, int prec,
   t->dlayers = (TrLayer*)A(sizeof(TrLayer) * L);
   size_t words = 0;
   for (int l = 1; l <= L; ++l) words += ((size_t)t->dp[l - 1] + 1) * t->dp[l];
-  if (hipHostMalloc((void**)&t->staging, words * 4, hipHostMallocDefault) != hipSuccess) {
+  if (words * 4 <= kStagingBytes &&
+      hipHostMalloc((void**)&t->staging, words * 4, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     t->staging = nullptr;
   }
@@ -846,36 +853,43 @@ int nnc_train_num_params(nnc_ctx ctx, int id, long long* count) {
   return NNC_OK;
 }
 
-// Parameters or gradients, unpadded and in FP64, layer by layer.  All copies
-// are queued behind the stream's work into pinned memory and waited for once
-// (a pageable copy per array, each waiting on its own into fresh host memory:
-// 15 steps of the warm-start network and its 1.1M parameters back 1,600 -> 1,380 us).
+// Parameters or gradients, unpadded and in FP64, layer by layer.  With staging
+// all copies are queued behind the stream's work into pinned memory and waited
+// for once (a pageable copy per array, each waiting on its own into fresh host
+// memory: 15 steps of the warm-start network and its 1.1M parameters back
+// 1,600 -> 1,380 us); without, one array at a time.
 static int copy_out(Ctx* c, Trainer* t, double* host, bool grads) {
+  auto unpad = [&](const float* from, int rows, int cols, int ld) {
+    for (int r = 0; r < rows; ++r, host += cols)
+      for (int q = 0; q < cols; ++q) host[q] = from[(size_t)r * ld + q];
+  };
   std::vector<float> pageable;
-  float* buf = t->staging;
-  if (!buf) {
-    size_t words = 0;
-    for (int l = 1; l <= t->L; ++l) words += ((size_t)t->dp[l - 1] + 1) * t->dp[l];
-    pageable.resize(words);
-    buf = pageable.data();
-  }
   size_t o = 0;
   for (int l = 1; l <= t->L; ++l) {
-    const size_t cw = (size_t)t->dp[l] * t->dp[l - 1];
-    TR_HIP(c, hipMemcpyAsync(buf + o, grads ? t->dW[l - 1] : t->Wm[l - 1], cw * 4, hipMemcpyDeviceToHost, c->stream));
-    o += cw;
-    TR_HIP(c, hipMemcpyAsync(buf + o, grads ? t->db[l - 1] : t->bm[l - 1], (size_t)t->dp[l] * 4, hipMemcpyDeviceToHost,
-                             c->stream));
-    o += t->dp[l];
+    const size_t cw = (size_t)t->dp[l] * t->dp[l - 1], cb = t->dp[l];
+    const float* w = grads ? t->dW[l - 1] : t->Wm[l - 1];
+    const float* b = grads ? t->db[l - 1] : t->bm[l - 1];
+    if (t->staging) {
+      TR_HIP(c, hipMemcpyAsync(t->staging + o, w, cw * 4, hipMemcpyDeviceToHost, c->stream));
+      TR_HIP(c, hipMemcpyAsync(t->staging + o + cw, b, cb * 4, hipMemcpyDeviceToHost, c->stream));
+      o += cw + cb;
+      continue;
+    }
+    pageable.resize(std::max(pageable.size(), std::max(cw, cb)));
+    if (l == 1) TR_HIP(c, hipStreamSynchronize(c->stream));
+    TR_HIP(c, hipMemcpy(pageable.data(), w, cw * 4, hipMemcpyDeviceToHost));
+    unpad(pageable.data(), t->d[l], t->d[l - 1], t->dp[l - 1]);
+    TR_HIP(c, hipMemcpy(pageable.data(), b, cb * 4, hipMemcpyDeviceToHost));
+    unpad(pageable.data(), 1, t->d[l], t->dp[l]);
   }
+  if (!t->staging) return NNC_OK;
   TR_HIP(c, hipStreamSynchronize(c->stream));
+  const float* from = t->staging;
   for (int l = 1; l <= t->L; ++l) {
-    const int rows = t->d[l], cols = t->d[l - 1], ld = t->dp[l - 1];
-    for (int r = 0; r < rows; ++r, host += cols)
-      for (int q = 0; q < cols; ++q) host[q] = buf[(size_t)r * ld + q];
-    buf += (size_t)t->dp[l] * ld;
-    for (int r = 0; r < rows; ++r) *host++ = buf[r];
-    buf += t->dp[l];
+    unpad(from, t->d[l], t->d[l - 1], t->dp[l - 1]);
+    from += (size_t)t->dp[l] * t->dp[l - 1];
+    unpad(from, 1, t->d[l], t->dp[l]);
+    from += t->dp[l];
   }
   return NNC_OK;
 }
