@@ -95,8 +95,11 @@ const char* nnc_last_error(nnc_ctx ctx);
  *   prec        enum nnc_prec of the bulk GEMMs.
  *   max_points  largest point count B any eval call on this net will use;
  *               the tangent workspace (about B*n*sum(d_l)*2 elements; FP32
- *               layer-sum networks hold one and a half times that, and their
- *               hidden weights once more at 6 bytes each) is allocated here.
+ *               layer-sum networks hold one and a half times that for P_l and
+ *               U_l) is allocated here.  Layer-sum networks also hold their
+ *               hidden weights once more, packed (2, 6 or 8 bytes each in BF16,
+ *               FP32 or FP64).  Where the packed forms do not fit, the sweep
+ *               runs on row-major operands and they are not held.
  *               From 64 points on, calls run the primal pass and the FP64
  *               adjoint as MFMA GEMMs, so a net created with max_points >= 64
  *               also holds FP64 copies of its hidden layers' transposed weights

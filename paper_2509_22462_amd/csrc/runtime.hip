@@ -64,16 +64,32 @@ int fail(Ctx* c, int code, const std::string& msg) {
   return code;
 }
 
+// hipMalloc, or NULL with no error left for the next launch's check to find.
+void* try_malloc(size_t bytes) {
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
 void* dalloc(Net* net, size_t bytes) {
   if (bytes == 0) bytes = 16;
-  void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+  void* p = try_malloc(bytes);
+  if (!p) return nullptr;
   if (hipMemset(p, 0, bytes) != hipSuccess) {
     hipFree(p);
     return nullptr;
   }
   net->allocs.push_back(p);
   return p;
+}
+
+// Frees one of the network's allocations (NULL: nothing).
+void release(Net* net, void* p) {
+  if (!p) return;
+  net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), p));
+  (void)hipDeviceSynchronize();
+  hipFree(p);
 }
 
 void free_net(Net* net) {
@@ -168,8 +184,8 @@ int ensure_part(Ctx* c, Net* net, size_t bytes) {
     net->part = nullptr;
     net->part_bytes = 0;
   }
-  void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) return fail(c, NNC_E_NOMEM, "K-split workspace");
+  void* p = try_malloc(bytes);
+  if (!p) return fail(c, NNC_E_NOMEM, "K-split workspace");
   net->part = p;
   net->part_bytes = bytes;
   return NNC_OK;
@@ -280,77 +296,86 @@ bool pk_wanted(const Net* net) {
   return net->Lt >= 2 && widest >= 6;
 }
 
-// Workspace of Hessian method `method` (network creation, or a method change:
-// plan time only).
-int ensure_hess_bufs(Ctx* c, Net* net, int method) {
+// The packed operands: weights, P_l large enough for the packed form as well,
+// and but for BF16 U in the place of S with its signs.  All or none.
+bool alloc_packed(Ctx* c, Net* net) {
+  const size_t N = (size_t)net->maxB * net->n;
+  const int Lt = net->Lt;
+  std::vector<void*> got;
+  auto G = [&](size_t bytes) -> void* {
+    void* p = try_malloc(bytes);
+    if (p) got.push_back(p);
+    return p;
+  };
+  std::vector<void*> P(Lt, nullptr), W(Lt + 1, nullptr);
+  bool have = true;
+  for (int l = 1; have && l < Lt; ++l) {
+    const Layer& nx = net->ly[l];
+    P[l] = G(std::max(N * nx.dinp * net->csz, pk_operand_bytes(net->ct, (long long)N, nx.dinp)));
+    W[l + 1] = P[l] ? G(pk_operand_bytes(net->ct, nx.doutp, nx.dinp)) : nullptr;
+    have = W[l + 1] != nullptr;
+  }
+  void *U = nullptr, *sgn = nullptr;
+  if (have && net->ct != DT_BF16) {
+    U = G(std::max(N * net->Ktot * net->csz, pk_u_bytes(net->ct, net->n, net->maxB, net->Ktot)));
+    sgn = U ? G((size_t)net->maxB * net->Ktot * (net->ct == DT_F64 ? 8 : 2)) : nullptr;
+    have = sgn != nullptr;
+  }
+  if (!have) {
+    for (void* p : got) hipFree(p);
+    return false;
+  }
+  free_batch(c);
+  for (int l = 1; l < Lt; ++l) {
+    release(net, net->P[l]);  // the smaller buffer of the other method
+    net->P[l] = P[l];
+    net->ly[l].Wk = W[l + 1];
+  }
+  net->SC = U;
+  net->sgn = sgn;
+  net->allocs.insert(net->allocs.end(), got.begin(), got.end());
+  net->pk_bufs = true;
+  return true;
+}
+
+// Gives the packed operands back: what follows them in a set-up did not fit.
+// The row-major buffers that take their place are smaller.
+void drop_packed(Ctx* c, Net* net) {
+  free_batch(c);
+  for (int l = 1; l < net->Lt; ++l) {
+    release(net, net->P[l]);
+    release(net, net->ly[l].Wk);
+    net->P[l] = net->ly[l].Wk = nullptr;
+  }
+  if (net->ct != DT_BF16) {
+    release(net, net->SC);
+    release(net, net->sgn);
+    net->SC = net->sgn = nullptr;
+  }
+  net->pk_bufs = net->pk = false;
+  net->ls_bufs = false;  // (alloc_hess_bufs fills in what is missing)
+}
+
+// What method `method` needs beside packed operands.
+int alloc_hess_bufs(Ctx* c, Net* net, int method) {
   const size_t N = (size_t)net->maxB * net->n;
   const int Lt = net->Lt;
   bool ok = true;
-  auto A = [&](size_t bytes) {
-    void* p = dalloc(net, bytes);
-    if (!p) ok = false;
-    return p;
+  auto A = [&](auto*& p, size_t bytes) {
+    if (!p && !(p = (std::remove_reference_t<decltype(p)>)dalloc(net, bytes))) ok = false;
   };
-  // Packed operands: weights, P_l large enough for the packed form as well, and
-  // U in the place of S with its signs.  Without the memory for them the sweep
-  // stays on the row-major operands below.
-  if (method == NNC_HESS_LAYERSUM && !net->ls_bufs && pk_wanted(net)) {
-    std::vector<void*> got;
-    auto G = [&](size_t bytes) -> void* {
-      void* p = nullptr;
-      if (hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-      }
-      got.push_back(p);
-      return p;
-    };
-    std::vector<void*> P(Lt, nullptr), W(Lt + 1, nullptr);
-    bool have = true;
-    for (int l = 1; have && l < Lt; ++l) {
-      const Layer& nx = net->ly[l];
-      P[l] = G(std::max(N * nx.dinp * net->csz, pk_operand_bytes(net->ct, (long long)N, nx.dinp)));
-      W[l + 1] = P[l] ? G(pk_operand_bytes(net->ct, nx.doutp, nx.dinp)) : nullptr;
-      have = W[l + 1] != nullptr;
-    }
-    void *U = nullptr, *sgn = nullptr;
-    if (have && net->ct != DT_BF16) {
-      U = G(std::max(N * net->Ktot * net->csz, pk_u_bytes(net->ct, net->n, net->maxB, net->Ktot)));
-      sgn = U ? G((size_t)net->maxB * net->Ktot * (net->ct == DT_F64 ? 8 : 2)) : nullptr;
-      have = sgn != nullptr;
-    }
-    if (have) {
-      net->SC = U;
-      net->sgn = sgn;
-      for (int l = 1; l < Lt; ++l) {
-        if (net->P[l]) {  // the smaller buffer of the other method
-          free_batch(c);
-          NNC_HIP(c, hipDeviceSynchronize());
-          net->allocs.erase(std::find(net->allocs.begin(), net->allocs.end(), net->P[l]));
-          hipFree(net->P[l]);
-        }
-        net->P[l] = P[l];
-        net->ly[l].Wk = W[l + 1];
-      }
-      net->allocs.insert(net->allocs.end(), got.begin(), got.end());
-      net->pk_bufs = true;
-    } else {
-      for (void* p : got) hipFree(p);
-    }
-  }
-  if (Lt >= 2 && !net->P[1])
-    for (int l = 1; l <= Lt - 1; ++l) net->P[l] = A(N * net->ly[l - 1].doutp * net->csz);
+  for (int l = 1; l <= Lt - 1; ++l) A(net->P[l], N * net->ly[l - 1].doutp * net->csz);
   if (method == NNC_HESS_FOR && !net->for_bufs) {
-    for (int l = 2; l <= Lt - 1; ++l) net->T[l] = A(N * net->ly[l - 1].doutp * net->csz);
-    if (Lt >= 1) net->Glast = A(N * net->ly[Lt - 1].doutp * net->csz);
-    net->for_bufs = true;
+    for (int l = 2; l <= Lt - 1; ++l) A(net->T[l], N * net->ly[l - 1].doutp * net->csz);
+    if (Lt >= 1) A(net->Glast, N * net->ly[Lt - 1].doutp * net->csz);
+    net->for_bufs = ok;
   }
   if (method == NNC_HESS_LAYERSUM && !net->ls_bufs) {
     if (Lt >= 1) {
-      net->TC = A(N * net->Ktot * net->csz);
-      if (!net->SC) net->SC = A(N * net->Ktot * net->csz);
+      A(net->TC, N * net->Ktot * net->csz);
+      A(net->SC, N * net->Ktot * net->csz);
     }
-    net->ls_bufs = true;
+    net->ls_bufs = ok;
   }
   if (!ok) return fail(c, NNC_E_NOMEM, "Hessian workspace");
   const size_t need = std::max<size_t>(hpart_need(net), 16);
@@ -362,12 +387,23 @@ int ensure_hess_bufs(Ctx* c, Net* net, int method) {
       net->Hpart = nullptr;
       net->hpart_bytes = 0;
     }
-    void* p = nullptr;
-    if (hipMalloc(&p, need) != hipSuccess) return fail(c, NNC_E_NOMEM, "Hessian partials");
+    void* p = try_malloc(need);
+    if (!p) return fail(c, NNC_E_NOMEM, "Hessian partials");
     net->Hpart = (double*)p;
     net->hpart_bytes = need;
   }
   return NNC_OK;
+}
+
+// Workspace of Hessian method `method` (network creation, or a method change:
+// plan time only).  Without the memory for packed operands and for what has to
+// stand beside them the sweep stays on row-major operands.
+int ensure_hess_bufs(Ctx* c, Net* net, int method) {
+  const bool packed = method == NNC_HESS_LAYERSUM && !net->ls_bufs && pk_wanted(net) && alloc_packed(c, net);
+  const int rc = alloc_hess_bufs(c, net, method);
+  if (rc != NNC_E_NOMEM || !packed) return rc;
+  drop_packed(c, net);
+  return alloc_hess_bufs(c, net, method);
 }
 
 // The packed weights, once the row-major ones are in place (network creation
@@ -400,6 +436,18 @@ int fill_ksplit(const GemmArgs& g) {
   const long long tiles = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64);
   if (tiles >= kFillTiles) return 1;
   return (int)std::max<long long>(1, std::min<long long>({8, 256 / tiles, g.K / 128}));
+}
+
+// The last of a set-up: packed weights, the choice of operands and the K-split
+// workspace, on row-major operands where that does not fit beside packed ones.
+int finish_setup(Ctx* c, Net* net) {
+  NNC_TRY(pack_weights(c, net));
+  update_pk(c, net, true);
+  const int rc = size_part(c, net);
+  if (rc != NNC_E_NOMEM || !net->pk_bufs) return rc;
+  drop_packed(c, net);
+  NNC_TRY(alloc_hess_bufs(c, net, NNC_HESS_LAYERSUM));
+  return size_part(c, net);
 }
 
 int gemm(Ctx* c, Net* net, int slot, GemmArgs g, bool acc64, int splits, int kind = NNC_KC_GEMM) {
@@ -814,6 +862,14 @@ int run_adjoint(Ctx* c, Net* net, int B, const double* lam) {
   return NNC_OK;
 }
 
+// Whether the method's buffers are there (a change of method that ran out of
+// memory may have left some of them missing).
+bool tangent_bufs_ok(const Net* net) {
+  for (int l = 1; l < net->Lt; ++l)
+    if (!net->P[l]) return false;
+  return net->Hpart && (net->hess_method == NNC_HESS_LAYERSUM ? net->ls_bufs : net->for_bufs);
+}
+
 // a6 + a7: the GEMMs of the forward- and reverse-tangent sweeps and of H,
 // as argument blocks (phase 0 forward, 1 reverse, 2 H; idx = step in phase).
 // Layer sum: the forward sweep writes T_l and S_l = diag(s_l) T_l of every
@@ -824,6 +880,7 @@ int run_adjoint(Ctx* c, Net* net, int B, const double* lam) {
 // the finalize kernel adds in order.  defer_s: the sweep writes T_l and P_l
 // only (it then needs no adjoint) and S is formed afterwards.
 int plan_layersum(Net* net, int B, std::vector<PlannedGemm>& out, bool defer_s = false) {
+  if (!tangent_bufs_ok(net)) return NNC_E_NOMEM;
   out.clear();
   const int n = net->n, Lt = net->Lt;
   const int N = B * n;
@@ -888,6 +945,7 @@ int plan_layersum(Net* net, int B, std::vector<PlannedGemm>& out, bool defer_s =
 }
 
 int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out) {
+  if (!tangent_bufs_ok(net)) return NNC_E_NOMEM;
   if (net->hess_method == NNC_HESS_LAYERSUM) return plan_layersum(net, B, out);
   out.clear();
   const int n = net->n, Lt = net->Lt;
@@ -1374,9 +1432,12 @@ int nnc_net_create(nnc_ctx ctx, int L, const int* dims, const int* acts, const d
   // Upload and convert the weights (FP64 host -> padded compute-type copies).
   size_t maxw = 0;
   for (int l = 1; l <= L; ++l) maxw = std::max(maxw, (size_t)dims[l] * dims[l - 1]);
-  double* tmp = nullptr;
-  hipError_t e = hipMalloc(&tmp, maxw * 8);
-  if (e != hipSuccess) {
+  double* tmp = (double*)try_malloc(maxw * 8);
+  if (!tmp && net->pk_bufs) {
+    drop_packed(c, net);
+    if (alloc_hess_bufs(c, net, net->hess_method) == NNC_OK) tmp = (double*)try_malloc(maxw * 8);
+  }
+  if (!tmp) {
     free_net(net);
     return fail(c, NNC_E_NOMEM, "device allocation failed (weight staging)");
   }
@@ -1412,9 +1473,7 @@ int nnc_net_create(nnc_ctx ctx, int L, const int* dims, const int* acts, const d
     if (hipDeviceSynchronize() != hipSuccess) rc = fail(c, NNC_E_HIP, "weight conversion failed");
   }
   hipFree(tmp);
-  if (rc == NNC_OK) rc = pack_weights(c, net);
-  update_pk(c, net, true);
-  if (rc == NNC_OK) rc = size_part(c, net);  // K-split workspace of the sweep's products
+  if (rc == NNC_OK) rc = finish_setup(c, net);
   if (rc != NNC_OK) {
     free_net(net);
     return rc;
@@ -1470,10 +1529,8 @@ int nnc_net_set_hess_method(nnc_ctx ctx, int id, int method) {
   NNC_TRY(ensure_hess_bufs(c, net, m));
   if (m != net->hess_method) {
     free_batch(c);  // batched launches are planned per method
-    NNC_TRY(pack_weights(c, net));
     net->hess_method = m;
-    update_pk(c, net, true);
-    NNC_TRY(size_part(c, net));
+    NNC_TRY(finish_setup(c, net));
   }
   return NNC_OK;
 }
