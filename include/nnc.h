@@ -253,11 +253,11 @@ int nnc_eval_batch(nnc_ctx ctx, int njobs, const nnc_job* jobs);
 
 /* nnc_autotune: time every candidate GEMM tiling on each tangent-sweep GEMM
  * shape of this net at B points (synthetic inputs x = 0.5, lambda = 1; HIP
- * events, 3 launches each), keep the fastest per shape in the context's
- * tuning table (used by the row-major kernels: forward-over-reverse sweeps,
- * and layer-sum networks without the packed workspace), and append the
- * choices as JSON lines to the file named by NNC_AUTOTUNE_CACHE when set (read
- * back by nnc_create).  A set-up call: it allocates temporary device buffers
+ * events), keep the fastest per shape in the context's tuning table, and
+ * append the choices as JSON lines to the file named by NNC_AUTOTUNE_CACHE
+ * when set (read back by nnc_create).  What is timed is what the net runs:
+ * the packed products of a layer sum (rows of acc64 = splits = 0), else the
+ * row-major ones.  A set-up call: it allocates temporary device buffers
  * and blocks until done; it overwrites the net's sweep workspace (the next
  * eval recomputes everything).
  * nnc_autotune_query: the tuned configuration id of one GEMM shape

@@ -129,12 +129,13 @@ int build_launches(Ctx* c, const std::vector<Net*>& nets, const nnc_job* jobs, i
     if (!acc64 && c->forced_cfg[ct] >= 0 && gemm_grouped_supports(ct, c->forced_cfg[ct], acc64))
       cfg = c->forced_cfg[ct];
     if (!gemm_grouped_supports(ct, cfg, acc64)) cfg = 3;
-    // packed products: the tiling their largest one would take alone
+    // packed products: the tiling their largest one would take alone, unsplit
     if (pk && !edge) {
       const GemmArgs* big = &groups[0].first;
       for (const auto& gr : groups)
         if ((long long)gr.first.M * gr.first.N * gr.first.K > (long long)big->M * big->N * big->K) big = &gr.first;
-      cfg = pk_choose(ct, big->M, big->N, big->K, 0).cfg;
+      const PkChoice alone = internal_pk_choice(c, ct, *big);
+      cfg = alone.ksplit == 1 ? alone.cfg : pk_choose(ct, big->M, big->N, big->K, 0).cfg;
     }
     // symmetric layer-sum products need square tiles of their own edge
     // (the 64 x 64 tiling also serves any other H product of the launch)
@@ -245,11 +246,13 @@ void load_tune_cache(Ctx* c) {
                "{\"arch\": \"gfx950\", \"dt\": %d, \"M\": %d, \"N\": %d, \"K\": %d, \"acc64\": %d, "
                "\"splits\": %d, \"cfg\": %d",
                &k.dt, &k.M, &k.N, &k.K, &k.acc64, &k.splits, &cfg) == 7 &&
-        cfg >= 0 && cfg < gemm_num_cfgs()) {
+        cfg >= 0 && k.dt >= 0 && k.dt <= 2 && cfg < (k.splits == 0 ? pk_num_cfgs((DType)k.dt) : gemm_num_cfgs())) {
       int ks = 1;  // "ksplit" is optional (absent = unsplit)
       const char* q = strstr(line, "\"ksplit\": ");
       if (q) ks = atoi(q + 10);
       if (ks < 1 || ks > 8) ks = 1;
+      // a packed product's partials stay within their bound
+      if (k.splits == 0 && (size_t)ks * k.M * k.N * (k.dt == DT_F64 ? 8 : 4) > kPkPartBytes) ks = 1;
       c->tuned[k] = TuneVal{cfg, ks};
     }
   }
@@ -400,7 +403,6 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
   B_HIP(c, hipEventCreate(&e1));
   const bool prof = c->prof;
   c->prof = false;
-  internal_update_pk(c, net, false);  // the tilings of the row-major products are what is timed
   rc = nnc_eval_hess_lag(ctx, id, B, dx, 0.0, dl, dH);
   std::vector<PlannedGemm> plan;
   if (!rc) rc = internal_plan_tangents(net, B, plan);
@@ -416,7 +418,10 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
   const int kKs[] = {2, 3, 4, 6};
   size_t part_need = 0;
   for (const PlannedGemm& p : plan)
-    if (internal_ksplit_ok(net, p.g, p.acc64, p.splits))
+    if (p.pk && p.phase == 0) {
+      for (int ks = 2; ks <= 8; ++ks)
+        if ((size_t)ks * p.g.M * p.g.N * psz <= kPkPartBytes) part_need = std::max(part_need, (size_t)ks * p.g.M * p.g.N * psz);
+    } else if (internal_ksplit_ok(net, p.g, p.acc64, p.splits))
       for (int ks : kKs)
         if ((size_t)ks * p.g.M * p.g.N * psz <= kPartCap)
           part_need = std::max(part_need, (size_t)ks * p.g.M * p.g.N * psz);
@@ -424,9 +429,13 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
   for (size_t pi = 0; !rc && pi < plan.size(); ++pi) {
     PlannedGemm& p = plan[pi];
     if (p.g.sym > 0) continue;  // the symmetric layer-sum product has a fixed tiling
-    const TuneKey key{(int)net->ct, p.g.M, p.g.N, p.g.K, (int)p.acc64, p.splits};
+    const bool pk = p.pk;
+    const TuneKey key{(int)net->ct, p.g.M, p.g.N, p.g.K, (int)p.acc64, pk ? 0 : p.splits};
     std::vector<int> kss{1};
-    if (internal_ksplit_ok(net, p.g, p.acc64, p.splits))
+    if (pk) {
+      for (int ks = 2; ks <= 8; ++ks)
+        if ((size_t)ks * p.g.M * p.g.N * psz <= kPkPartBytes) kss.push_back(ks);
+    } else if (internal_ksplit_ok(net, p.g, p.acc64, p.splits))
       for (int ks : kKs)
         if ((size_t)ks * p.g.M * p.g.N * psz <= net->part_bytes) kss.push_back(ks);
     struct Trial {
@@ -439,6 +448,13 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
     // stride ldo; FP64 for the H products) is compared with that of the
     // plain 64 x 64 register-staged tiling on the same inputs; a candidate
     // further than tol from it is never chosen.
+    // (Packed products write T only where it is asked for: for the comparison it is.)
+    auto launch = [&](const GemmArgs& g, int cfg, int ks) -> hipError_t {
+      if (pk) return launch_gemm_pk(net->ct, PkChoice{cfg, ks}, g, net->part, c->stream);
+      return internal_launch_gemm_ks(net, g, p.acc64, p.splits, cfg, ks, c->stream);
+    };
+    GemmArgs shown = p.g;
+    if (!shown.out0) shown.out0 = (char*)net->TC + (size_t)p.g.ucol * net->csz;
     const DType ot = p.acc64 || p.g.epi == EPI_H64 ? DT_F64 : net->ct;
     const size_t osz = ot == DT_F64 ? 8 : net->csz;
     const size_t ref_elems = (size_t)(p.g.M - 1) * p.g.ldo + p.g.N;
@@ -447,17 +463,16 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
     unsigned* dcmp = nullptr;
     bool have_ref = false;
     if (hipMalloc(&ref, ref_elems * osz) == hipSuccess && hipMalloc(&dcmp, 2 * sizeof(unsigned)) == hipSuccess &&
-        gemm_cfg_supports(net->ct, 3, p.acc64)) {
-      GemmArgs g = p.g;
-      have_ref = internal_launch_gemm_ks(net, g, p.acc64, p.splits, 3, 1, c->stream) == hipSuccess &&
-                 hipMemcpyAsync(ref, p.g.out0, ref_elems * osz, hipMemcpyDeviceToDevice, c->stream) == hipSuccess &&
+        (pk || gemm_cfg_supports(net->ct, 3, p.acc64))) {
+      have_ref = launch(shown, 3, 1) == hipSuccess &&
+                 hipMemcpyAsync(ref, shown.out0, ref_elems * osz, hipMemcpyDeviceToDevice, c->stream) == hipSuccess &&
                  hipStreamSynchronize(c->stream) == hipSuccess;
     }
     auto compare = [&]() -> double {  // after a candidate ran: its out0 against the reference
       if (!have_ref) return 0.0;
       unsigned h[2] = {0u, 0u};
       if (hipMemsetAsync(dcmp, 0, 2 * sizeof(unsigned), c->stream) != hipSuccess ||
-          launch_max_abs_diff(ot, p.g.out0, ref, p.g.M, p.g.N, p.g.ldo, dcmp, c->stream) != hipSuccess ||
+          launch_max_abs_diff(ot, shown.out0, ref, p.g.M, p.g.N, p.g.ldo, dcmp, c->stream) != hipSuccess ||
           hipMemcpyAsync(h, dcmp, sizeof(h), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
           hipStreamSynchronize(c->stream) != hipSuccess)
         return INFINITY;
@@ -467,18 +482,19 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
       return (double)d / std::max((double)r, 1e-30);
     };
     int rejected = 0;
-    for (int cfg = 0; cfg < gemm_num_cfgs() && !rc; ++cfg) {
-      if (!gemm_cfg_supports(net->ct, cfg, p.acc64) || !gemm_cfg_tunable(net->ct, cfg)) continue;
+    for (int cfg = 0; cfg < (pk ? pk_num_cfgs(net->ct) : gemm_num_cfgs()) && !rc; ++cfg) {
+      if (!pk && (!gemm_cfg_supports(net->ct, cfg, p.acc64) || !gemm_cfg_tunable(net->ct, cfg))) continue;
       for (int ks : kss) {
-        GemmArgs g = p.g;
-        if (internal_launch_gemm_ks(net, g, p.acc64, p.splits, cfg, ks, c->stream) != hipSuccess) continue;
+        const GemmArgs& g = p.g;
+        if (pk && pk_slices(net->ct, cfg, g.K, ks) != ks) continue;
+        if (launch(g, cfg, ks) != hipSuccess) continue;
         // two rounds of five launches, the faster round counts (other work on
         // the device shifts single measurements by several percent)
         float ms = 1e30f;
         for (int round = 0; round < 2 && !rc; ++round) {
           hipEventRecord(e0, c->stream);
           const int reps = 5;
-          for (int r = 0; r < reps; ++r) internal_launch_gemm_ks(net, g, p.acc64, p.splits, cfg, ks, c->stream);
+          for (int r = 0; r < reps; ++r) launch(g, cfg, ks);
           hipEventRecord(e1, c->stream);
           if (hipEventSynchronize(e1) != hipSuccess) {
             rc = NNC_E_HIP;
@@ -490,6 +506,7 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
           ms = std::min(ms, t / reps);
         }
         if (rc) break;
+        if (shown.out0 != g.out0) launch(shown, cfg, ks);
         const double err = compare();
         if (err <= tol)
           timed.push_back(Trial{cfg, ks, ms, err});
@@ -508,6 +525,10 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
     const float best_ms = best.ms;
     for (const Trial& t : timed) {
       if (t.ms > 1.02f * best_ms) continue;
+      if (pk) {
+        if (t.ks < best.ks) best = t;
+        continue;
+      }
       const long long at = (long long)gemm_cfg(t.cfg).bm * gemm_cfg(t.cfg).bn;
       const long long ab = (long long)gemm_cfg(best.cfg).bm * gemm_cfg(best.cfg).bn;
       if (t.ks < best.ks || (t.ks == best.ks && at > ab)) best = t;
@@ -518,11 +539,13 @@ int nnc_autotune(nnc_ctx ctx, int id, int B) {
               "{\"arch\": \"gfx950\", \"dt\": %d, \"M\": %d, \"N\": %d, \"K\": %d, \"acc64\": %d, "
               "\"splits\": %d, \"cfg\": %d, \"name\": \"%s\", \"ms\": %.5f, \"ksplit\": %d, "
               "\"validated\": %s, \"max_rel_err\": %.3e, \"candidates\": %d, \"rejected\": %d}\n",
-              key.dt, key.M, key.N, key.K, key.acc64, key.splits, best.cfg, gemm_cfg(best.cfg).name, best.ms,
+              key.dt, key.M, key.N, key.K, key.acc64, key.splits, best.cfg, pk ? "packed" : gemm_cfg(best.cfg).name, best.ms,
               best.ks, have_ref ? "true" : "false", best.err, (int)timed.size() + rejected, rejected);
   }
   if (cache) fclose(cache);
-  internal_update_pk(c, net, true);
+  // other networks of this precision take the table's splits too
+  for (Net* n : c->nets)
+    if (!rc && n && n->ct == net->ct) rc = internal_size_part(c, n);
   c->prof = prof;
   hipEventDestroy(e0);
   hipEventDestroy(e1);

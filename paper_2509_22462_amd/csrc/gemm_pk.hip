@@ -851,6 +851,13 @@ PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes) {
   return best;
 }
 
+int pk_num_cfgs(DType t) { return pk_cfgs(t); }
+
+int pk_slices(DType t, int cfg, int K, int ks) {
+  const int kper = pk_kper(pk_cfg(t, cfg), K, ks);
+  return (K + kper - 1) / kper;
+}
+
 size_t pk_operand_bytes(DType t, long long rows, int K) {
   return (size_t)((rows + 15) / 16 * 16) * K * (t == DT_F32 ? 6 : t == DT_BF16 ? 2 : 8);
 }

@@ -143,6 +143,13 @@ struct PkChoice {
 // Tiling and K split for an M x N x K product whose K-split partials may take
 // part_bytes.
 PkChoice pk_choose(DType t, int M, int N, int K, size_t part_bytes);
+int pk_num_cfgs(DType t);
+// Most that the K-split partials of one packed product may take.  A fixed bound:
+// the choice of the split, and so the rounding of a result, must not depend on
+// what a network has allocated for other shapes.
+constexpr size_t kPkPartBytes = (size_t)64 << 20;
+// The K slices that a split into ks of whole stages of tiling cfg comes to.
+int pk_slices(DType t, int cfg, int K, int ks);
 size_t pk_operand_bytes(DType t, long long rows, int K);
 hipError_t launch_pack_operand(DType t, const void* W, long long ldw, int rows, int K, void* out, hipStream_t s);
 // One product in ksplit K slices (partials in part, added in slice order).
@@ -378,6 +385,7 @@ struct ProfRec {
 };
 
 // Tuned tiling per GEMM shape: (dtype, M, N, K, acc64, splits) -> config id.
+// (Packed sweep products: acc64 = splits = 0.)
 struct TuneKey {
   int dt, M, N, K, acc64, splits;
   bool operator<(const TuneKey& o) const {
@@ -451,8 +459,9 @@ int internal_seed(Ctx* c, Net* net, int B);
 hipError_t internal_launch_gemm_ks(Net* net, GemmArgs g, bool acc64, int splits, int cfg, int ks,
                                    hipStream_t s);
 bool internal_ksplit_ok(const Net* net, const GemmArgs& g, bool acc64, int splits);
-void internal_update_pk(Ctx* c, Net* net, bool allow);
 int internal_ensure_part(Ctx* c, Net* net, size_t bytes);
+int internal_size_part(Ctx* c, Net* net);
+PkChoice internal_pk_choice(const Ctx* c, DType t, const GemmArgs& g);
 int internal_finalize(Ctx* c, Net* net, int B, int splits, double obj, double* H, int symtile);
 // SoftMax output: the rank-two vectors from the output layer's tangents (after the forward sweep).
 int internal_softmax_uv(Ctx* c, Net* net, int B);

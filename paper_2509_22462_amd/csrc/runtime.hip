@@ -193,11 +193,15 @@ int ensure_part(Ctx* c, Net* net, size_t bytes) {
 
 int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out);
 
-// Most that the K-split partials of one packed product may take: the choice
-// of the split, and so the rounding of a result, must not depend on what the
-// network has allocated for other shapes.
 constexpr long long kFillTiles = 128;  // fill_ksplit
-constexpr size_t kPkPartBytes = (size_t)64 << 20;
+
+// Tiling and K split of a packed sweep product: the tuned table's, else the
+// estimate's.
+PkChoice pk_choice(const Ctx* c, DType t, int M, int N, int K) {
+  auto it = c->tuned.find(TuneKey{(int)t, M, N, K, 0, 0});
+  if (it == c->tuned.end()) return pk_choose(t, M, N, K, kPkPartBytes);
+  return PkChoice{it->second.cfg, it->second.ksplit};
+}
 
 // Workspace for the K splits the tuned table (or a forced split) asks for at
 // B = 1 and B = max_points.
@@ -226,7 +230,7 @@ int size_part(Ctx* c, Net* net) {
     for (int B = 1; B <= net->maxB; ++B)
       for (int l = 1; l < net->Lt; ++l) {
         const int M = B * net->n, N = net->ly[l].doutp;
-        const int ks = pk_choose(net->ct, M, N, net->ly[l].dinp, kPkPartBytes).ksplit;
+        const int ks = pk_choice(c, net->ct, M, N, net->ly[l].dinp).ksplit;
         if (ks > 1) need = std::max(need, (size_t)ks * M * N * part_size(net));
       }
   return ensure_part(c, net, need);
@@ -419,10 +423,9 @@ int pack_weights(Ctx* c, Net* net) {
 }
 
 // Whether the sweep runs on packed operands: whenever the network has them,
-// unless the caller forces a tiling or K split of the row-major kernels (or
-// `allow` is false: autotuning times those).
-void update_pk(Ctx* c, Net* net, bool allow) {
-  net->pk = allow && net->pk_bufs && net->hess_method == NNC_HESS_LAYERSUM && c->forced_cfg[net->ct] < 0 &&
+// unless the caller forces a tiling or K split of the row-major kernels.
+void update_pk(Ctx* c, Net* net) {
+  net->pk = net->pk_bufs && net->hess_method == NNC_HESS_LAYERSUM && c->forced_cfg[net->ct] < 0 &&
             c->forced_ksplit[net->ct] < 1;
 }
 
@@ -442,7 +445,7 @@ int fill_ksplit(const GemmArgs& g) {
 // workspace, on row-major operands where that does not fit beside packed ones.
 int finish_setup(Ctx* c, Net* net) {
   NNC_TRY(pack_weights(c, net));
-  update_pk(c, net, true);
+  update_pk(c, net);
   const int rc = size_part(c, net);
   if (rc != NNC_E_NOMEM || !net->pk_bufs) return rc;
   drop_packed(c, net);
@@ -492,7 +495,7 @@ int run_product(Ctx* c, Net* net, const PlannedGemm& p) {
     return NNC_OK;
   }
   if (p.pk) {
-    const PkChoice ch = pk_choose(net->ct, p.g.M, p.g.N, p.g.K, kPkPartBytes);
+    const PkChoice ch = pk_choice(c, net->ct, p.g.M, p.g.N, p.g.K);
     NNC_LAUNCH(c, NNC_KC_GEMM, launch_gemm_pk(net->ct, ch, p.g, net->part, c->stream));
     return NNC_OK;
   }
@@ -1664,7 +1667,7 @@ int nnc_set_gemm_config(nnc_ctx ctx, int prec, int config) {
   c->forced_cfg[dt] = config;
   free_batch(c);  // batched launches are planned with the tiling: re-plan on the next call
   for (Net* net : c->nets)
-    if (net) update_pk(c, net, true);
+    if (net) update_pk(c, net);
   return NNC_OK;
 }
 
@@ -1679,7 +1682,7 @@ int nnc_set_gemm_ksplit(nnc_ctx ctx, int prec, int ksplit) {
   free_batch(c);
   for (Net* net : c->nets)
     if (net && net->ct == t) {
-      update_pk(c, net, true);
+      update_pk(c, net);
       NNC_TRY(size_part(c, net));
     }
   return NNC_OK;
@@ -1772,7 +1775,8 @@ hipError_t internal_launch_gemm_ks(Net* net, GemmArgs g, bool acc64, int splits,
 bool internal_ksplit_ok(const Net* net, const GemmArgs& g, bool acc64, int splits) {
   return ksplit_ok(net, g, acc64, splits);
 }
-void internal_update_pk(Ctx* c, Net* net, bool allow) { update_pk(c, net, allow); }
+int internal_size_part(Ctx* c, Net* net) { return size_part(c, net); }
+PkChoice internal_pk_choice(const Ctx* c, DType t, const GemmArgs& g) { return pk_choice(c, t, g.M, g.N, g.K); }
 int internal_ensure_part(Ctx* c, Net* net, size_t bytes) { return ensure_part(c, net, bytes); }
 int internal_finalize(Ctx* c, Net* net, int B, int splits, double obj, double* H, int symtile) {
   return run_finalize(c, net, B, splits, obj, H, symtile);
