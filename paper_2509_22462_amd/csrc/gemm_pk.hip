@@ -975,7 +975,10 @@ hipError_t launch_gemm_pk_sym_grouped(DType t, int edge, const GemmArgs* groups,
 
 // Time of a round of tiles (32 elements of K: 1.1 / 3.6 us at edge 128 in
 // FP32 / FP64, 0.37 of it per tile at edge 64) against the partials
-// written and read back.  A slice keeps 128 elements or more.
+// written and read back.  A slice keeps 128 elements or more.  (The rounds take
+// no less than the tiles' time over all CUs: where that and the partials of sp
+// slices exceed the best, so do those of more.  A network is sized by asking for
+// every number of points up to max_points.)
 int pk_sym_splits(DType t, int n, int B, int K) {
   const int edge = pk_sym_edge(n);
   const double tt = (n + edge - 1) / edge;
@@ -983,9 +986,12 @@ int pk_sym_splits(DType t, int n, int B, int K) {
   const double us = (t == DT_F32 ? 1.1 : 3.6) * (edge == 128 ? 1.0 : 0.37);
   int best = 1;
   double best_us = 1e30;
+  const double least = tiles * (K / 32.0) * us / 256.0 * (1.0 - 1e-9);
   for (int sp = 1; sp <= 256 && (sp == 1 || K / sp >= 128); ++sp) {
     const double rounds = (double)(((long long)(tiles * sp) + 255) / 256);
-    const double c = rounds * (K / 32.0 / sp) * us + sp * (0.1 + (double)B * n * n * 16.0 / 4.5e6) + (sp > 16 ? 5.0 : 0.0);
+    const double parts = sp * (0.1 + (double)B * n * n * 16.0 / 4.5e6);
+    if (least + parts >= best_us) break;
+    const double c = rounds * (K / 32.0 / sp) * us + parts + (sp > 16 ? 5.0 : 0.0);
     if (c < best_us) {
       best_us = c;
       best = sp;

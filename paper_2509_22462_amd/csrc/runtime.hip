@@ -230,6 +230,7 @@ int size_part(Ctx* c, Net* net) {
     for (int B = 1; B <= net->maxB; ++B)
       for (int l = 1; l < net->Lt; ++l) {
         const int M = B * net->n, N = net->ly[l].doutp;
+        if ((size_t)2 * M * N * part_size(net) > kPkPartBytes) continue;  // never split
         const int ks = pk_choice(c, net->ct, M, N, net->ly[l].dinp).ksplit;
         if (ks > 1) need = std::max(need, (size_t)ks * M * N * part_size(net));
       }
