@@ -84,7 +84,7 @@ def gemm_source_sha():
     pkg = os.path.join(ROOT, "paper_2509_22462_amd")
     h = hashlib.sha256()
     for rel in ("csrc/gemm.hip", "csrc/gemm_kernels.h", "csrc/gemm_dma.hip", "csrc/gemm_common.h",
-                "csrc/gemm_pk.hip", "csrc/pk_device.h",
+                "csrc/gemm_pk.hip", "csrc/pk_device.h", "csrc/lds_dma.h",
                 "tuning/gfx950.jsonl"):
         h.update(open(os.path.join(pkg, rel), "rb").read())
     return h.hexdigest()[:16]

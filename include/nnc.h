@@ -32,9 +32,11 @@
  *     on the context's stream.
  *   - The library allocates device memory only in nnc_create, nnc_net_create
  *     and the nnc_train_* set-up calls — never inside an eval call.
- *   - Results are deterministic: identical inputs give bitwise-identical
+ *   - Results are deterministic: identical calls give bitwise-identical
  *     outputs (no floating-point atomics; split reductions are summed in a
- *     fixed order).
+ *     fixed order, and where they are split depends on the shapes of the call
+ *     and the tuning table alone).  A point's last bits may differ between
+ *     calls with other numbers of points, nnc_eval_batch, and after tuning.
  *   - Calls on one context must not overlap from several host threads.
  */
 #ifndef NNC_H

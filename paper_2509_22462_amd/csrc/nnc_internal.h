@@ -133,10 +133,11 @@ hipError_t launch_gemm_grouped(DType t, int cfg, bool acc64, const GemmArgs* gro
                                int ngroups, int grid, hipStream_t s);
 
 // ---------------------------------------------------------------- packed products
-// Layer-sum sweep products on packed operands (gemm_pk.hip; FP32 and BF16):
+// Layer-sum sweep products on packed operands (gemm_pk.hip):
 // g.A the packed tangents P_l [M][K], g.B the packed weights [N][K] (K and N
 // multiples of 64), epilogues EPI_FWD_LS / EPI_FWD_LT with out1 packed (ldo1 =
-// its K) and EPI_PART.
+// its K) and EPI_PART.  FP32 elements are three BF16 parts, and six of their
+// nine products are formed.
 struct PkChoice {
   int cfg, ksplit;
 };

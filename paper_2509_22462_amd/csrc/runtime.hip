@@ -253,8 +253,8 @@ void layersum_layout(Net* net) {
 // work items for about four workgroups per CU, at most 8 slices, whole K tiles.
 // Fewer than 64 tiles (one point of up to 640 inputs) would leave most CUs
 // without a workgroup at 8 slices: they take as many as make about two per CU,
-// each of 16 K tiles or more.  (117 inputs, K = 152,064, FP32: 3 tiles, 24 workgroups
-// at 8 slices: 522 -> 55 us.)
+// each of 16 K tiles or more.  (117 inputs, K = 152,064, FP32 without packed
+// operands: 3 tiles, 24 workgroups at 8 slices: 522 -> 55 us.)
 int ls_hsplits(const Net* net, int B) {
   const long long tt = (net->n + kSymTile - 1) / kSymTile;
   const long long tiles = (long long)B * tt * (tt + 1) / 2;
@@ -1120,8 +1120,7 @@ int run_tangents(Ctx* c, Net* net, int B, double obj, double* H) {
 // CUs with the sweep's GEMMs, which then run slower, so the streams' weight
 // bytes at HBM rate must take at least a quarter of one point's sweep flops
 // at the MFMA peak of its type (per point, so that every B below 64 takes
-// the same path and a point gets the same bits alone or in a batch).  Measured
-// with and without: 137M net FP32 448 vs 445 H/s (ratio 0.08: not taken), BF16
+// the same path).  Measured with and without: 137M net FP32 448 vs 445 H/s (ratio 0.08: not taken), BF16
 // 1576 -> 1683 (0.65); the deep, narrow net FP32 212 -> 242 (0.52), BF16 340 -> 445.
 bool sweep_overlap_ok(const Ctx* c, const Net* net, int B, bool jac) {
   if (!c->side || net->hess_method != NNC_HESS_LAYERSUM || net->Lt == 0) return false;
