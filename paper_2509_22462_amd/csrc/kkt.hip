@@ -28,7 +28,7 @@
 //
 // What bounds it: the chain of n / 64 panels, each with 64 dependent pivots;
 // the products (n^3 / 3 flops per system) run on v_mfma_f64_16x16x4_f64
-// beside it.  16 systems of 784: 569 us, where assembling M and three launches
+// beside it.  16 systems of 784: 557 us, where assembling M and three launches
 // per panel took 3,370 us.
 #include <math.h>
 
@@ -323,7 +323,7 @@ __device__ __forceinline__ void kkt_back_block(At at, Diag diag, int subs, int l
 // columns of L during the others'.  Wave 0 brings the next 16 x 16 block up to
 // date itself, so that only the solve with the block just factored stands
 // between two runs of pivots.  16 systems of 784: 42 us a panel when four waves
-// did both in turn, 34 us now.
+// did both in turn, 34 us then; 36 with the corrections of kkt_factor16's products.
 //
 // ONE: a single panel, solved here too (no panel before it to read).
 constexpr int kPanelThreads = 320;
