@@ -193,7 +193,19 @@ int ensure_part(Ctx* c, Net* net, size_t bytes) {
 
 int plan_tangents(Net* net, int B, std::vector<PlannedGemm>& out);
 
-constexpr long long kFillTiles = 128;  // fill_ksplit
+constexpr long long kFillTiles = 128;
+
+// K slices of a row-major product without a row in the tuned table: a few 64 x 64 tiles
+// run their K tiles one after the other on a few CUs, so below 128 tiles K is
+// split until there are about 256 workgroups, every slice keeping 128 elements
+// or more.  (70 Jacobian rows of the 784-1000-500-250-10 classifier, FP32: three
+// products 56 -> 33 us with their reductions.)  size_part reserves what this
+// asks for.
+int fill_ksplit(const GemmArgs& g) {
+  const long long tiles = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  if (tiles >= kFillTiles) return 1;
+  return (int)std::max<long long>(1, std::min<long long>({8, 256 / tiles, g.K / 128}));
+}
 
 // Tiling and K split of a packed sweep product: the tuned table's, else the
 // estimate's.
@@ -219,13 +231,30 @@ int size_part(Ctx* c, Net* net) {
       if (ks > 1) need = std::max(need, (size_t)ks * p.g.M * p.g.N * part_size(net));
     }
   }
-  // Products of few tiles (fill_ksplit): 8 slices of the largest with fewer than
-  // 128 tiles.  Reserved for every network, so that whether a product is split
-  // depends on the product alone, not on max_points or on earlier tuning.
-  size_t widest = 0;
-  for (const Layer& ly : net->ly) widest = std::max<size_t>(widest, std::max(ly.dinp, ly.doutp));
-  const size_t rows = (size_t)net->maxB * std::max(net->n, net->m);
-  need = std::max(need, 8 * std::min<size_t>(rows * widest, (size_t)kFillTiles * 64 * 64) * part_size(net));
+  // Products of few tiles (fill_ksplit), at every number of points that has such:
+  // whether one is split depends on the product alone, not on max_points or on
+  // earlier tuning.  (Packed sweeps have none; the Jacobian's run from 64 rows on.)
+  auto fill = [&](const GemmArgs& g) {
+    const int ks = fill_ksplit(g);
+    if (ks > 1) need = std::max(need, (size_t)ks * g.M * g.N * part_size(net));
+    return g.M <= 64 * kFillTiles;  // more points may still have fewer tiles than that
+  };
+  for (int B = 1, more = 1; more && B <= net->maxB; ++B) {
+    more = 0;
+    std::vector<PlannedGemm> plan;
+    NNC_TRY(plan_tangents(net, B, plan));
+    for (const PlannedGemm& p : plan)
+      if (!p.pk && ksplit_ok(net, p.g, p.acc64, p.splits)) more |= fill(p.g);
+    if (net->ct != net->at) continue;
+    if (B * net->m < 64) more = 1;
+    for (int l = 1; B * net->m >= 64 && l < net->L; ++l) {
+      GemmArgs g{};
+      g.M = B * net->m;
+      g.N = l == 1 ? net->n : net->ly[l - 1].dinp;
+      g.K = net->ly[l - 1].doutp;
+      more |= fill(g);
+    }
+  }
   if (net->pk_bufs)
     for (int B = 1; B <= net->maxB; ++B)
       for (int l = 1; l < net->Lt; ++l) {
@@ -428,18 +457,6 @@ int pack_weights(Ctx* c, Net* net) {
 void update_pk(Ctx* c, Net* net) {
   net->pk = net->pk_bufs && net->hess_method == NNC_HESS_LAYERSUM && c->forced_cfg[net->ct] < 0 &&
             c->forced_ksplit[net->ct] < 1;
-}
-
-// K slices of a row-major product without a row in the tuned table: a few 64 x 64 tiles
-// run their K tiles one after the other on a few CUs, so below 128 tiles K is
-// split until there are about 256 workgroups, every slice keeping 128 elements
-// or more.  (70 Jacobian rows of the 784-1000-500-250-10 classifier, FP32: three
-// products 56 -> 33 us with their reductions.)  size_part reserves the most this
-// can ask for.
-int fill_ksplit(const GemmArgs& g) {
-  const long long tiles = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-  if (tiles >= kFillTiles) return 1;
-  return (int)std::max<long long>(1, std::min<long long>({8, 256 / tiles, g.K / 128}));
 }
 
 // The last of a set-up: packed weights, the choice of operands and the K-split
